@@ -83,9 +83,12 @@ def measured_traffic(kernel, workload):
 # Timing-report names -> the HIP kernels they launch (demangled-name patterns), for reading
 # rocprofv3 output of the same run.
 KERNEL_PATTERNS = {
-    "gemm_nt_f16out": r"k_gemm_nt(_big|_lds)?<(\d+, \d+, )?0(, (true|false))?(, \d+)?(, (true|false))?>",
-    "gemm_nt_f32out": r"k_gemm_nt(_big|_lds)?<(\d+, \d+, )?1(, (true|false))?(, \d+)?(, (true|false))?>",
-    "gemm_nt_logits": r"k_gemm_nt(_big|_lds)?<(\d+, \d+, )?2(, (true|false))?(, \d+)?(, (true|false))?>",
+    "gemm_nt_f16out": r"k_gemm_nt(_big|_lds)?<(\d+, \d+, )?0(, (true|false))?(, \d+)?(, (true|false))?>"
+                      r"|k_gemm_nt_mid<(\d+, ){5}[03]>",
+    "gemm_nt_f32out": r"k_gemm_nt(_big|_lds)?<(\d+, \d+, )?1(, (true|false))?(, \d+)?(, (true|false))?>"
+                      r"|k_gemm_nt_mid<(\d+, ){5}1>",
+    "gemm_nt_logits": r"k_gemm_nt(_big|_lds)?<(\d+, \d+, )?2(, (true|false))?(, \d+)?(, (true|false))?>"
+                      r"|k_gemm_nt_mid<(\d+, ){5}2>",
     "gemm_tn_f32out": r"k_gemm_tn(_big|_lds)?<(\d+, )?0(, (true|false))?>",
     "gemm_tn_act_bwd": r"k_gemm_tn(_big|_lds)?<(\d+, )?1(, (true|false))?>",
     "gemm_tn_probs_dh": r"k_gemm_tn(_big|_lds)?<(\d+, )?2(, (true|false))?>",

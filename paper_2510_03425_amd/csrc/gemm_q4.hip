@@ -851,6 +851,7 @@ int gemm_splits(int tiles, int ktiles) {
 size_t gemm_part_floats(int M, int ncols, int splits) { return splits > 1 ? (size_t)splits * M * ncols : 0; }
 
 GemmPlan plan_nt(int M, const int* Ns, int nseg, int K, int epi) {
+  if (gemm_nt_mid_ok(K)) return GemmPlan{0, 0, 1};
   int t256 = 0, t128 = 0;
   for (int s = 0; s < nseg; ++s) {
     t256 += (Ns[s] + 255) / 256;
@@ -906,6 +907,13 @@ hipError_t launch_gemm_nt(const NtArgs& a0, int epi, hipStream_t st, hipEvent_t 
     if (ew != hipSuccess) return ew;
   }
   bool fused_act = false;
+  if (gemm_nt_mid_ok(a.K)) {
+    const hipError_t em = launch_gemm_nt_mid(a, epi, flops, bytes, st);
+    if (em != hipSuccess || epi == NT_LOGITS) return em;
+    if (a.norm_w)
+      return launch_rmsnorm_fwd((const float*)a.seg[0].out, a.norm_w, a.M, a.seg[0].N, a.eps, a.norm_out, nullptr, st);
+    return hipSuccess;
+  }
   if (plan.big) {
     fused_act = nt_gated_fused(a, epi, plan.bn, S);
     hipError_t eb = launch_gemm_nt_big(a, epi, plan.bn, S, flops, bytes, st);

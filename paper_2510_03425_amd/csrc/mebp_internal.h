@@ -84,6 +84,10 @@ GemmPlan plan_tn(int M, int Kout, const int* Ns, int nseg, bool softmax);  // so
 // statistics tiles per row of the LM-head logits GEMM over V columns (64 columns each)
 int gemm_logit_stat_tiles(int V);
 hipError_t launch_gemm_nt_big(const NtArgs& a, int epi, int bn, int S, double flops, double bytes, hipStream_t st);
+// the products of gemm_mid.hip (reductions that are a multiple of 64): one launch with every
+// epilogue of the arguments fused except the row norm
+bool gemm_nt_mid_ok(int K);
+hipError_t launch_gemm_nt_mid(const NtArgs& a, int epi, double flops, double bytes, hipStream_t st);
 // whether launch_gemm_nt_big forms z = act(g) * u of a gated product in its epilogue
 bool nt_gated_fused(const NtArgs& a, int epi, int bn, int S);
 

@@ -1,0 +1,50 @@
+"""GPU parity of the forward products' tile configurations (gemm_mid.hip) at the sizes where
+they can go wrong, through one layer's forward against the fp64 oracle: a single reduction step
+(more K ranges than steps), odd step counts, token and column counts that are no multiple of a
+tile, every tile shape that the cost model picks, RoPE over head dims 64 / 128 / 256 and
+positions that wrap inside a tile.
+
+Bound: the branch (x_out - x_in) is a sum of products of fp16 operands (relative rounding 2^-11
+each, a few in a row: norm, q / k / v, O, z) accumulated in fp32, so its rel-L2 error stays below
+a few 1e-3; a wrong row, column, step or head is an error of order one in some row.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from mebp_inputs import ALL7, Config, layer_input, make_inputs
+from paper_2510_03425_amd.device import DeviceModel
+
+from gpu_util import ROW_TOL, max_row_rel_l2, rel_l2, say
+
+pytestmark = pytest.mark.gpu
+
+# hidden, heads, kv heads, head dim, ffn, batch, tokens, act, rank
+CASES = [
+    (64, 1, 1, 64, 192, 1, 33, "silu", 8),        # one K step
+    (192, 3, 1, 64, 448, 2, 49, "gelu_tanh", 16),  # three and seven steps, positions wrap in a tile
+    (320, 2, 1, 128, 4864, 1, 129, "silu", 16),    # five steps; 129 = one row past a tile
+    (576, 3, 1, 256, 3008, 2, 515, "gelu_tanh", 8),  # nine and 47 steps, the widest tile
+    (896, 14, 2, 64, 1728, 1, 255, "silu", 8),     # fourteen steps, one row short of a tile
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=lambda c: f"d{c[0]}-dh{c[3]}-f{c[4]}-{c[5]}x{c[6]}")
+def test_layer_forward_tiles(built_lib, gpu, case):
+    d, h, kv, dh, f, b, t, act, r = case
+    cfg = Config(name="mid", n_layers=1, hidden=d, n_heads=h, n_kv_heads=kv, head_dim=dh, ffn=f, vocab=0, act=act,
+                 lora_rank=r, lora_alpha=2.0 * r, lora_modules=ALL7, batch=b, seq=t)
+    inp = make_inputs(cfg, seed=3, norm="random")
+    x, _ = layer_input(cfg, 11)
+    dm = DeviceModel(inp, device=str(gpu))
+    xi = torch.from_numpy(x).to(gpu)
+    xo = torch.full_like(xi, float("nan"))
+    say("forward tiles", case)
+    dm.layer_forward(0, xi, xo)
+    torch.cuda.synchronize()
+    got = xo.double().cpu().numpy() - x
+    ref = O.layer_forward(cfg, 0, O.decompress_layer(cfg, inp, 0), x) - x
+    err, row = rel_l2(got, ref), max_row_rel_l2(got, ref)
+    say("rel-L2", err, "worst row", row)
+    assert err <= 5e-3 and row <= ROW_TOL
