@@ -89,10 +89,10 @@ KERNEL_PATTERNS = {
                       r"|k_gemm_nt_mid<(\d+, ){5}1>",
     "gemm_nt_logits": r"k_gemm_nt(_big|_lds)?<(\d+, \d+, )?2(, (true|false))?(, \d+)?(, (true|false))?>"
                       r"|k_gemm_nt_mid<(\d+, ){5}2>",
-    "gemm_tn_f32out": r"k_gemm_tn(_big|_lds)?<(\d+, )?0(, (true|false))?>",
-    "gemm_tn_act_bwd": r"k_gemm_tn(_big|_lds)?<(\d+, )?1(, (true|false))?>",
-    "gemm_tn_probs_dh": r"k_gemm_tn(_big|_lds)?<(\d+, )?2(, (true|false))?>",
-    "gemm_tn_bf16out": r"k_gemm_tn(_big|_lds)?<(\d+, )?3(, (true|false))?>",
+    "gemm_tn_f32out": r"k_gemm_tn(_big|_lds)?<(\d+, )?0(, (true|false))?>|k_gemm_tn_frag<(\d+, ){3}0>",
+    "gemm_tn_act_bwd": r"k_gemm_tn(_big|_lds)?<(\d+, )?1(, (true|false))?>|k_gemm_tn_frag<(\d+, ){3}1>",
+    "gemm_tn_probs_dh": r"k_gemm_tn(_big|_lds)?<(\d+, )?2(, (true|false))?>|k_gemm_tn_frag<(\d+, ){3}2>",
+    "gemm_tn_bf16out": r"k_gemm_tn(_big|_lds)?<(\d+, )?3(, (true|false))?>|k_gemm_tn_frag<(\d+, ){3}3>",
     "lora_rows": r"k_lora_rows<",
     "lora_outer": r"k_lora_outer<",
     "attn_fwd": r"k_attn_fwd",

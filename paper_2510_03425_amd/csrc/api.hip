@@ -103,23 +103,31 @@ struct Layout {
   int lm_chunk;   // vocabulary columns per LM-head chunk
   int lm_splits;  // split-K factor of a whole chunk's dH product (narrower chunks use fewer)
   int ntiles;     // statistics tiles of a whole chunk (the stats row pitch)
-  size_t split_floats;
+  size_t split_floats, split_floats1;  // of the split-K scratch, and of its second copy
   size_t lora_part_floats;
-  size_t w16_elems;  // transient bf16 weights of the large-tile transposed products
+  // bf16 weights of the transposed products in fragment order: a layer's seven matrices, or one
+  // vocabulary chunk's; 0: left out (the products then decompress the int4 weights themselves)
+  size_t w16_elems;
 };
 
-size_t nt_part(int M, int K, std::initializer_list<int> Ns) {
+// Split planes of a forward product: gated (gate, up) and q | k | v have no row-norm follow-up,
+// the others may have one or not; of a transposed product: all but the activation backward have
+// one (see gemm_nt_mid_splits and gemm_tn_frag_splits).
+size_t nt_part(int M, int K, std::initializer_list<int> Ns, bool gated = false) {
   int v[3], n = 0, ncat = 0;
   for (int x : Ns) {
     v[n++] = x;
     ncat += x;
   }
-  return gemm_part_floats(M, ncat, plan_nt(M, v, n, K, NT_STORE_F32).splits);
+  if (!gemm_nt_mid_ok(K)) return gemm_part_floats(M, ncat, plan_nt(M, v, n, K, NT_STORE_F32).splits);
+  const int s0 = gemm_nt_mid_splits(M, v, n, K, gated, false), s1 = n > 1 ? s0 : gemm_nt_mid_splits(M, v, n, K, false, true);
+  return gemm_part_floats(M, ncat, s0 > s1 ? s0 : s1);
 }
-size_t tn_part(int M, int Kout, std::initializer_list<int> Ns) {
+size_t tn_part(int M, int Kout, std::initializer_list<int> Ns, bool followup, bool w16) {
   int v[3], n = 0;
   for (int x : Ns) v[n++] = x;
-  return gemm_part_floats(M, Kout, plan_tn(M, Kout, v, n, false).splits);
+  return gemm_part_floats(M, Kout, w16 ? gemm_tn_frag_splits(M, Kout, v, n, kMaxSplits, followup)
+                                       : plan_tn(M, Kout, v, n, false).splits);
 }
 
 // Columns of one LM-head vocabulary chunk: the chunk's fp16 logits [N][chunk] take at most
@@ -136,19 +144,9 @@ int lm_chunk_cols(size_t N, int V) {
   return c >= (size_t)V ? V : (int)c;
 }
 
-int lm_head_splits(int N, int d, int V) {
-  // token tiles are 256 rows in the large-tile kernel, 128 in the other
-  const int bm = plan_tn(N, d, &V, 1, true).big ? 256 : 128;
-  const int tiles = ((d + 127) / 128) * ((N + bm - 1) / bm);
-  int s = (512 + tiles - 1) / tiles;
-  const int max_s = ((V + 63) / 64 + 7) / 8;
-  if (s > max_s) s = max_s;
-  if (s > 64) s = 64;
-  if (s < 1) s = 1;
-  return s;
-}
+int lm_head_splits(int N, int d, int V) { return gemm_tn_frag_splits(N, d, &V, 1, kMaxHeadSplits, true); }
 
-bool make_layout(const mebp_config* c, int B, int T, Layout* L) {
+bool make_layout(const mebp_config* c, int B, int T, Layout* L, bool w16 = true) {
   const size_t N = (size_t)B * T, d = c->hidden, qd = (size_t)c->n_heads * c->head_dim,
                kvd = (size_t)c->n_kv_heads * c->head_dim, F = c->ffn, r = c->lora_rank > 0 ? c->lora_rank : 16,
                V = c->vocab, H = c->n_heads;
@@ -209,15 +207,19 @@ bool make_layout(const mebp_config* c, int B, int T, Layout* L) {
     auto mx = [&](size_t v) { m = v > m ? v : m; };
     mx(nt_part(M, D, {Q, KV, KV}));
     mx(nt_part(M, Q, {D}));
-    mx(nt_part(M, D, {FF, FF}));
+    mx(nt_part(M, D, {FF, FF}, true));
     mx(nt_part(M, FF, {D}));
-    mx(tn_part(M, FF, {D}));
-    mx(tn_part(M, D, {FF, FF}));
-    mx(tn_part(M, Q, {D}));
-    mx(tn_part(M, D, {Q, KV, KV}));
     // attention scratch for the sliding-window layers and the global ones
+    mx(attn_plan(B, T, c->n_heads, c->n_kv_heads, c->head_dim, c->window).fwd_floats);
+    mx(attn_plan(B, T, c->n_heads, c->n_kv_heads, c->head_dim, 0).fwd_floats);
+    // (the second copy serves a recompute: forward products and attention only)
+    L->split_floats1 = m;
     mx(attn_part_floats(B, T, c->n_heads, c->n_kv_heads, c->head_dim, c->window));
     mx(attn_part_floats(B, T, c->n_heads, c->n_kv_heads, c->head_dim, 0));
+    mx(tn_part(M, FF, {D}, false, w16));
+    mx(tn_part(M, D, {FF, FF}, true, w16));
+    mx(tn_part(M, Q, {D}, true, w16));
+    mx(tn_part(M, D, {Q, KV, KV}, true, w16));
     L->split_floats = m;
     sz[S_SPLIT] = m * 4;
     // every dB / dA launch of a layer: (widest column count, jobs)
@@ -229,14 +231,12 @@ bool make_layout(const mebp_config* c, int B, int T, Layout* L) {
       lp = v > lp ? v : lp;
     L->lora_part_floats = lp;
     sz[S_PART] = lp * 4;
-    // the transposed products of the backward (down, gate + up, o, q + k + v) and the LM
-    // head's dH product over one vocabulary chunk, one at a time
     size_t w = 0;
-    const int n_down[1] = {D}, n_gu[2] = {FF, FF}, n_o[1] = {D}, n_qkv[3] = {Q, KV, KV}, n_lm[1] = {(int)Vc};
-    for (size_t v : {gemm_tn_w16_elems(M, FF, n_down, 1, false), gemm_tn_w16_elems(M, D, n_gu, 2, false),
-                     gemm_tn_w16_elems(M, Q, n_o, 1, false), gemm_tn_w16_elems(M, D, n_qkv, 3, false),
-                     V ? gemm_tn_w16_elems(M, D, n_lm, 1, true) : (size_t)0})
-      w = v > w ? v : w;
+    if (w16) {
+      w = frag_elems(D, FF) + 2 * frag_elems(FF, D) + frag_elems(D, Q) + frag_elems(Q, D) + 2 * frag_elems(KV, D);
+      const size_t lm = V ? frag_elems((int)Vc, D) : 0;
+      w = lm > w ? lm : w;
+    }
     L->w16_elems = w;
     sz[S_W16] = w * 2;
   }
@@ -244,10 +244,10 @@ bool make_layout(const mebp_config* c, int B, int T, Layout* L) {
   L->guards = g_guards.load() != 0;
   L->nguard = 0;
   auto place = [&](int i, int copy) {
-    const size_t at = o;
-    o += ((sz[i] + 255) & ~(size_t)255) + (L->guards ? kGuardBytes : 0);
+    const size_t at = o, n = i == S_SPLIT && copy ? L->split_floats1 * 4 : sz[i];
+    o += ((n + 255) & ~(size_t)255) + (L->guards ? kGuardBytes : 0);
     if (L->guards) {
-      const size_t g = at + ((sz[i] + 3) & ~(size_t)3);
+      const size_t g = at + ((n + 3) & ~(size_t)3);
       L->g_off[L->nguard] = g;
       L->g_len[L->nguard] = (uint32_t)(o - g);
       L->g_tag[L->nguard] = i + S_COUNT * copy;
@@ -334,10 +334,10 @@ int guard_verdict(const Layout& L, void* ws, hipStream_t st) {
 // Runs `body` (the launches of one entry point on `stream`) between a fill and a check of
 // the guards when the layout has them; otherwise just runs it.
 template <class F>
-int guarded(const mebp_config* c, int B, int T, void* ws, mebp_stream_t stream, F&& body) {
+int guarded(const mebp_config* c, int B, int T, void* ws, mebp_stream_t stream, F&& body, bool w16 = true) {
   if (!g_guards.load()) return body();
   Layout L;
-  make_layout(c, B, T, &L);
+  make_layout(c, B, T, &L, w16);
   if (!L.guards) return body();
   int e = guard_launch(L, ws, (hipStream_t)stream, true);
   if (e || (e = body())) return e;
@@ -484,7 +484,7 @@ Tp* xs(const Ctx& x, int s) {
 SplitScratch split_scratch(const Ctx& x) {
   SplitScratch sc;
   sc.part = xs<float>(x, S_SPLIT);
-  sc.part_floats = x.L.split_floats;
+  sc.part_floats = x.split_set ? x.L.split_floats1 : x.L.split_floats;
   return sc;
 }
 
@@ -527,9 +527,27 @@ void set_scratch(const Ctx& x, TnArgs& t) {
   const SplitScratch sc = split_scratch(x);
   t.part = sc.part;
   t.part_floats = sc.part_floats;
-  // one copy: the transposed products run on the context's main stream, one after another
-  t.w16 = slot<uint16_t>(x.ws, x.L, S_W16);
-  t.w16_elems = x.L.w16_elems;
+}
+
+// The layer's weights in fragment order (one copy: the transposed products run on the context's
+// main stream, one after another), in the order down | gate, up | o | q, k, v: where the product
+// of projection p starts.
+const uint16_t* frag_weights(const Ctx& x, int p) {
+  if (!x.L.w16_elems) return nullptr;
+  static const int order[MEBP_NPROJ] = {MEBP_DOWN, MEBP_GATE, MEBP_UP, MEBP_O, MEBP_Q, MEBP_K, MEBP_V};
+  const uint16_t* w = slot<uint16_t>(x.ws, x.L, S_W16);
+  for (int i = 0; order[i] != p; ++i) w += frag_elems(x.D.out[order[i]], x.D.in[order[i]]);
+  return w;
+}
+hipError_t write_frag_weights(const Ctx& x, const mebp_layer_base* base, bool qkv) {
+  if (!x.L.w16_elems) return hipSuccess;
+  FragArgs f{};
+  for (int p : {MEBP_DOWN, MEBP_GATE, MEBP_UP, MEBP_O, MEBP_Q, MEBP_K, MEBP_V}) {
+    if (!qkv && p <= MEBP_V) continue;
+    f.seg[f.nseg++] = FragSeg{base->w[p].q4, base->w[p].scale, x.D.out[p], x.D.in[p],
+                              const_cast<uint16_t*>(frag_weights(x, p)), 0};
+  }
+  return launch_frag_weights(f, x.st);
 }
 
 TnSeg tn_seg(const Ctx& x, const mebp_layer_base* base, const mebp_layer_lora* lora, int p, const bf16* G) {
@@ -750,6 +768,7 @@ int layer_backward_only(const Ctx& x, int l, const mebp_layer_base* base, const 
   float* da = xs<float>(x, S_DA);
 
   const bool sandwich = c->arch & MEBP_ARCH_SANDWICH;
+  HIP_TRY(write_frag_weights(x, base, dx != nullptr));
   // y = h + down(z)   (sandwich: y = h + RMSNorm(t), t = down(z): the down projection's
   // gradient is the norm's backward of dy)
   bf16* gdown = dyb;
@@ -766,6 +785,7 @@ int layer_backward_only(const Ctx& x, int l, const mebp_layer_base* base, const 
     TnArgs t{};
     set_scratch(x, t);
     t.M = D.N; t.Kout = D.F; t.nseg = 1; t.r = D.r;
+    t.w16 = frag_weights(x, MEBP_DOWN);
     t.seg[0] = tn_seg(x, base, lora, MEBP_DOWN, gdown);
     t.g = g; t.u = u; t.ldgu = D.F; t.act = c->act;
     HIP_TRY(launch_gemm_tn(t, TN_ACT_BWD, TN_A_BF16, x.st, lr));  // g <- dg, u <- d(up)
@@ -778,6 +798,7 @@ int layer_backward_only(const Ctx& x, int l, const mebp_layer_base* base, const 
     TnArgs t{};
     set_scratch(x, t);
     t.M = D.N; t.Kout = D.d; t.nseg = 2; t.r = D.r;
+    t.w16 = frag_weights(x, MEBP_GATE);
     t.seg[0] = tn_seg(x, base, lora, MEBP_GATE, dg);
     t.seg[1] = tn_seg(x, base, lora, MEBP_UP, dup);
     t.out = dc; t.ldo = D.d;
@@ -797,6 +818,7 @@ int layer_backward_only(const Ctx& x, int l, const mebp_layer_base* base, const 
     TnArgs t{};
     set_scratch(x, t);
     t.M = D.N; t.Kout = D.qd; t.nseg = 1; t.r = D.r;
+    t.w16 = frag_weights(x, MEBP_O);
     t.seg[0] = tn_seg(x, base, lora, MEBP_O, go);
     t.outb = dO; t.ldo = D.qd;
     // the attention backward's delta = rowsum(dO * O) comes with dO
@@ -826,6 +848,7 @@ int layer_backward_only(const Ctx& x, int l, const mebp_layer_base* base, const 
     TnArgs t{};
     set_scratch(x, t);
     t.M = D.N; t.Kout = D.d; t.nseg = 3; t.r = D.r;
+    t.w16 = frag_weights(x, MEBP_Q);
     t.seg[0] = tn_seg(x, base, lora, MEBP_Q, dq);
     t.seg[1] = tn_seg(x, base, lora, MEBP_K, dk);
     t.seg[2] = tn_seg(x, base, lora, MEBP_V, dv);
@@ -897,7 +920,11 @@ int lm_head(const Ctx& x, const mebp_q4* emb, const float* norm_final, const flo
       t.seg[0].G = (const bf16*)logits; t.seg[0].ldg = Vc;
       t.seg[0].q4 = eq4; t.seg[0].scale = esc; t.seg[0].N = w;
       t.out = part; t.ldo = d; t.splits = lm_head_splits(N, d, w);
-      t.w16 = slot<uint16_t>(x.ws, x.L, S_W16); t.w16_elems = x.L.w16_elems;
+      uint16_t* wf = slot<uint16_t>(x.ws, x.L, S_W16);
+      FragArgs f{};
+      f.seg[f.nseg++] = FragSeg{eq4, esc, w, d, wf, 0};
+      HIP_TRY(launch_frag_weights(f, x.st));
+      t.w16 = wf;
       HIP_TRY(launch_gemm_tn(t, TN_PARTIAL_F32, TN_A_BF16, x.st));
       HIP_TRY(launch_ce_dh_accum(part, t.splits, N, d, alpha, first, dhf, x.st));
     }
@@ -908,14 +935,14 @@ int lm_head(const Ctx& x, const mebp_q4* emb, const float* norm_final, const flo
   return MEBP_OK;
 }
 
-Ctx make_ctx(const mebp_config* c, int B, int T, void* ws, mebp_stream_t stream) {
+Ctx make_ctx(const mebp_config* c, int B, int T, void* ws, mebp_stream_t stream, bool w16 = true) {
   Ctx x;
   x.c = c;
   x.D = dims(c, B, T);
   x.B = B;
   x.T = T;
   x.ws = ws;
-  make_layout(c, B, T, &x.L);
+  make_layout(c, B, T, &x.L, w16);
   x.st = (hipStream_t)stream;
   x.set = 0;
   x.split_set = 0;
@@ -1294,19 +1321,26 @@ int mebp_layer_recompute_backward_static(const mebp_config* cfg, int32_t layer, 
   // the layer's own slots only: the LM head's are not part of this call
   mebp_config c0 = *cfg;
   c0.vocab = 0;
-  const size_t need = mebp_workspace_bytes(&c0, B, T);
-  if (need > MEBP_STATIC_SCRATCH_BYTES)
-    return fail(MEBP_EWORKSPACE, "layer needs %zu bytes of scratch, more than the %zu the library holds", need,
+  // (without the fragment-ordered weights where the layer fits only then)
+  Layout L;
+  make_layout(&c0, B, T, &L);
+  const bool w16 = L.total <= MEBP_STATIC_SCRATCH_BYTES;
+  if (!w16) make_layout(&c0, B, T, &L, false);
+  if (L.total > MEBP_STATIC_SCRATCH_BYTES)
+    return fail(MEBP_EWORKSPACE, "layer needs %zu bytes of scratch, more than the %zu the library holds", L.total,
                 (size_t)MEBP_STATIC_SCRATCH_BYTES);
   void* ws = static_scratch();
   if (!ws) return MEBP_EHIP;
-  return guarded(&c0, B, T, ws, stream, [&] {
-    Ctx x = make_ctx(&c0, B, T, ws, stream);
-    float* rope;
-    int e2;
-    if ((e2 = rope_table(x, layer, &rope))) return e2;
-    return layer_backward(x, layer, base, lora, x_ckpt, dy, dx, grads, rope);
-  });
+  return guarded(
+      &c0, B, T, ws, stream,
+      [&] {
+        Ctx x = make_ctx(&c0, B, T, ws, stream, w16);
+        float* rope;
+        int e2;
+        if ((e2 = rope_table(x, layer, &rope))) return e2;
+        return layer_backward(x, layer, base, lora, x_ckpt, dy, dx, grads, rope);
+      },
+      w16);
 }
 
 int mebp_lm_head_ce_backward(const mebp_config* cfg, const mebp_q4* emb, const float* norm_final,

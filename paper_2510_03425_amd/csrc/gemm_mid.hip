@@ -120,6 +120,22 @@ DEV void load8(rsrc_t r, uint32_t off, bool keep, float s, float (&o)[8]) {
   o[6] = s * __builtin_bit_cast(float, b.z); o[7] = s * __builtin_bit_cast(float, b.w);
 }
 
+// Tile of this workgroup, numbered for the caches: every XCD gets a contiguous range (xcd_tile),
+// walked in bands of eight row blocks, the rows of a band fastest. The 64 workgroups that an XCD
+// runs at a time then cover 8 x 8 tiles, whose row and column operands are each fetched once
+// into its L2 for eight users.
+DEV TileId band_tile() {
+  const TileId t = xcd_tile();
+  const int gx = gridDim.x, gy = gridDim.y, lin = t.x + gx * t.y, band = lin / (8 * gx), r = lin - band * 8 * gx;
+  const int hgt = min(8, gy - 8 * band), x = r / hgt;
+  return TileId{x, 8 * band + r - x * hgt, t.z};
+}
+
+template <class T>
+DEV T sel(bool c, T x, T y) {
+  return c ? x : y;
+}
+
 // ------------------------------------------------------------------------------ forward
 // C[m][n] = sum_k X[m][k] W[n][k], fp16 operands, on 32 MI x 64 WN output tiles: WN waves of
 // 32 MI x 64 side by side, WK groups of them that split the reduction inside the workgroup.
@@ -134,7 +150,8 @@ DEV void load8(rsrc_t r, uint32_t off, bool keep, float s, float (&o)[8]) {
 // The two 32-column blocks of a wave are chosen by the epilogue that pairs them in registers:
 // the halves (e, e + dh/2) of a RoPE head, the gate and up columns of the same features, or
 // simply 64 consecutive columns.
-enum MidEpi { MID_F16 = 0, MID_F32 = 1, MID_LOGITS = 2, MID_GATED = 3 };
+// MID_PARTIAL: raw fp32 tiles into plane blockIdx.z of `part` (grid-split reductions).
+enum MidEpi { MID_F16 = 0, MID_F32 = 1, MID_LOGITS = 2, MID_GATED = 3, MID_PARTIAL = 4 };
 
 // The waits of the loop count vector-memory instructions, so every load that it issues must
 // have a use (the compiler drops the others): code rows (of CS) and scales (0 or 1) that step j
@@ -163,7 +180,7 @@ __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_nt_mid(const NtArgs a)
   static_assert(CS == 2 || CS == 4, "K steps per load of the codes");
   static_assert(WN == 1 || WK == 1, "a shared ring and a split reduction are not combined");
   static_assert(4 * MI % WN == 0, "the waves of a shared ring load equal parts of a stage");
-  static_assert(WK == 1 || (4 * MI) % WK == 0, "each wave finishes whole row groups");
+  static_assert(WK == 1 || (4 * MI) % WK == 0 || WK % (4 * MI) == 0, "waves finish whole row groups");
   __shared__ __attribute__((aligned(1024))) uint8_t lds0[WK * STB];
   __shared__ __attribute__((aligned(1024))) uint8_t lds1[WK * STB];
   __shared__ __attribute__((aligned(1024))) uint8_t lds2[ST == 4 ? WK * STB : 16];
@@ -174,6 +191,7 @@ __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_nt_mid(const NtArgs a)
     constexpr int st = decltype(S_)::value;
     return (st == 0 ? lds0 : st == 1 ? lds1 : st == 2 ? lds2 : lds3) + wk * STB;
   };
+  // (plain order: every XCD keeps a few columns' weights; bands measured the same here)
   const int m0 = blockIdx.y * BM, K = a.K, Kh = K >> 1, kgroups = K >> 5;
   // this wave's two column blocks: weight rows c[j] .. c[j] + 32 of segment sj
   int s0 = 0, s1 = 0, c0, c1;
@@ -204,7 +222,8 @@ __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_nt_mid(const NtArgs a)
   const rsrc_t rS1 = make_rsrc(SEG(s1, scale) + (size_t)min(c1, Nn) * kgroups, (size_t)r1 * kgroups * 2);
   // (ranges of a split reduction start on even steps: whole 64-byte pieces of the code rows)
   const int nk = K / BK, np = (nk + 1) >> 1;
-  const int kt_begin = 2 * (np * wk / WK), kt_end = min(nk, 2 * (np * (wk + 1) / WK));
+  const int z = EPI == MID_PARTIAL ? (int)blockIdx.z * WK + wk : wk, Z = EPI == MID_PARTIAL ? (int)gridDim.z * WK : WK;
+  const int kt_begin = 2 * (np * z / Z), kt_end = min(nk, 2 * (np * (z + 1) / Z));
 
   // activation loads: instruction i fills rows 8 (wn + WN i) .. + 8 of the group's stage
   uint32_t offA[NA];
@@ -312,7 +331,7 @@ __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_nt_mid(const NtArgs a)
   if (kt_begin < kt_end) {
     // the LoRA term starts the accumulators while the first tiles are in flight (of a split
     // reduction: those of the last group, whose range is never empty)
-    const bool lora0 = (WK == 1 || wk == WK - 1) && EPI != MID_LOGITS && SEG(s0, lora_B);
+    const bool lora0 = (WK == 1 || wk == WK - 1) && EPI != MID_LOGITS && EPI != MID_PARTIAL && SEG(s0, lora_B);
     const bool lora1 = EPI == MID_GATED ? (WK == 1 || wk == WK - 1) && a.seg[1].lora_B : lora0;
     load_codes(IC<0>{}, IC<CS>{}, kt_begin);
     load_scales(IC<0>{}, kt_begin);
@@ -440,12 +459,12 @@ __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_nt_mid(const NtArgs a)
   // residual) go through buffer resources based at row m0: rows past M and columns past the
   // segment are dropped (or read 0) by the bounds check, without branches.
   const int n0 = c0 + l32, n1 = c1 + l32, rows = min(BM, a.M - m0);
-  constexpr int ESZ = EPI == MID_F32 ? 4 : 2;
-  const int ldo = SEG(s0, ldo), rope = EPI == MID_F16 ? SEG(s0, rope) : 0;
+  constexpr int ESZ = EPI == MID_F32 || EPI == MID_PARTIAL ? 4 : 2;
+  const int ldo = EPI == MID_PARTIAL ? a.ldp : SEG(s0, ldo), rope = EPI == MID_F16 ? SEG(s0, rope) : 0;
   auto out_rsrc = [&](void* base, int ld) {
     return make_rsrc((char*)base + (size_t)m0 * ld * ESZ, ((size_t)(rows - 1) * ld + Nn) * ESZ);
   };
-  const rsrc_t rO = out_rsrc(SEG(s0, out), ldo);
+  const rsrc_t rO = out_rsrc(EPI == MID_PARTIAL ? (void*)(a.part + (size_t)blockIdx.z * a.M * a.ldp + SEG(s0, col0)) : SEG(s0, out), ldo);
   const uint32_t o0 = n0 < Nn ? (uint32_t)(4 * h * ldo + n0) * ESZ : 0x80000000u;
   const uint32_t o1 = n1 < Nn ? (uint32_t)(4 * h * ldo + n1) * ESZ : 0x80000000u;
   const rsrc_t rO1 = EPI == MID_GATED ? out_rsrc(a.seg[1].out, a.seg[1].ldo) : rO;
@@ -512,8 +531,9 @@ __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_nt_mid(const NtArgs a)
           st16(rO, o1, so, v1[r]);
         }
       } else {
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v0[r] + x.x0[r]), rO, o0, so, 0);
-        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v1[r] + x.x1[r]), rO, o1, so, 0);
+        const float y0 = EPI == MID_F32 ? v0[r] + x.x0[r] : v0[r], y1 = EPI == MID_F32 ? v1[r] + x.x1[r] : v1[r];
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, y0), rO, o0, so, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, y1), rO, o1, so, 0);
       }
     }
   };
@@ -542,7 +562,11 @@ __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_nt_mid(const NtArgs a)
         p0[(i * 16 + q) * 64] = acc[i][0][q];
         p1[(i * 16 + q) * 64] = acc[i][1][q];
       }
-    constexpr int GPW = 4 * MI / WK;  // row groups per wave
+    constexpr int GPW = WK > 4 * MI ? 1 : 4 * MI / WK;  // row groups per wave
+    if (WK > 4 * MI && wk >= 4 * MI) {
+      __syncthreads();
+      return;
+    }
     Extra x[GPW];
 #pragma unroll
     for (int gi = 0; gi < GPW; ++gi) fetch((wk * GPW + gi) >> 2, (wk * GPW + gi) & 3, x[gi]);
@@ -572,24 +596,394 @@ __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_nt_mid(const NtArgs a)
 }
 
 
-// Tile configurations and their cost model: `fix` microseconds of launch, first loads and
-// epilogue, then per K step of a wave `lat` while a compute unit has one workgroup at most and
-// `thr` per workgroup when it has several. Measured on 27 products of 128 .. 16384 tokens with
-// reductions of 896 .. 10240 (each configuration timed on each): the estimate is within about
-// 15 % and picks the fastest configuration or one within 6 % of it.
+// ---------------------------------------------------------------------------- transposed
+// C[m][c] = sum_seg sum_n G_seg[m][n] W_seg[n][c], bf16 operands, on weights that a pass just
+// before wrote as bf16 in the order in which the MFMA reads them: for every K step (64 rows n of
+// a segment) and every 32 columns four 1 KiB blocks, block t holding for lane l the eight rows
+// 32 (l / 32) + 8 t .. + 8 of column l % 32, as 16 bytes at 16 l. Rows past a segment and columns
+// past Kout are zero. A wave's fragment is then one coalesced 1 KiB load straight into the
+// registers of the MFMA: the weights pass through neither LDS nor a transpose, and LDS carries
+// the gradient tile alone. What bounds the many-token products is the power-limited MFMA rate
+// (1.0 .. 1.15 PFLOP/s; a large plain bf16 product of the library reaches 1.2), at few tokens the
+// fetch of the weights by a few workgroups. Against the kernels they replace (us, conversion pass
+// included, same GPU): activation backward of the 2560-wide shape at 16384 tokens 1258 + 17 ->
+// 913 + 13, its gate/up input gradient 1963 + 33 -> 1679 + 25, its LM-head dH product per
+// 16384-column chunk 1433 + 26 -> 1374 + 20; at 999 tokens of the 896-wide shape activation
+// backward 85 -> 20 + 5, gate/up input gradient 107 -> 32 + 6; at 512 tokens of the 1152-wide one
+// 94 -> 41 + 10. Converting a whole layer at once instead of product by product saves four
+// launches.
+constexpr int kFragBlock = 1024;
+
+// bf16 of q * s (rounded to nearest even) in fragment order; one thread per 8 rows x 8 columns.
+// Bound by its writes: 2 bytes per weight beside 0.56 read; a wave's 64 x 64 block is put in
+// order in LDS, so that its stores are consecutive (52 million weights: 42 us with each lane
+// storing its own 128 bytes, 25 us so, 5.5 TB/s).
+__global__ __launch_bounds__(256) void k_frag_weights(const FragArgs a) {
+  __shared__ uint4 buf[4][512];
+  const int bid = blockIdx.x, lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+  int s = 0;
+  while (s + 1 < a.nseg && a.seg[s + 1].blk0 <= bid) ++s;
+  const FragSeg sg = a.seg[s];
+  // one wave per 64 rows x 64 columns; the four waves of a workgroup side by side
+  const int nc = (sg.cols + 63) / 64, nr = (sg.N + BK - 1) / BK;
+  const int tile = (bid - sg.blk0) * 4 + w, kt = tile / nc, cb = tile - kt * nc;
+  if (kt >= nr) return;
+  const int r8 = lane >> 3, c8 = lane & 7, n0 = BK * kt + 8 * r8, c0 = 64 * cb + 8 * c8;
+  const int Kh = sg.cols >> 1, kg = (sg.cols + 31) >> 5;
+  const rsrc_t rQ = make_rsrc(sg.q4, (size_t)sg.N * Kh), rS = make_rsrc(sg.scale, (size_t)sg.N * kg * 2);
+  uint32_t q[8], sc[8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    // rows past N are past the resource and read 0; columns past the width are masked
+    q[e] = bload32(rQ, c0 < sg.cols ? (uint32_t)((n0 + e) * Kh + (c0 >> 1)) : 0x80000000u);
+    sc[e] = bload16(rS, c0 < sg.cols ? (uint32_t)((n0 + e) * kg + (c0 >> 5)) * 2 : 0x80000000u);
+  }
+  float v[8][8];
+#pragma unroll
+  for (int e = 0; e < 8; ++e)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[e][j] = (float)nib_s(q[e], j) * half_bits_to_f32((uint16_t)sc[e]);
+  // 16-byte unit (column block c8 / 4, block t = r8 % 4, half r8 / 4, column 8 (c8 % 4) + j); the
+  // low bits of j are XORed with c8, so that the eight lanes of one LDS cycle hit all banks
+  const int u0 = (c8 >> 2) * 256 + (r8 & 3) * 64 + (r8 >> 2) * 32 + (c8 & 3) * 8;
+#pragma unroll
+  for (int j = 0; j < 8; ++j)
+    buf[w][u0 + (j ^ c8)] = make_uint4(pack_bf16x2(v[0][j], v[1][j]), pack_bf16x2(v[2][j], v[3][j]),
+                                       pack_bf16x2(v[4][j], v[5][j]), pack_bf16x2(v[6][j], v[7][j]));
+  uint4* dst = (uint4*)sg.out + ((size_t)kt * nc + cb) * 512;
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int u = 64 * i + lane, c = (i >> 2) * 4 + ((lane >> 3) & 3);
+    dst[u] = buf[w][u ^ c];
+  }
+}
+
+// Tiles of 32 MI x 64 WN with WK K ranges as in the forward kernel. NT epilogues of TnEpi; with
+// WK = 1 the 16-bit ones go through LDS, 16 rows at a time, so that a lane moves 8 consecutive
+// columns of a row (16-byte accesses instead of 2-byte ones in the MFMA layout).
+template <int MI, int WN, int WK, int EPI>
+__global__ __launch_bounds__(64 * WN * WK, MI > 4 ? 1 : 2) void k_gemm_tn_frag(const TnArgs a) {
+  constexpr int NJ = 2, BM = 32 * MI, NA = 4 * MI / WN, STB = BM * BK * 2;
+  static_assert(WN == 1 || WK == 1, "a shared ring and a split reduction are not combined");
+  static_assert(4 * MI % WN == 0, "the waves of a shared ring load equal parts of a stage");
+  static_assert(WK == 1 || (4 * MI) % WK == 0 || WK % (4 * MI) == 0, "waves finish whole row groups");
+  __shared__ __attribute__((aligned(1024))) uint8_t lds0[WK * STB];
+  __shared__ __attribute__((aligned(1024))) uint8_t lds1[WK * STB];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wn = WN > 1 ? wave : 0, wk = WK > 1 ? wave : 0, h = lane >> 5, l32 = lane & 31;
+  auto stage = [&](auto S_) -> uint8_t* { return (decltype(S_)::value == 0 ? lds0 : lds1) + wk * STB; };
+  const TileId tl = band_tile();
+  const int m0 = tl.y * BM, Kout = a.Kout, ct = tl.x * WN + wn, c0 = 64 * ct, rows = min(BM, a.M - m0);
+  const int ncb = (Kout + 63) / 64 * 2;
+  // K steps before the second, before the third segment and in all
+  const int e0 = (a.seg[0].N + BK - 1) / BK, e1 = e0 + (a.nseg > 1 ? (a.seg[1].N + BK - 1) / BK : 0),
+            total = e1 + (a.nseg > 2 ? (a.seg[2].N + BK - 1) / BK : 0);
+  const int z = tl.z * WK + wk, Z = gridDim.z * WK;
+  const int t_begin = (int)((long long)total * z / Z), t_end = (int)((long long)total * (z + 1) / Z);
+  // (selected per step by value: a conditional on the variables themselves selects an address and
+  // keeps them in scratch memory)
+  const int ld0 = a.seg[0].ldg, ld1 = a.seg[1].ldg, ld2 = a.seg[2].ldg;
+  const int N0 = a.seg[0].N, N1 = a.seg[1].N, N2 = a.seg[2].N;
+  const u16* G0 = (const u16*)a.seg[0].G + (size_t)m0 * ld0;
+  const u16* G1 = (const u16*)a.seg[1].G + (size_t)m0 * ld1;
+  const u16* G2 = (const u16*)a.seg[2].G + (size_t)m0 * ld2;
+  const rsrc_t rB = make_rsrc(a.w16, ct * 2 < ncb ? (size_t)total * ncb * 4 * kFragBlock : 0);
+  const uint32_t offB = (uint32_t)(ct * 8 * kFragBlock + 16 * lane);
+  uint4 rb[2][NJ][4];
+  auto load_a = [&](auto S_, int t) {
+    const bool i0 = t < e0, i1 = t < e1;
+    const int ldg = sel(i0, ld0, sel(i1, ld1, ld2)), Ns = sel(i0, N0, sel(i1, N1, N2));
+    const int n0 = (t - sel(i0, 0, sel(i1, e0, e1))) * BK;
+    const rsrc_t ra = make_rsrc(sel(i0, G0, sel(i1, G1, G2)), (size_t)rows * ldg * 2);
+    lds_u8* dst = (lds_u8*)stage(S_);
+    // instruction i: rows row0 + 8 WN i .. + 8, whose chunk order depends on the parity of the
+    // row block; columns past the segment read as zero (the sign bit puts the offset out of range)
+    const int row0 = 8 * wn + (lane >> 3);
+    uint32_t vo[2];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const int n = n0 + 8 * ((lane & 7) ^ (((row0 + 8 * WN * p) >> 1) & 7));
+      vo[p] = (uint32_t)(row0 * ldg + n) * 2 | ((uint32_t)(Ns - 1 - n) & 0x80000000u);
+    }
+#pragma unroll
+    for (int i = 0; i < NA; ++i) load_lds16(ra, dst + 1024 * (wn + WN * i), vo[WN % 2 ? i & 1 : 0], 16 * WN * i * ldg);
+    __builtin_amdgcn_sched_barrier(0);  // the waits count the weights as issued after the tile
+  };
+  auto load_b = [&](auto B_, int t) {
+    constexpr int bf = decltype(B_)::value;
+    const uint32_t so = (uint32_t)t * (uint32_t)ncb * (4 * kFragBlock);
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) rb[bf][j][q] = bload128s(rB, offB + (4 * j + q) * kFragBlock, so);
+  };
+  f32x16 acc[MI][NJ];
+#pragma unroll
+  for (int i = 0; i < MI; ++i)
+#pragma unroll
+    for (int j = 0; j < NJ; ++j)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
+  auto mma = [&](auto S_, const uint4 (&b)[NJ][4]) {
+    const uint8_t* As = stage(S_) + l32 * 128;
+    auto rd = [&](int t, uint4 (&dst)[MI]) {
+      const int pos = ((4 * h + t) ^ ((lane >> 1) & 7)) * 16;
+#pragma unroll
+      for (int i = 0; i < MI; ++i) dst[i] = *(const uint4*)(As + 4096 * i + pos);
+    };
+    uint4 af[2][MI];
+    rd(0, af[0]);
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      if (t < 3) rd(t + 1, af[(t + 1) & 1]);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int i = 0; i < MI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) acc[i][j] = mfma32<OpBF16>(af[t & 1][i], b[j][t], acc[i][j]);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  };
+  // step: the next tile's gradient rows and weights in flight during this one's MFMAs; ends when
+  // this wave's (and, through a shared ring, every wave's) gradient rows have landed
+  auto step = [&](auto I_, int t) {
+    constexpr int I = decltype(I_)::value;
+    const int tn = min(t + 1, t_end - 1);
+    load_a(IC<1 - I>{}, tn);
+    load_b(IC<1 - I>{}, tn);
+    mma(IC<I>{}, rb[I]);
+    wait_vmcnt<4 * NJ>();
+    if constexpr (WN > 1) __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  if (t_begin < t_end) {
+    load_a(IC<0>{}, t_begin);
+    load_b(IC<0>{}, t_begin);
+    // the LoRA term du A of every segment starts the accumulators (of the last K range)
+    if (EPI != TN_PARTIAL_F32 && z == Z - 1) {
+      const int q0 = 8 * h, r = a.r;
+      const bool keep = q0 < r;
+      for (int s = 0; s < a.nseg; ++s) {
+        const float* A = a.seg[s].lora_A;
+        if (!A) continue;
+        const rsrc_t rV = make_rsrc(A, (size_t)r * Kout * 4), rU = make_rsrc(a.seg[s].lora_du, (size_t)a.M * r * 4);
+        float u[MI][8], v[NJ][8];
+#pragma unroll
+        for (int j = 0; j < NJ; ++j) {
+          const int c = c0 + 32 * j + l32;
+#pragma unroll
+          for (int e = 0; e < 8; ++e)
+            v[j][e] = __builtin_bit_cast(
+                float, bload32(rV, keep && c < Kout ? (uint32_t)((q0 + e) * Kout + c) * 4 : 0x80000000u));
+        }
+#pragma unroll
+        for (int i = 0; i < MI; ++i) load8(rU, (uint32_t)(((m0 + 32 * i + l32) * r + q0) * 4), keep, 1.f, u[i]);
+        lora_acc<MI, NJ>(acc, u, v);
+      }
+    }
+    wait_vmcnt<0>();
+    if constexpr (WN > 1) __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    int t = t_begin;
+    for (; t + 2 <= t_end; t += 2) {
+      step(IC<0>{}, t);
+      step(IC<1>{}, t + 1);
+    }
+    if (t < t_end) mma(IC<0>{}, rb[0]);
+  }
+  wait_vmcnt<0>();
+
+  // fp32 outputs: column lane % 32 of both blocks, rows 32 i + 8 qg + 4 h + (0..3), through a
+  // buffer resource based at row m0 (rows past M and columns past Kout are dropped)
+  const int n0 = c0 + l32, n1 = n0 + 32;
+  const int ldo = EPI == TN_ACT_BWD ? a.ldgu : a.ldo;
+  const size_t osz = ((size_t)(rows - 1) * ldo + Kout);
+  if constexpr (WK == 1 && (EPI == TN_ACT_BWD || EPI == TN_STORE_BF16)) {
+    constexpr int LDE = (WN + 1) / 2 * (16 * 68 * 4) <= STB ? 68 : 64;
+    __syncthreads();  // every wave is done with the ring
+    static_assert((WN + 1) / 2 * (16 * LDE * 4) <= STB, "staging regions");
+    float* ep = reinterpret_cast<float*>((wave & 1 ? lds1 : lds0) + (wave >> 1) * (16 * LDE * 4));
+    const int rr = lane >> 3, ch = lane & 7, c = c0 + 8 * ch;
+    const bool cok = c < Kout;  // (a multiple of 8: a lane's 8 columns are inside or past it)
+    const rsrc_t r0 = make_rsrc((u16*)(EPI == TN_ACT_BWD ? a.g : a.outb) + (size_t)m0 * ldo, osz * 2);
+    const rsrc_t r1 = make_rsrc(EPI == TN_ACT_BWD ? (u16*)a.u + (size_t)m0 * ldo : nullptr, EPI == TN_ACT_BWD ? osz * 2 : 0);
+    auto off = [&](int row) { return cok ? (uint32_t)(row * ldo + c) * 2 : 0x80000000u; };
+    auto put = [&](rsrc_t r, uint32_t o, uint4 v) {
+      typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+      const u32x4 x = {v.x, v.y, v.z, v.w};
+      __builtin_amdgcn_raw_buffer_store_b128(x, r, (int)o, 0, 0);
+    };
+    auto run = [&](auto K_) {
+      constexpr int KIND = decltype(K_)::value;
+#pragma unroll
+      for (int ih = 0; ih < 2 * MI; ++ih) {
+        uint4 gw[2], uw[2];
+        if constexpr (EPI == TN_ACT_BWD) {
+#pragma unroll
+          for (int p = 0; p < 2; ++p) {
+            gw[p] = bload128(r0, off(16 * ih + 8 * p + rr));
+            uw[p] = bload128(r1, off(16 * ih + 8 * p + rr));
+          }
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+#pragma unroll
+          for (int j = 0; j < NJ; ++j)
+            ep[(8 * (q >> 2) + 4 * h + (q & 3)) * LDE + 32 * j + l32] = acc[ih >> 1][j][8 * (ih & 1) + q];
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+          const int r = 8 * p + rr;
+          const float4 v0 = *(const float4*)(ep + r * LDE + 8 * ch), v1 = *(const float4*)(ep + r * LDE + 8 * ch + 4);
+          const float dz[8] = {v0.x, v0.y, v0.z, v0.w, v1.x, v1.y, v1.z, v1.w};
+          uint32_t o[4], ou[4];
+          if constexpr (EPI == TN_ACT_BWD) {
+            // dz -> dg = dz u act'(g), du = dz act(g), in place over g and u
+            const uint32_t gq[4] = {gw[p].x, gw[p].y, gw[p].z, gw[p].w}, uq[4] = {uw[p].x, uw[p].y, uw[p].z, uw[p].w};
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+              float a0, d0, a1, d1;
+              act_and_grad<KIND>(f16_lo(gq[k]), a0, d0);
+              act_and_grad<KIND>(f16_hi(gq[k]), a1, d1);
+              o[k] = pack_bf16x2(dz[2 * k] * f16_lo(uq[k]) * d0, dz[2 * k + 1] * f16_hi(uq[k]) * d1);
+              ou[k] = pack_bf16x2(dz[2 * k] * a0, dz[2 * k + 1] * a1);
+            }
+            put(r1, off(16 * ih + r), make_uint4(ou[0], ou[1], ou[2], ou[3]));
+          } else {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) o[k] = pack_bf16x2(dz[2 * k], dz[2 * k + 1]);
+          }
+          put(r0, off(16 * ih + r), make_uint4(o[0], o[1], o[2], o[3]));
+        }
+      }
+    };
+    if (EPI == TN_ACT_BWD && a.act)
+      run(IC<1>{});
+    else
+      run(IC<0>{});
+    return;
+  }
+  const size_t plane = EPI == TN_PARTIAL_F32 ? (size_t)tl.z * a.M * ldo : 0;
+  const rsrc_t rO = EPI == TN_ACT_BWD      ? make_rsrc((u16*)a.g + (size_t)m0 * ldo, osz * 2)
+                    : EPI == TN_STORE_BF16 ? make_rsrc((u16*)a.outb + (size_t)m0 * ldo, osz * 2)
+                                           : make_rsrc(a.out + plane + (size_t)m0 * ldo, osz * 4);
+  const rsrc_t rU = EPI == TN_ACT_BWD ? make_rsrc((u16*)a.u + (size_t)m0 * ldo, osz * 2) : rO;
+  constexpr int ESZ = EPI == TN_STORE_F32 || EPI == TN_PARTIAL_F32 ? 4 : 2;
+  const uint32_t o0 = n0 < Kout ? (uint32_t)(4 * h * ldo + n0) * ESZ : 0x80000000u;
+  const uint32_t o1 = n1 < Kout ? (uint32_t)(4 * h * ldo + n1) * ESZ : 0x80000000u;
+  auto st16 = [&](rsrc_t r, uint32_t vo, int so, float v) {
+    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, to_bf16(v)), r, vo, so, 0);
+  };
+  auto ld16 = [&](rsrc_t r, uint32_t vo, int so) {
+    return (float)__builtin_bit_cast(f16, (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(r, (int)vo, so, 0));
+  };
+  auto emit = [&](int i, int qg, const float (&v0)[4], const float (&v1)[4]) {
+    const int row = 32 * i + 8 * qg;
+    float g0[4], g1[4], u0[4], u1[4];
+    if constexpr (EPI == TN_ACT_BWD) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int so = (row + r) * ldo * 2;
+        g0[r] = ld16(rO, o0, so);
+        g1[r] = ld16(rO, o1, so);
+        u0[r] = ld16(rU, o0, so);
+        u1[r] = ld16(rU, o1, so);
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int so = (row + r) * ldo * ESZ;
+      if constexpr (EPI == TN_ACT_BWD) {
+        st16(rO, o0, so, v0[r] * u0[r] * act_grad_f(g0[r], a.act));
+        st16(rO, o1, so, v1[r] * u1[r] * act_grad_f(g1[r], a.act));
+        st16(rU, o0, so, v0[r] * act_f(g0[r], a.act));
+        st16(rU, o1, so, v1[r] * act_f(g1[r], a.act));
+      } else if constexpr (EPI == TN_STORE_BF16) {
+        st16(rO, o0, so, v0[r]);
+        st16(rO, o1, so, v1[r]);
+      } else {
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v0[r]), rO, o0, so, 0);
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, v1[r]), rO, o1, so, 0);
+      }
+    }
+  };
+  if constexpr (WK == 1) {
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int qg = 0; qg < 4; ++qg) {
+        const float v0[4] = {acc[i][0][4 * qg], acc[i][0][4 * qg + 1], acc[i][0][4 * qg + 2], acc[i][0][4 * qg + 3]};
+        const float v1[4] = {acc[i][1][4 * qg], acc[i][1][4 * qg + 1], acc[i][1][4 * qg + 2], acc[i][1][4 * qg + 3]};
+        emit(i, qg, v0, v1);
+      }
+  } else {
+    // the K ranges' partial tiles through the idle rings, summed in range order
+    float* p0 = reinterpret_cast<float*>(lds0) + wk * (STB / 4) + lane;
+    float* p1 = reinterpret_cast<float*>(lds1) + wk * (STB / 4) + lane;
+#pragma unroll
+    for (int i = 0; i < MI; ++i)
+#pragma unroll
+      for (int q = 0; q < 16; ++q) {
+        p0[(i * 16 + q) * 64] = acc[i][0][q];
+        p1[(i * 16 + q) * 64] = acc[i][1][q];
+      }
+    __syncthreads();
+    constexpr int GPW = WK > 4 * MI ? 1 : 4 * MI / WK;
+    if (WK > 4 * MI && wk >= 4 * MI) return;
+#pragma unroll
+    for (int gi = 0; gi < GPW; ++gi) {
+      const int g = wk * GPW + gi, i = g >> 2, qg = g & 3;
+      const float* b0 = reinterpret_cast<const float*>(lds0) + (i * 16 + 4 * qg) * 64 + lane;
+      const float* b1 = reinterpret_cast<const float*>(lds1) + (i * 16 + 4 * qg) * 64 + lane;
+      float v0[4], v1[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        v0[r] = b0[64 * r];
+        v1[r] = b1[64 * r];
+      }
+#pragma unroll
+      for (int z2 = 1; z2 < WK; ++z2)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          v0[r] += b0[z2 * (STB / 4) + 64 * r];
+          v1[r] += b1[z2 * (STB / 4) + 64 * r];
+        }
+      emit(i, qg, v0, v1);
+    }
+  }
+}
+
+// Tile configurations and their cost model, in microseconds: `fix` of launch, first loads and
+// epilogue, then per K step of a wave `lat` while a compute unit has one workgroup at most, or
+// for each workgroup that it has `thr` per step and `wg` that no other one hides. Fitted to 27
+// forward products of 128 .. 16384 tokens with reductions of 896 .. 10240 and 25 transposed ones
+// with reductions of 688 .. 20480, each configuration timed on each: mostly within 15 % of the
+// measured times, and the pick is the fastest configuration or one within 10 % of it. A
+// reduction may also be split over the grid (S planes, summed by the finalize kernel that also
+// applies the product's follow-up): a wave has 1 / S of the steps, at the cost of the planes'
+// traffic at 3 TB/s and, where no follow-up kernel would have run anyway, of one more launch.
+// (More K ranges inside a workgroup, 8 or 16 of 32 x 64, gain nothing: the compute unit's cache
+// then bounds the tile.)
 struct MidCfg {
   int mi, wn, wk;
-  float fix, lat, thr;
+  float fix, lat, thr, wg;
 };
-constexpr MidCfg kMid[] = {
-    {4, 4, 1, 7.0f, 0.90f, 0.98f},  // 128 x 256: many tiles
-    {4, 1, 4, 5.0f, 1.20f, 1.56f},  // 128 x 64, four K ranges: about 256 tiles
-    {2, 1, 8, 6.0f, 1.40f, 1.70f},  // 64 x 64, eight K ranges: long reductions, few tiles
-    {2, 1, 4, 5.0f, 0.80f, 0.85f},
-    {2, 1, 2, 4.0f, 0.78f, 0.43f},
-    {1, 1, 4, 3.5f, 0.50f, 0.53f},  // 32 x 64: the fewest tokens
+constexpr MidCfg kMidNt[] = {
+    {4, 4, 1, 7.0f, 0.90f, 0.98f, 0.0f},  // 128 x 256: many tiles
+    {4, 1, 4, 5.0f, 1.20f, 1.36f, 4.0f},  // 128 x 64, four K ranges: about 256 tiles
+    {2, 1, 8, 6.0f, 1.40f, 1.70f, 0.0f},  // 64 x 64, eight K ranges: long reductions, few tiles
+    {2, 1, 4, 5.0f, 0.80f, 0.85f, 0.0f},
+    {2, 1, 2, 4.0f, 0.78f, 0.43f, 0.0f},
+    {1, 1, 4, 3.5f, 0.50f, 0.53f, 0.0f},  // 32 x 64: the fewest tokens
 };
-constexpr int kMidCount = sizeof(kMid) / sizeof(kMid[0]);
+constexpr MidCfg kMidTn[] = {
+    {4, 4, 1, 7.0f, 0.86f, 1.04f, 0.0f}, {4, 1, 4, 5.0f, 1.10f, 1.40f, 2.0f},
+    {2, 1, 8, 6.0f, 1.30f, 1.31f, 2.2f}, {2, 1, 4, 4.5f, 0.72f, 0.67f, 0.8f},
+    {2, 1, 2, 4.0f, 0.65f, 0.37f, 0.7f}, {1, 1, 4, 3.5f, 0.50f, 0.52f, 0.0f},
+    {2, 4, 1, 5.0f, 0.54f, 0.57f, 1.0f},  // 64 x 256
+};
+struct MidPlan {
+  int cfg, splits;
+};
 
 int mid_columns(const MidCfg& c, const int* Ns, int nseg, bool gated) {
   if (gated) return (Ns[0] + 32 * c.wn - 1) / (32 * c.wn);
@@ -598,58 +992,120 @@ int mid_columns(const MidCfg& c, const int* Ns, int nseg, bool gated) {
   return t;
 }
 
-int mid_pick(int M, const int* Ns, int nseg, int K, bool gated, bool logits) {
-  int best = 0;
+// columns(c): workgroup columns of configuration c; unit: K steps that a range is a multiple of;
+// width: output columns (the planes); followup: a finalize kernel costs no extra launch
+template <class F>
+MidPlan mid_plan(const MidCfg* cfgs, int n, int M, int ksteps, int unit, int max_s, int width, bool followup, F columns) {
+  MidPlan best{0, 1};
   float bt = 1e30f;
-  for (int i = 0; i < kMidCount; ++i) {
-    const MidCfg& c = kMid[i];
-    if (logits && i) break;  // (whose statistics take whole rows of a wave)
-    const int tiles = mid_columns(c, Ns, nseg, gated) * ((M + 32 * c.mi - 1) / (32 * c.mi));
-    const int pairs = (K / BK + 1) / 2, steps = 2 * ((pairs + c.wk - 1) / c.wk), per = (tiles + 255) / 256;
-    const float t = c.fix + steps * (per <= 1 ? c.lat : per * c.thr);
-    if (t < bt) {
-      bt = t;
-      best = i;
+  for (int i = 0; i < n; ++i) {
+    const MidCfg& c = cfgs[i];
+    const int base = columns(c) * ((M + 32 * c.mi - 1) / (32 * c.mi));
+    for (int S = 1; S <= max_s; S = S < 4 ? S + 1 : S + S / 2) {
+      if (S > 1 && S * c.wk * 2 > ksteps) break;  // two steps per wave at least
+      const int units = (ksteps + unit - 1) / unit, steps = unit * ((units + c.wk * S - 1) / (c.wk * S));
+      const long long tiles = (long long)base * S;
+      const float per = (float)((tiles + 255) / 256), one = steps * c.lat, many = per * (steps * c.thr + c.wg);
+      float t = c.fix + (per > 1.f && many > one ? many : one);
+      if (S > 1) t += 1.5f + 8e-6f / 3.f * S * M * width + (followup ? 0.f : 4.5f);
+      if (t < bt) {
+        bt = t;
+        best = MidPlan{i, S};
+      }
     }
   }
   return best;
 }
 
+MidPlan mid_plan_nt(int M, const int* Ns, int nseg, int K, bool gated, bool logits, bool followup) {
+  int width = 0;
+  for (int s = 0; s < nseg; ++s) width += Ns[s];
+  // (the logits' statistics take whole rows of a wave: the widest tile)
+  return mid_plan(kMidNt, logits ? 1 : (int)(sizeof(kMidNt) / sizeof(MidCfg)), M, K / BK, 2, logits ? 1 : kMaxSplits, width,
+                  followup, [&](const MidCfg& c) { return mid_columns(c, Ns, nseg, gated); });
+}
+
+MidPlan mid_plan_tn(int M, int Kout, const int* Ns, int nseg, int max_s, bool followup) {
+  int kt = 0;
+  for (int s = 0; s < nseg; ++s) kt += (Ns[s] + BK - 1) / BK;
+  return mid_plan(kMidTn, (int)(sizeof(kMidTn) / sizeof(MidCfg)), M, kt, 1, max_s, Kout, followup,
+                  [&](const MidCfg& c) { return (Kout + 64 * c.wn - 1) / (64 * c.wn); });
+}
+
 }  // namespace
+
+size_t frag_elems(int N, int cols) {
+  return (size_t)((N + BK - 1) / BK * BK) * (size_t)((cols + 63) / 64 * 64);
+}
+
+hipError_t launch_frag_weights(FragArgs a, hipStream_t st) {
+  long long blocks = 0;
+  double bytes = 0;
+  for (int s = 0; s < a.nseg; ++s) {
+    FragSeg& g = a.seg[s];
+    if (g.cols % 8) return hipErrorInvalidValue;
+    g.blk0 = (int)blocks;
+    const size_t n = frag_elems(g.N, g.cols);
+    blocks += (long long)((n / 4096 + 3) / 4);
+    bytes += 2.0 * n + (double)g.N * (g.cols / 2 + 2 * ((g.cols + 31) / 32));
+  }
+  if (!blocks) return hipSuccess;
+  MEBP_TIMED(st, "frag_weights", 0.0, bytes,
+             hipLaunchKernelGGL(k_frag_weights, dim3((unsigned)blocks), dim3(256), 0, st, a));
+  return hipGetLastError();
+}
 
 bool gemm_nt_mid_ok(int K) { return K % BK == 0; }
 
-hipError_t launch_gemm_nt_mid(const NtArgs& a0, int epi, double flops, double bytes, hipStream_t st) {
+int gemm_nt_mid_splits(int M, const int* Ns, int nseg, int K, bool gated, bool followup) {
+  return mid_plan_nt(M, Ns, nseg, K, gated, false, followup).splits;
+}
+
+int gemm_tn_frag_splits(int M, int Kout, const int* Ns, int nseg, int max_s, bool followup) {
+  return mid_plan_tn(M, Kout, Ns, nseg, max_s, followup).splits;
+}
+
+hipError_t launch_gemm_nt_mid(const NtArgs& a0, int epi, int S, double flops, double bytes, hipStream_t st) {
   NtArgs a = a0;
   if (a.K % BK || a.lda % 8 || ((uintptr_t)a.X & 15)) return hipErrorInvalidValue;
   int Ns[3];
   for (int s = 0; s < a.nseg; ++s) Ns[s] = a.seg[s].N;
-  const int pick = mid_pick(a.M, Ns, a.nseg, a.K, a.gated, epi == NT_LOGITS);
-  const MidCfg& c = kMid[pick];
+  const bool logits = epi == NT_LOGITS, gated = a.gated && S == 1;
+  // the tile for S planes was planned with them; without (or after the caller dropped them) plan anew
+  MidPlan p = mid_plan_nt(a.M, Ns, a.nseg, a.K, a.gated, logits, a.norm_w != nullptr);
+  if (p.splits != S) {
+    int width = 0;
+    for (int s = 0; s < a.nseg; ++s) width += Ns[s];
+    p = mid_plan(kMidNt, logits ? 1 : (int)(sizeof(kMidNt) / sizeof(MidCfg)), a.M, a.K / BK, 2, 1, width, true,
+                 [&](const MidCfg& c) { return mid_columns(c, Ns, a.nseg, gated); });
+  }
+  const MidCfg& c = kMidNt[p.cfg];
   int t = 0;
   for (int s = 0; s < a.nseg; ++s) {
     a.seg[s].tile0 = t;
     t += (a.seg[s].N + 64 * c.wn - 1) / (64 * c.wn);
   }
-  const dim3 grid(mid_columns(c, Ns, a.nseg, a.gated), (a.M + 32 * c.mi - 1) / (32 * c.mi));
+  const dim3 grid(mid_columns(c, Ns, a.nseg, gated), (a.M + 32 * c.mi - 1) / (32 * c.mi), S);
   const char* name = epi == NT_STORE_F16 ? "gemm_nt_f16out" : epi == NT_STORE_F32 ? "gemm_nt_f32out" : "gemm_nt_logits";
 #define MID_GO(MI, WN, WK, EPI) \
   MEBP_TIMED(st, name, flops, bytes, \
              hipLaunchKernelGGL((k_gemm_nt_mid<MI, WN, WK, 2, 2, EPI>), grid, dim3(64 * WN * WK), 0, st, a))
 #define MID_EPI(MI, WN, WK)              \
   do {                                   \
-    if (a.gated)                         \
+    if (S > 1)                           \
+      MID_GO(MI, WN, WK, MID_PARTIAL);   \
+    else if (gated)                      \
       MID_GO(MI, WN, WK, MID_GATED);     \
     else if (epi == NT_STORE_F16)        \
       MID_GO(MI, WN, WK, MID_F16);       \
     else                                 \
       MID_GO(MI, WN, WK, MID_F32);       \
   } while (0)
-  if (epi == NT_LOGITS) {
+  if (logits) {
     MID_GO(4, 4, 1, MID_LOGITS);
     return hipGetLastError();
   }
-  switch (pick) {
+  switch (p.cfg) {
     case 0: MID_EPI(4, 4, 1); break;
     case 1: MID_EPI(4, 1, 4); break;
     case 2: MID_EPI(2, 1, 8); break;
@@ -659,6 +1115,57 @@ hipError_t launch_gemm_nt_mid(const NtArgs& a0, int epi, double flops, double by
   }
 #undef MID_EPI
 #undef MID_GO
+  return hipGetLastError();
+}
+
+hipError_t launch_gemm_tn_frag(const TnArgs& a, int epi, int S, double flops, double bytes, hipStream_t st) {
+  int Ns[3];
+  for (int s = 0; s < a.nseg; ++s) {
+    Ns[s] = a.seg[s].N;
+    if (a.seg[s].N % 8 || a.seg[s].ldg % 8 || ((uintptr_t)a.seg[s].G & 15)) return hipErrorInvalidValue;
+  }
+  if (a.Kout % 8 || !a.w16) return hipErrorInvalidValue;
+  // the tile from the plan that chose S planes; a plan of one plane where the caller dropped them
+  MidPlan p = mid_plan_tn(a.M, a.Kout, Ns, a.nseg, epi == TN_PARTIAL_F32 ? kMaxHeadSplits : kMaxSplits,
+                          epi == TN_PARTIAL_F32 || tn_followup(a, epi));
+  if (p.splits != S) p = mid_plan_tn(a.M, a.Kout, Ns, a.nseg, 1, true);
+  const MidCfg& c = kMidTn[p.cfg];
+  const int e = S > 1 ? TN_PARTIAL_F32 : epi;
+  TnArgs b = a;
+  if (S > 1 && epi != TN_PARTIAL_F32) {
+    b.out = a.part;
+    b.ldo = a.Kout;
+  }
+  const dim3 grid((a.Kout + 64 * c.wn - 1) / (64 * c.wn), (a.M + 32 * c.mi - 1) / (32 * c.mi), S);
+  const char* name = epi == TN_PARTIAL_F32 ? "gemm_tn_probs_dh"
+                     : epi == TN_STORE_F32  ? "gemm_tn_f32out"
+                     : epi == TN_ACT_BWD    ? "gemm_tn_act_bwd"
+                                            : "gemm_tn_bf16out";
+#define FRAG_GO(MI, WN, WK, EPI) \
+  MEBP_TIMED(st, name, flops, bytes, \
+             hipLaunchKernelGGL((k_gemm_tn_frag<MI, WN, WK, EPI>), grid, dim3(64 * WN * WK), 0, st, b))
+#define FRAG_EPI(MI, WN, WK)                   \
+  do {                                         \
+    if (e == TN_PARTIAL_F32)                   \
+      FRAG_GO(MI, WN, WK, TN_PARTIAL_F32);     \
+    else if (e == TN_STORE_F32)                \
+      FRAG_GO(MI, WN, WK, TN_STORE_F32);       \
+    else if (e == TN_ACT_BWD)                  \
+      FRAG_GO(MI, WN, WK, TN_ACT_BWD);         \
+    else                                       \
+      FRAG_GO(MI, WN, WK, TN_STORE_BF16);      \
+  } while (0)
+  switch (p.cfg) {
+    case 0: FRAG_EPI(4, 4, 1); break;
+    case 1: FRAG_EPI(4, 1, 4); break;
+    case 2: FRAG_EPI(2, 1, 8); break;
+    case 3: FRAG_EPI(2, 1, 4); break;
+    case 4: FRAG_EPI(2, 1, 2); break;
+    case 5: FRAG_EPI(1, 1, 4); break;
+    default: FRAG_EPI(2, 4, 1); break;
+  }
+#undef FRAG_EPI
+#undef FRAG_GO
   return hipGetLastError();
 }
 

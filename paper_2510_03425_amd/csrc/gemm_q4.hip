@@ -897,7 +897,8 @@ hipError_t launch_gemm_nt(const NtArgs& a0, int epi, hipStream_t st, hipEvent_t 
   int Ns[3];
   for (int s = 0; s < a.nseg; ++s) Ns[s] = a.seg[s].N;
   const GemmPlan plan = plan_nt(a.M, Ns, a.nseg, a.K, epi);
-  int S = plan.splits;
+  const bool mid = gemm_nt_mid_ok(a.K);
+  int S = !mid ? plan.splits : epi == NT_LOGITS ? 1 : gemm_nt_mid_splits(a.M, Ns, a.nseg, a.K, a.gated, a.norm_w);
   if (S > 1 && (!a.part || a.part_floats < gemm_part_floats(a.M, ncat, S))) S = 1;
   if (a.norm_w && a.seg[0].N > 4096) S = 1;  // the fused row norm keeps a row in one workgroup
   a.ldp = ncat;
@@ -907,14 +908,16 @@ hipError_t launch_gemm_nt(const NtArgs& a0, int epi, hipStream_t st, hipEvent_t 
     if (ew != hipSuccess) return ew;
   }
   bool fused_act = false;
-  if (gemm_nt_mid_ok(a.K)) {
-    const hipError_t em = launch_gemm_nt_mid(a, epi, flops, bytes, st);
+  if (mid) {
+    const hipError_t em = launch_gemm_nt_mid(a, epi, S, flops, bytes, st);
     if (em != hipSuccess || epi == NT_LOGITS) return em;
-    if (a.norm_w)
-      return launch_rmsnorm_fwd((const float*)a.seg[0].out, a.norm_w, a.M, a.seg[0].N, a.eps, a.norm_out, nullptr, st);
-    return hipSuccess;
-  }
-  if (plan.big) {
+    if (S == 1) {
+      // every follow-up but the row norm is in the product's epilogue
+      if (a.norm_w)
+        return launch_rmsnorm_fwd((const float*)a.seg[0].out, a.norm_w, a.M, a.seg[0].N, a.eps, a.norm_out, nullptr, st);
+      return hipSuccess;
+    }
+  } else   if (plan.big) {
     fused_act = nt_gated_fused(a, epi, plan.bn, S);
     hipError_t eb = launch_gemm_nt_big(a, epi, plan.bn, S, flops, bytes, st);
     if (eb != hipSuccess) return eb;
@@ -971,13 +974,6 @@ hipError_t launch_gemm_nt(const NtArgs& a0, int epi, hipStream_t st, hipEvent_t 
   return hipGetLastError();
 }
 
-size_t gemm_tn_w16_elems(int M, int Kout, const int* Ns, int nseg, bool softmax) {
-  if (!plan_tn(M, Kout, Ns, nseg, softmax).big) return 0;
-  size_t n = 0;
-  for (int s = 0; s < nseg; ++s) n += (size_t)Ns[s] * Kout;
-  return n;
-}
-
 hipError_t launch_gemm_tn(const TnArgs& a0, int epi, int amode, hipStream_t st, hipEvent_t lora_ready) {
   if (amode != TN_A_BF16) return hipErrorInvalidValue;
   if (a0.delta && (epi != TN_STORE_BF16 || !a0.delta_o || a0.delta_T <= 0 || a0.M % a0.delta_T ||
@@ -1000,7 +996,7 @@ hipError_t launch_gemm_tn(const TnArgs& a0, int epi, int amode, hipStream_t st, 
   if (epi == TN_PARTIAL_F32) {
     S = a.splits;
   } else {
-    S = plan.splits;
+    S = a.w16 ? gemm_tn_frag_splits(a.M, a.Kout, Ns, a.nseg, kMaxSplits, tn_followup(a, epi)) : plan.splits;
     if (S > 1 && (!a.part || a.part_floats < gemm_part_floats(a.M, a.Kout, S))) S = 1;
     if (a.out2 && a.Kout > 4096) S = 1;
   }
@@ -1008,31 +1004,15 @@ hipError_t launch_gemm_tn(const TnArgs& a0, int epi, int amode, hipStream_t st, 
   bytes += epi == TN_STORE_BF16 ? 2 * outb : epi == TN_ACT_BWD ? 8 * outb
          : epi == TN_PARTIAL_F32 ? 4 * outb * S : 4 * outb;
   dim3 grid(ct, mt, S);
-  // the large-tile kernel on a transient bf16 copy of the weights (written before the wait
-  // for the LoRA projection, so the two may overlap)
-  bool w16 = false;
-  if (plan.big && a.w16) {
-    size_t need = 0;
-    for (int s = 0; s < a.nseg; ++s) need += (size_t)a.seg[s].N * a.Kout;
-    if (need <= a.w16_elems) {
-      size_t off = 0;
-      for (int s = 0; s < a.nseg; ++s) {
-        const hipError_t ed =
-            launch_dequant(a.seg[s].q4, a.seg[s].scale, a.seg[s].N, a.Kout, 32, nullptr, a.w16 + off, st);
-        if (ed != hipSuccess) return ed;
-        a.seg[s].q4 = reinterpret_cast<const uint8_t*>(a.w16 + off);
-        a.seg[s].scale = nullptr;
-        off += (size_t)a.seg[s].N * a.Kout;
-      }
-      w16 = true;
-    }
-  }
   if (lora_ready && S == 1) {
     const hipError_t ew = hipStreamWaitEvent(st, lora_ready, 0);
     if (ew != hipSuccess) return ew;
   }
-  if (plan.big) {
-    hipError_t eb = launch_gemm_tn_big(a, epi, amode, plan.bn, S, flops, bytes, st, w16);
+  if (a.w16) {
+    const hipError_t ef = launch_gemm_tn_frag(a, epi, S, flops, bytes, st);
+    if (ef != hipSuccess) return ef;
+  } else if (plan.big) {
+    hipError_t eb = launch_gemm_tn_big(a, epi, amode, plan.bn, S, flops, bytes, st);
     if (eb != hipSuccess) return eb;
   } else {
     switch (epi) {

@@ -87,7 +87,12 @@ hipError_t launch_gemm_nt_big(const NtArgs& a, int epi, int bn, int S, double fl
 // the products of gemm_mid.hip (reductions that are a multiple of 64): one launch with every
 // epilogue of the arguments fused except the row norm
 bool gemm_nt_mid_ok(int K);
-hipError_t launch_gemm_nt_mid(const NtArgs& a, int epi, double flops, double bytes, hipStream_t st);
+hipError_t launch_gemm_nt_mid(const NtArgs& a, int epi, int S, double flops, double bytes, hipStream_t st);
+// planes that the reduction of such a product is split into (followup: its finalize kernel
+// replaces a row-norm launch)
+int gemm_nt_mid_splits(int M, const int* Ns, int nseg, int K, bool gated, bool followup);
+// the transposed products on fragment-ordered weights (TnArgs::w16)
+int gemm_tn_frag_splits(int M, int Kout, const int* Ns, int nseg, int max_s, bool followup);
 // whether launch_gemm_nt_big forms z = act(g) * u of a gated product in its epilogue
 bool nt_gated_fused(const NtArgs& a, int epi, int bn, int S);
 
@@ -137,20 +142,36 @@ struct TnArgs {
   float* out2;
   bf16* out2b;
   float eps;
-  // optional scratch for a transient bf16 copy of the segments' weights: when the large-tile
-  // kernel is chosen and sum_seg N_seg * Kout <= w16_elems, the weights are decompressed
-  // into it first (bf16 of q * s, rounded to nearest even, [N_seg][Kout] back to back) and
-  // the kernel reads them without decompressing (identical operands, identical results)
-  uint16_t* w16;
-  size_t w16_elems;
+  // bf16 weights of the segments in fragment order (launch_frag_weights), back to back; null:
+  // the kernels that decompress the int4 weights themselves
+  const uint16_t* w16;
 };
+hipError_t launch_gemm_tn_frag(const TnArgs& a, int epi, int S, double flops, double bytes, hipStream_t st);
+// whether a product has a follow-up that its finalize kernel does (the row norm's backward or
+// the attention backward's delta) and that is a launch of its own otherwise
+inline bool tn_followup(const TnArgs& a, int epi) {
+  return (epi == TN_STORE_F32 && a.out2) || (epi == TN_STORE_BF16 && a.delta);
+}
+// most planes of a layer product, and of the LM head's dH product
+constexpr int kMaxSplits = 8, kMaxHeadSplits = 64;
+// bf16 weights in MFMA fragment order (gemm_mid.hip): one matrix [N][cols] of a table
+struct FragSeg {
+  const uint8_t* q4;
+  const uint16_t* scale;
+  int N, cols;
+  uint16_t* out;
+  int blk0;              // set by the launcher
+};
+struct FragArgs {
+  FragSeg seg[7];
+  int nseg;
+};
+// elements of one matrix in that order (rows and columns rounded up to 64)
+size_t frag_elems(int N, int cols);
+hipError_t launch_frag_weights(FragArgs a, hipStream_t st);
 hipError_t launch_gemm_tn(const TnArgs& a, int epi, int amode, hipStream_t st, hipEvent_t lora_ready = nullptr);
-// w16: seg.q4 points at bf16 weights [N][Kout] (no scales)
 hipError_t launch_gemm_tn_big(const TnArgs& a, int epi, int amode, int bn, int S, double flops, double bytes,
-                              hipStream_t st, bool w16 = false);
-// bf16 elements of the transient weight copy that launch_gemm_tn would use for these
-// segments (0 when the large-tile kernel is not chosen)
-size_t gemm_tn_w16_elems(int M, int Kout, const int* Ns, int nseg, bool softmax);
+                              hipStream_t st);
 
 // Test aid: one production GEMM kernel chosen by `kind` (the MEBP_TEST_GEMM_* values of the
 // C ABI) on caller operands, one split, no LoRA term or residual, fp32 outputs. Forward

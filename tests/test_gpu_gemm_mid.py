@@ -1,5 +1,5 @@
-"""GPU parity of the forward products' tile configurations (gemm_mid.hip) at the sizes where
-they can go wrong, through one layer's forward against the fp64 oracle: a single reduction step
+"""GPU parity of the tile configurations of the forward and the transposed products (gemm_mid.hip)
+at the sizes where they can go wrong, through one layer against the fp64 oracle: a single reduction step
 (more K ranges than steps), odd step counts, token and column counts that are no multiple of a
 tile, every tile shape that the cost model picks, RoPE over head dims 64 / 128 / 256 and
 positions that wrap inside a tile.
@@ -16,7 +16,7 @@ import oracle as O
 from mebp_inputs import ALL7, Config, layer_input, make_inputs
 from paper_2510_03425_amd.device import DeviceModel
 
-from gpu_util import ROW_TOL, max_row_rel_l2, rel_l2, say
+from gpu_util import ROW_TOL, TOL, max_row_rel_l2, rel_l2, say, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -48,3 +48,38 @@ def test_layer_forward_tiles(built_lib, gpu, case):
     err, row = rel_l2(got, ref), max_row_rel_l2(got, ref)
     say("rel-L2", err, "worst row", row)
     assert err <= 5e-3 and row <= ROW_TOL
+
+
+# the transposed products reduce over the output features: widths that are no multiple of the
+# 64-row step (ffn 688, 208), of the 64-column blocks (hidden 96, 320), one to several segments,
+# splits over the grid (long reductions at few tokens) and every tile shape of the plan
+BWD_CASES = CASES + [
+    (96, 1, 1, 64, 688, 1, 70, "silu", 16),
+    (128, 4, 2, 64, 208, 1, 200, "gelu_tanh", 8),
+    (256, 2, 1, 128, 6912, 1, 300, "silu", 8),
+]
+
+
+@pytest.mark.parametrize("case", BWD_CASES, ids=lambda c: f"d{c[0]}-dh{c[3]}-f{c[4]}-{c[5]}x{c[6]}")
+def test_layer_backward_tiles(built_lib, gpu, case):
+    """Bound: gradients are products of bf16 operands (relative rounding 2^-9, three to six in a
+    row), 2e-2 as everywhere in these tests; a wrong tile is an error of order one."""
+    d, h, kv, dh, f, b, t, act, r = case
+    cfg = Config(name="mid", n_layers=1, hidden=d, n_heads=h, n_kv_heads=kv, head_dim=dh, ffn=f, vocab=0, act=act,
+                 lora_rank=r, lora_alpha=2.0 * r, lora_modules=ALL7, batch=b, seq=t)
+    inp = make_inputs(cfg, seed=4, norm="random")
+    x, dy = layer_input(cfg, 12)
+    dm = DeviceModel(inp, device=str(gpu))
+    tx, tdy = torch.from_numpy(x).to(gpu), torch.from_numpy(dy).to(gpu)
+    dx = torch.full_like(tx, float("nan"))
+    say("backward tiles", case)
+    dm.layer_backward(0, tx, tdy, dx)
+    torch.cuda.synchronize()
+    dx_ref, g_ref = O.layer_backward(cfg, 0, O.decompress_layer(cfg, inp, 0), x, dy)
+    errs = {"dx": rel_l2(to_np(dx) - dy, dx_ref - dy)}
+    for p, (dA, dB) in g_ref.items():
+        errs["dA_" + p], errs["dB_" + p] = rel_l2(to_np(dm.dA[0][p]), dA), rel_l2(to_np(dm.dB[0][p]), dB)
+    row = max_row_rel_l2(to_np(dx) - dy, dx_ref - dy)
+    say("rel-L2", {k: f"{v:.2e}" for k, v in errs.items()}, "worst row", row)
+    assert max(errs.values()) <= TOL, errs
+    assert row <= 2 * ROW_TOL  # (without the residual dy, which the other row checks include)
