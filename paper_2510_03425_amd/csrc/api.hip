@@ -7,6 +7,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <algorithm>
 #include <atomic>
 #include <map>
 #include <mutex>
@@ -222,13 +223,16 @@ bool make_layout(const mebp_config* c, int B, int T, Layout* L, bool w16 = true)
     mx(tn_part(M, D, {Q, KV, KV}, true, w16));
     L->split_floats = m;
     sz[S_SPLIT] = m * 4;
-    // every dB / dA launch of a layer: (widest column count, jobs)
+    // the dB and dA launch of each stage of a layer, for any of its projections adapted
     size_t lp = 0;
-    for (size_t v : {lora_outer_part_floats(M, Q > KV ? Q : KV, R, 3), lora_outer_part_floats(M, D, R, 3),
-                     lora_outer_part_floats(M, D, R, 1), lora_outer_part_floats(M, Q, R, 1),
-                     lora_outer_part_floats(M, FF, R, 2), lora_outer_part_floats(M, D, R, 2),
-                     lora_outer_part_floats(M, FF, R, 1)})
-      lp = v > lp ? v : lp;
+    for (uint32_t mask = 1; mask < 8; ++mask) {
+      const int out[3] = {Q, KV, KV};
+      int cols = 0;
+      for (int p = 0; p < 3; ++p)
+        if (mask >> p & 1) cols += out[p] + D;
+      for (int v : {cols, mask & 1 ? FF + D : 0, mask == 3 ? 2 * (FF + D) : 0, Q + D})
+        if (v) lp = std::max(lp, lora_outer_part_floats(M, v, R));
+    }
     L->lora_part_floats = lp;
     sz[S_PART] = lp * 4;
     size_t w = 0;
@@ -598,7 +602,7 @@ hipError_t lora_down(const Ctx& x, const mebp_layer_lora* lora, const f16* X, in
 
 // LoRA backward of the adapted projections among `ps`, with output gradients G_p (bf16
 // [N][out_p]) and the shared input X (fp16 [N][in]): du = s G B, dB = s G^T u, dA = du^T X.
-// Three launches for all of them. The input-gradient GEMM that adds du A waits for *ready;
+// Two launches for all of them (and a reduce at many tokens). The input-gradient GEMM that adds du A waits for *ready;
 // dB and dA feed nothing later in the backward and follow du on the same stream.
 hipError_t lora_bwd(const Ctx& x, const mebp_layer_lora* lora, const mebp_layer_lora_grad* grads,
                     std::initializer_list<int> ps, std::initializer_list<const bf16*> Gs, const f16* X,
@@ -610,28 +614,32 @@ hipError_t lora_bwd(const Ctx& x, const mebp_layer_lora* lora, const mebp_layer_
   ra.r = D.r;
   ra.wt = 1;
   ra.s = D.s;
-  LoraOuterArgs ob{}, oa{};
-  ob.M = oa.M = D.N;
-  ob.r = oa.r = D.r;
-  ob.layout = 0;
-  oa.layout = 1;
-  ob.part = oa.part = xs<float>(x, S_PART);
-  ob.part_floats = oa.part_floats = x.L.lora_part_floats;
+  // dB: one group per projection (its own G); dA: one group, the shared input read once
+  LoraOuterArgs oa{};
+  oa.M = D.N;
+  oa.r = D.r;
+  oa.part = xs<float>(x, S_PART);
+  oa.part_floats = x.L.lora_part_floats;
+  LoraOuterGroup da{};
+  da.Mx = X; da.f16in = 1; da.layout = 1;
   auto g = Gs.begin();
   for (int p : ps) {
     const bf16* G = *g++;
     if (!adapted(x, p)) continue;
     ra.job[ra.njobs++] = LoraRowsJob{G, D.out[p], D.out[p], lora->B[p], ldu(x, p)};
-    ob.job[ob.njobs++] = LoraOuterJob{G, D.out[p], D.out[p], lu(x, p), grads->dB[p], D.s};
-    oa.job[oa.njobs++] = LoraOuterJob{X, D.in[p], D.in[p], ldu(x, p), grads->dA[p], 1.0f};
+    LoraOuterGroup& db = oa.g[oa.ng++];
+    db = LoraOuterGroup{};
+    db.Mx = G; db.ldm = db.C = D.out[p]; db.nj = 1;
+    db.V[0] = lu(x, p); db.out[0] = grads->dB[p]; db.s[0] = D.s;
+    da.ldm = da.C = D.in[p];
+    da.V[da.nj] = ldu(x, p); da.out[da.nj] = grads->dA[p]; da.s[da.nj] = 1.0f;
+    ++da.nj;
   }
+  if (da.nj) oa.g[oa.ng++] = da;
   if (ra.njobs == 0) return hipSuccess;
   hipError_t e = on_aux(x, ready, [&](hipStream_t st) { return launch_lora_rows(ra, 1, st); });
   if (e != hipSuccess) return e;
-  hipStream_t so = x.aux ? x.aux : x.st;
-  e = launch_lora_outer(ob, 1, so);
-  if (e != hipSuccess) return e;
-  return launch_lora_outer(oa, 0, so);
+  return launch_lora_outer(oa, x.aux ? x.aux : x.st);
 }
 
 // Forward of one layer. keep=false: full forward to x_out. keep=true: recompute for the

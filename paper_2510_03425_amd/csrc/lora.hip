@@ -33,16 +33,19 @@ DEV void split_hi_lo(const float (&f)[8], uint4& hi, uint4& lo) {
 }
 
 // ------------------------------------------------------------------------------ rows
-// out[m][j] = s * sum_k X[m][k] W(j,k); workgroup = 64 rows x 16 outputs and LR_WAVES waves
+// out[m][j] = s * sum_k X[m][k] W(j,k); workgroup = 16 RT rows x 16 outputs and LR_WAVES waves
 // that take interleaved 64-wide K super-steps (every row segment a lane group loads is 128
-// contiguous bytes), two super-steps in flight per iteration (one with three jobs); the
-// per-wave partial tiles are summed through LDS in wave order. The many waves keep enough
-// loads in flight to stream X near the HBM rate even with few row blocks.
+// contiguous bytes), two super-steps in flight per iteration (one with three jobs of 64 rows);
+// the per-wave partial tiles are summed through LDS in wave order. Bound by the stream of X at
+// many tokens; at few, by the workgroups that run: RT is the largest of 4, 2, 1 that still gives
+// 256 of them (4096 tokens, K = 8960: 64 rows are 64 workgroups and 50 us = 1.5 TB/s, 16 rows
+// 256 and 31 us; 16384 tokens, K = 10240, two jobs: 187 us = 3.6 TB/s with 64 rows).
 // NJ = 1: blockIdx.y selects the job. NJ > 1: the NJ jobs share X (the q, k, v or gate, up
 // down-projections of one normalised input), read once for all of them.
-constexpr int LR_ROWS = 64, LR_WAVES = 8;
-template <class Op, int NJ>
+constexpr int LR_WAVES = 8;
+template <class Op, int NJ, int RT>
 __global__ __launch_bounds__(64 * LR_WAVES) void k_lora_rows(const LoraRowsArgs a) {
+  constexpr int LR_ROWS = 16 * RT;
   __shared__ float red[LR_WAVES][LR_ROWS][17];
   const int jb0 = NJ > 1 ? 0 : blockIdx.y;
   const LoraRowsJob& jx = a.job[jb0];
@@ -52,34 +55,39 @@ __global__ __launch_bounds__(64 * LR_WAVES) void k_lora_rows(const LoraRowsArgs 
   const int nsup = (K + 63) / 64;
   const int j = lane & 15;
 
+  // Loads go through buffer resources: what lies past the rows, the reduction or the rank has an
+  // offset past its resource and reads 0, without branches.
+  const rsrc_t rX = make_rsrc(X + (size_t)m0 * jx.ldx, ((size_t)(min(LR_ROWS, M - m0) - 1) * jx.ldx + K) * 2);
   auto load_w = [&](const float* W, int k, uint4& bh, uint4& bl) {
     float f[8];
-    if (k < K && j < r) {
-      if (a.wt == 0) {
-        const float4 p = *(const float4*)(W + (size_t)j * K + k), q = *(const float4*)(W + (size_t)j * K + k + 4);
-        f[0] = p.x; f[1] = p.y; f[2] = p.z; f[3] = p.w; f[4] = q.x; f[5] = q.y; f[6] = q.z; f[7] = q.w;
-      } else {
-#pragma unroll
-        for (int i = 0; i < 8; ++i) f[i] = W[(size_t)(k + i) * r + j];
-      }
+    const rsrc_t rW = make_rsrc(W, (size_t)r * K * 4);
+    if (a.wt == 0) {
+      const uint32_t o = (uint32_t)(j * K + k) * 4 | ((uint32_t)(K - 1 - k) & 0x80000000u);
+      const uint4 p = bload128(rW, o), q = bload128(rW, o + 16);
+      f[0] = __builtin_bit_cast(float, p.x); f[1] = __builtin_bit_cast(float, p.y);
+      f[2] = __builtin_bit_cast(float, p.z); f[3] = __builtin_bit_cast(float, p.w);
+      f[4] = __builtin_bit_cast(float, q.x); f[5] = __builtin_bit_cast(float, q.y);
+      f[6] = __builtin_bit_cast(float, q.z); f[7] = __builtin_bit_cast(float, q.w);
     } else {
+      const uint32_t bad = (uint32_t)(r - 1 - j) & 0x80000000u;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) f[i] = 0.f;
+      for (int i = 0; i < 8; ++i) f[i] = __builtin_bit_cast(float, bload32(rW, (uint32_t)((k + i) * r + j) * 4 | bad));
     }
     split_hi_lo<Op>(f, bh, bl);
   };
   // the super-step's two 32-wide halves of rows t*16 + lane%16 (K is a multiple of 8, so a
   // chunk is either wholly inside the row or wholly past it)
-  auto load_x = [&](int k, uint4 (&xv)[2][4]) {
+  const uint32_t xrow = (uint32_t)((lane & 15) * jx.ldx) * 2;
+  auto load_x = [&](int k, uint4 (&xv)[2][RT]) {
 #pragma unroll
     for (int hh = 0; hh < 2; ++hh)
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        const int m = m0 + t * 16 + (lane & 15), kk = k + 32 * hh;
-        xv[hh][t] = (kk < K && m < M) ? *(const uint4*)(X + (size_t)m * jx.ldx + kk) : make_uint4(0, 0, 0, 0);
+      for (int t = 0; t < RT; ++t) {
+        const int kk = k + 32 * hh;
+        xv[hh][t] = bload128s(rX, (xrow + 2 * kk) | ((uint32_t)(K - 1 - kk) & 0x80000000u), (uint32_t)(32 * t * jx.ldx));
       }
   };
-  auto mma = [&](int k, const uint4 (&xv)[2][4], f32x4 (&acc)[NJ][4]) {
+  auto mma = [&](int k, const uint4 (&xv)[2][RT], f32x4 (&acc)[NJ][RT]) {
 #pragma unroll
     for (int q = 0; q < NJ; ++q)
 #pragma unroll
@@ -87,23 +95,23 @@ __global__ __launch_bounds__(64 * LR_WAVES) void k_lora_rows(const LoraRowsArgs 
         uint4 bh, bl;
         load_w(a.job[jb0 + q].W, k + 32 * hh, bh, bl);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
+        for (int t = 0; t < RT; ++t) {
           acc[q][t] = mfma16_raw<Op>(xv[hh][t], bh, acc[q][t]);
           acc[q][t] = mfma16_raw<Op>(xv[hh][t], bl, acc[q][t]);
         }
       }
   };
 
-  f32x4 acc[NJ][4];
+  f32x4 acc[NJ][RT];
 #pragma unroll
   for (int q = 0; q < NJ; ++q)
 #pragma unroll
-    for (int t = 0; t < 4; ++t) acc[q][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int t = 0; t < RT; ++t) acc[q][t] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int ko = 8 * (lane >> 4);
-  if constexpr (NJ < 3) {
+  if constexpr (NJ < 3 || RT < 4) {
     for (int ss = w; ss < nsup; ss += 2 * LR_WAVES) {
       const int k0 = ss * 64 + ko, k1 = (ss + LR_WAVES) * 64 + ko;
-      uint4 x0[2][4], x1[2][4];
+      uint4 x0[2][RT], x1[2][RT];
       load_x(k0, x0);
       load_x(k1, x1);
       mma(k0, x0, acc);
@@ -113,7 +121,7 @@ __global__ __launch_bounds__(64 * LR_WAVES) void k_lora_rows(const LoraRowsArgs 
     // three jobs' accumulators leave registers for one super-step in flight
     for (int ss = w; ss < nsup; ss += LR_WAVES) {
       const int k0 = ss * 64 + ko;
-      uint4 x0[2][4];
+      uint4 x0[2][RT];
       load_x(k0, x0);
       mma(k0, x0, acc);
     }
@@ -123,7 +131,7 @@ __global__ __launch_bounds__(64 * LR_WAVES) void k_lora_rows(const LoraRowsArgs 
   for (int q = 0; q < NJ; ++q) {
     if (q) __syncthreads();  // the previous job's sums have been read
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < RT; ++t)
 #pragma unroll
       for (int rr = 0; rr < 4; ++rr) red[w][t * 16 + 4 * (lane >> 4) + rr][j] = acc[q][t][rr];
     __syncthreads();
@@ -141,143 +149,206 @@ __global__ __launch_bounds__(64 * LR_WAVES) void k_lora_rows(const LoraRowsArgs 
 }
 
 // ----------------------------------------------------------------------------- outer
-// R(c, j) = s * sum_m Mx[m][c] V[m][j]; workgroup = 128 columns c x 16 j (each wave 32 c);
-// per iteration 64 tokens are staged transposed in LDS (c-major, token-contiguous) together
-// with V^T as hi/lo planes. The products run in bf16 (V may be a tiny gradient); an fp16 Mx
-// is converted to bf16 while staged. The LDS tiles are double-buffered and the next
-// iteration's tokens are loaded into registers while the current ones are multiplied, so
-// one barrier per iteration suffices and loads overlap.
-// NJ = 1: blockIdx.y selects the job. NJ > 1: the NJ jobs share Mx (dA of q, k, v or of
-// gate, up: one layer input against each projection's du), staged once for all of them.
-constexpr int LO_C = 128, LO_M = 64, LO_LD = LO_M + 8;
-template <bool MX_F16, int NJ>
-__global__ __launch_bounds__(256) void k_lora_outer(const LoraOuterArgs a) {
-  __shared__ __attribute__((aligned(16))) u16 Mt[2][LO_C * LO_LD];
-  __shared__ __attribute__((aligned(16))) u16 Vh[2][NJ][16 * LO_LD];
-  __shared__ __attribute__((aligned(16))) u16 Vl[2][NJ][16 * LO_LD];
-  const int jb0 = NJ > 1 ? 0 : blockIdx.y;
-  const LoraOuterJob& jx = a.job[jb0];
-  const u16* Mx = (const u16*)jx.Mx;
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int C = jx.C, M = a.M, r = a.r;
-  const int c0 = blockIdx.x * LO_C, ms = blockIdx.z, MS = gridDim.z;
-  if (c0 >= C) return;
-  const int nsteps = (M + LO_M - 1) / LO_M;
+// R(c, j) = s * sum_m Mx[m][c] V[m][j] for every job of a stage in one launch (dB and dA; jobs
+// that share Mx, such as dA of q, k, v, form a group that reads it once). A wave owns 64 columns
+// and stages 64 tokens of them at a time transposed (c-major, token-contiguous) in LDS of its
+// own; V^T goes beside them as hi / lo planes. The next step's tokens are loaded into registers
+// meanwhile. Products run in bf16 (V may be a tiny gradient); an fp16 Mx is converted while
+// staged. Two ways to share a launch out:
+//  * TS, few tokens: the LO_W waves of a workgroup take interleaved token steps of the same 64
+//    columns, with V planes of their own (no barrier in the loop), and their partial tiles are
+//    summed in wave order through LDS. No reduce launch.
+//  * else, many tokens: the waves stand side by side (64 LO_W columns) and share one double-
+//    buffered V (a quarter of its loads and conversions each), one barrier per step; the tokens
+//    are split over the grid (blockIdx.y, partial planes in a.part, summed in split order by the
+//    reduce kernel).
+// Bound by the stream of Mx, and at few tokens by the latency of one step: all of a step's loads
+// are in flight at once. A layer's gradients, 999 tokens of 896 / 4864: 55 us in 4 launches (14
+// launches and 120 us as single products with a token split and a reduction each).
+constexpr int LO_C = 64, LO_M = 64, LO_LD = LO_M + 8, LO_W = 4, LO_V = 2 * 16 * LO_LD;
+template <int NJ, bool TS>
+__global__ __launch_bounds__(64 * LO_W) void k_lora_outer(const LoraOuterArgs a) {
+  __shared__ __attribute__((aligned(16))) u16 smem[LO_W * LO_C * LO_LD + (TS ? LO_W : 2) * NJ * LO_V];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int gi = 0;
+  while (gi + 1 < a.ng && a.g[gi + 1].blk0 <= (int)blockIdx.x) ++gi;
+  const LoraOuterGroup& gr = a.g[gi];
+  const int C = gr.C, M = a.M, r = a.r, nj = min(gr.nj, NJ), ldm = gr.ldm;
+  const int c0 = ((int)blockIdx.x - gr.blk0) * (TS ? LO_C : LO_C * LO_W) + (TS ? 0 : w * LO_C);
+  const bool f16in = gr.f16in;
+  // TS: wave-private tile and V planes; else private tile, two shared buffers of V planes
+  u16* Mt = smem + w * LO_C * LO_LD;
+  u16* Vall = smem + LO_W * LO_C * LO_LD;
+  const int nsteps = (M + LO_M - 1) / LO_M, ms = blockIdx.y, MS = gridDim.y;
   const int sb = (int)((long long)nsteps * ms / MS), se = (int)((long long)nsteps * (ms + 1) / MS);
-  // threads 0..127: one 8x8 block of Mx (8 tokens x 8 columns); 128..255: 8 tokens of V
-  const bool mx_role = tid < 128;
-  const int rb = tid & 7, cb = (tid >> 3) & 15;      // Mx role: token block, column block
-  const int jv = (tid - 128) & 15, mq = (tid - 128) >> 4;  // V role: output j, token group
-  uint32_t in[8][4];
-  float f[NJ][8];
+  const int rb = lane & 7, cb = lane >> 3;  // 8 x 8 block: tokens 8 rb .., columns 8 cb ..
+  // V: output jv and NV tokens from NV tg on (TS: eight tokens each in two halves of 32)
+  constexpr int NV = TS ? 8 : 64 / (4 * LO_W), NH = TS ? 2 : 1;
+  const int jv = lane & 15, tg = TS ? lane >> 4 : tid >> 4;
+  const uint32_t oc = c0 + 8 * cb < C ? (uint32_t)(8 * rb * ldm + c0 + 8 * cb) * 2 : 0x80000000u;
+  // (an invalid output's offset gets the sign bit, past every resource: no branch per load, whose
+  // waits would line the loads up one behind the other)
+  const uint32_t vbad = (uint32_t)(r - 1 - jv) & 0x80000000u;
+  uint4 in[8];
+  float f[NJ][NH][NV];
   auto load = [&](int st) {
     const int mb = st * LO_M;
-    if (mx_role) {
+    const rsrc_t rT = make_rsrc((const u16*)gr.Mx + (size_t)mb * ldm, ((size_t)(min(LO_M, M - mb) - 1) * ldm + C) * 2);
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        const int m = mb + rb * 8 + i, c = c0 + cb * 8;
-        uint4 v = make_uint4(0, 0, 0, 0);
-        if (m < M && c < C) v = *(const uint4*)(Mx + (size_t)m * jx.ldm + c);
-        in[i][0] = v.x; in[i][1] = v.y; in[i][2] = v.z; in[i][3] = v.w;
-      }
-    } else {
+    for (int i = 0; i < 8; ++i) in[i] = bload128s(rT, oc, (uint32_t)(i * ldm) * 2);
 #pragma unroll
-      for (int q = 0; q < NJ; ++q)
+    for (int q = 0; q < NJ; ++q) {
+      if (q >= nj) break;
+      const rsrc_t rV = make_rsrc(gr.V[q], (size_t)M * r * 4);
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const int m = mb + mq * 8 + i;
-          f[q][i] = (m < M && jv < r) ? a.job[jb0 + q].V[(size_t)m * r + jv] : 0.f;
-        }
+      for (int hh = 0; hh < NH; ++hh)
+#pragma unroll
+        for (int i = 0; i < NV; ++i)
+          f[q][hh][i] = __builtin_bit_cast(
+              float, bload32(rV, (uint32_t)((mb + 32 * hh + NV * tg + i) * r + jv) * 4 | vbad));
     }
   };
-  auto store = [&](int buf) {
-    if (mx_role) {
-      if (MX_F16) {
+  auto store = [&](u16* Vp) {
+    uint32_t x[8][4];
 #pragma unroll
-        for (int i = 0; i < 8; ++i) {
-          const uint4 v = f16x8_to_bf16x8(make_uint4(in[i][0], in[i][1], in[i][2], in[i][3]));
-          in[i][0] = v.x; in[i][1] = v.y; in[i][2] = v.z; in[i][3] = v.w;
-        }
-      }
+    for (int i = 0; i < 8; ++i) {
+      const uint4 v = f16in ? f16x8_to_bf16x8(in[i]) : in[i];
+      x[i][0] = v.x; x[i][1] = v.y; x[i][2] = v.z; x[i][3] = v.w;
+    }
 #pragma unroll
-      for (int jc = 0; jc < 8; ++jc) {
-        uint4 o;
-        if (jc & 1) {
-          o = make_uint4(perm_hi16(in[0][jc >> 1], in[1][jc >> 1]), perm_hi16(in[2][jc >> 1], in[3][jc >> 1]),
-                         perm_hi16(in[4][jc >> 1], in[5][jc >> 1]), perm_hi16(in[6][jc >> 1], in[7][jc >> 1]));
+    for (int jc = 0; jc < 8; ++jc) {
+      const int d = jc >> 1;
+      uint4 o;
+      if (jc & 1)
+        o = make_uint4(perm_hi16(x[0][d], x[1][d]), perm_hi16(x[2][d], x[3][d]), perm_hi16(x[4][d], x[5][d]),
+                       perm_hi16(x[6][d], x[7][d]));
+      else
+        o = make_uint4(perm_lo16(x[0][d], x[1][d]), perm_lo16(x[2][d], x[3][d]), perm_lo16(x[4][d], x[5][d]),
+                       perm_lo16(x[6][d], x[7][d]));
+      *(uint4*)(Mt + (8 * cb + jc) * LO_LD + 8 * rb) = o;
+    }
+#pragma unroll
+    for (int q = 0; q < NJ; ++q) {
+      if (q >= nj) break;
+#pragma unroll
+      for (int hh = 0; hh < NH; ++hh) {
+        u16* ph = Vp + (2 * q * 16 + jv) * LO_LD + 32 * hh + NV * tg;
+        u16* pl = ph + 16 * LO_LD;
+        if constexpr (NV == 8) {
+          uint4 hi, lo;
+          split_hi_lo<OpBF16>(f[q][hh], hi, lo);
+          *(uint4*)ph = hi;
+          *(uint4*)pl = lo;
         } else {
-          o = make_uint4(perm_lo16(in[0][jc >> 1], in[1][jc >> 1]), perm_lo16(in[2][jc >> 1], in[3][jc >> 1]),
-                         perm_lo16(in[4][jc >> 1], in[5][jc >> 1]), perm_lo16(in[6][jc >> 1], in[7][jc >> 1]));
+          static_assert(NV == 4 || NV == 8, "tokens of V per lane");
+          const float* v = f[q][hh];
+          const uint32_t h0 = pack_bf16x2(v[0], v[1]), h1 = pack_bf16x2(v[2], v[3]);
+          *(uint2*)ph = make_uint2(h0, h1);
+          *(uint2*)pl = make_uint2(pack_bf16x2(v[0] - bf16_lo(h0), v[1] - bf16_hi(h0)),
+                                   pack_bf16x2(v[2] - bf16_lo(h1), v[3] - bf16_hi(h1)));
         }
-        *(uint4*)(Mt[buf] + (cb * 8 + jc) * LO_LD + rb * 8) = o;
-      }
-    } else {
-#pragma unroll
-      for (int q = 0; q < NJ; ++q) {
-        uint4 hi, lo;
-        split_hi_lo<OpBF16>(f[q], hi, lo);
-        *(uint4*)(Vh[buf][q] + jv * LO_LD + mq * 8) = hi;
-        *(uint4*)(Vl[buf][q] + jv * LO_LD + mq * 8) = lo;
       }
     }
   };
-  f32x4 acc[NJ][2];
+  f32x4 acc[NJ][4];
 #pragma unroll
-  for (int q = 0; q < NJ; ++q) acc[q][0] = acc[q][1] = f32x4{0.f, 0.f, 0.f, 0.f};
-  if (sb < se) load(sb);
-  for (int st = sb; st < se; ++st) {
-    const int buf = (st - sb) & 1;
-    store(buf);
-    __syncthreads();
-    if (st + 1 < se) load(st + 1);
+  for (int q = 0; q < NJ; ++q)
+#pragma unroll
+    for (int t = 0; t < 4; ++t) acc[q][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  // LDS accesses of one wave stay in order; the compiler must keep them so (other lanes' data)
+  auto fence = [] {
+    __builtin_amdgcn_wave_barrier();
+    asm volatile("" ::: "memory");
+  };
+  const int s0 = TS ? sb + w : sb, ds = TS ? LO_W : 1;
+  if (s0 < se) load(s0);
+  for (int st = s0; st < se; st += ds) {
+    u16* Vp = Vall + (TS ? w : (st - sb) & 1) * NJ * LO_V;
+    fence();
+    store(Vp);
+    if constexpr (TS)
+      fence();
+    else
+      __syncthreads();  // (the other buffer was read before the previous step's barrier)
+    if (st + ds < se) load(st + ds);
 #pragma unroll
     for (int kk = 0; kk < LO_M; kk += 32) {
-      uint4 av[2];
+      uint4 av[4];
 #pragma unroll
-      for (int ct = 0; ct < 2; ++ct)
-        av[ct] = *(const uint4*)(Mt[buf] + (w * 32 + ct * 16 + (lane & 15)) * LO_LD + kk + 8 * (lane >> 4));
+      for (int t = 0; t < 4; ++t) av[t] = *(const uint4*)(Mt + (16 * t + (lane & 15)) * LO_LD + kk + 8 * (lane >> 4));
 #pragma unroll
       for (int q = 0; q < NJ; ++q) {
-        const uint4 bh = *(const uint4*)(Vh[buf][q] + (lane & 15) * LO_LD + kk + 8 * (lane >> 4));
-        const uint4 bl = *(const uint4*)(Vl[buf][q] + (lane & 15) * LO_LD + kk + 8 * (lane >> 4));
+        if (q >= nj) break;
+        const uint4 bh = *(const uint4*)(Vp + (2 * q * 16 + (lane & 15)) * LO_LD + kk + 8 * (lane >> 4));
+        const uint4 bl = *(const uint4*)(Vp + ((2 * q + 1) * 16 + (lane & 15)) * LO_LD + kk + 8 * (lane >> 4));
 #pragma unroll
-        for (int ct = 0; ct < 2; ++ct) {
-          acc[q][ct] = mfma16_raw<OpBF16>(av[ct], bh, acc[q][ct]);
-          acc[q][ct] = mfma16_raw<OpBF16>(av[ct], bl, acc[q][ct]);
+        for (int t = 0; t < 4; ++t) {
+          acc[q][t] = mfma16_raw<OpBF16>(av[t], bh, acc[q][t]);
+          acc[q][t] = mfma16_raw<OpBF16>(av[t], bl, acc[q][t]);
         }
       }
     }
   }
-  // lane holds R rows c = c0 + w*32 + ct*16 + 4g + rr, column j = lane%16
-  const int j = lane & 15;
+  auto put = [&](int q, int c, int j, float v) {
+    const size_t at = gr.layout == 0 ? (size_t)c * r + j : (size_t)j * C + c;
+    if (MS > 1)
+      a.part[gr.part0 + ((size_t)q * MS + ms) * C * r + at] = v;
+    else
+      gr.out[q][at] = gr.s[q] * v;
+  };
+  // lane: column 16 t + 4 (lane / 16) + rr, output lane % 16
+  if constexpr (!TS) {
 #pragma unroll
-  for (int q = 0; q < NJ; ++q) {
-    const LoraOuterJob& jb = a.job[jb0 + q];
-    const int y = jb0 + q;
+    for (int q = 0; q < NJ; ++q) {
+      if (q >= nj) break;
 #pragma unroll
-    for (int ct = 0; ct < 2; ++ct)
+      for (int t = 0; t < 4; ++t)
 #pragma unroll
-      for (int rr = 0; rr < 4; ++rr) {
-        const int c = c0 + w * 32 + ct * 16 + 4 * (lane >> 4) + rr;
-        if (c >= C || j >= r) continue;
-        if (MS > 1)
-          a.part[(((size_t)y * MS + ms) * a.cmax + c) * r + j] = acc[q][ct][rr];
-        else
-          jb.out[a.layout == 0 ? (size_t)c * r + j : (size_t)j * C + c] = jb.s * acc[q][ct][rr];
+        for (int rr = 0; rr < 4; ++rr) {
+          const int c = c0 + 16 * t + 4 * (lane >> 4) + rr, j = lane & 15;
+          if (c < C && j < r) put(q, c, j, acc[q][t][rr]);
+        }
+    }
+  } else {
+    static_assert(!TS || LO_C * LO_LD * 2 >= LO_C * 16 * 4, "a job's partial tile fits the wave's staging tile");
+    float* red = reinterpret_cast<float*>(Mt);
+    for (int q = 0; q < nj; ++q) {
+      // (every wave is done with its tile, or with the previous job's sums)
+      __syncthreads();
+#pragma unroll
+      for (int qq = 0; qq < NJ; ++qq) {
+        if (qq != q) continue;
+#pragma unroll
+        for (int t = 0; t < 4; ++t)
+#pragma unroll
+          for (int rr = 0; rr < 4; ++rr) red[(16 * t + 4 * (lane >> 4) + rr) * 16 + (lane & 15)] = acc[qq][t][rr];
       }
+      __syncthreads();
+      for (int o = tid; o < LO_C * 16; o += 64 * LO_W) {
+        // dA rows ([r][C]) are written column-fastest, dB rows ([C][r]) rank-fastest
+        const int c = gr.layout == 0 ? o >> 4 : o & (LO_C - 1), j = gr.layout == 0 ? o & 15 : o / LO_C;
+        if (c0 + c >= C || j >= r) continue;
+        float v = 0.f;
+#pragma unroll
+        for (int ww = 0; ww < LO_W; ++ww)
+          v += reinterpret_cast<const float*>(smem + ww * LO_C * LO_LD)[c * 16 + j];
+        put(q, c0 + c, j, v);
+      }
+    }
   }
 }
 
-// sum the token-split partials of every job in split order and write with layout / scale
+// sum the token-split partials of every job in split order; blockIdx.y counts the jobs
 __global__ void k_lora_outer_reduce(const LoraOuterArgs a, int MS) {
-  const LoraOuterJob& jb = a.job[blockIdx.y];
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  const int r = a.r;
-  if (i >= jb.C * r) return;
-  const int c = i / r, j = i % r;
+  int gi = 0, q = blockIdx.y;
+  while (q >= a.g[gi].nj) q -= a.g[gi++].nj;
+  const LoraOuterGroup& gr = a.g[gi];
+  const size_t n = (size_t)gr.C * a.r, i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const float* p = a.part + gr.part0 + (size_t)q * MS * n + i;
   float acc = 0.f;
-  for (int z = 0; z < MS; ++z) acc += a.part[(((size_t)blockIdx.y * MS + z) * a.cmax + c) * r + j];
-  jb.out[a.layout == 0 ? (size_t)c * r + j : (size_t)j * jb.C + c] = jb.s * acc;
+  for (int z = 0; z < MS; ++z) acc += p[(size_t)z * n];
+  gr.out[q][i] = gr.s[q] * acc;
 }
 
 __global__ void k_fill_i32(int* p, int n, int v) {
@@ -285,15 +356,19 @@ __global__ void k_fill_i32(int* p, int n, int v) {
   if (i < n) p[i] = v;
 }
 
-// token splits of an outer launch with `groups` workgroup columns per split (column blocks
-// times the jobs that do not share their input): about 512 workgroups, two per CU (LDS and
-// registers allow two or three), so that one workgroup's loads overlap another's transposes
-// and MFMAs (256 workgroups measured 25-35 % slower on the large launches)
-int outer_splits(int M, int cmax, int groups) {
-  const int cb = ((cmax + LO_C - 1) / LO_C) * groups, steps = (M + LO_M - 1) / LO_M;
-  if (steps < 16) return 1;
-  int s = (512 + cb - 1) / cb;
-  if (s > steps / 4) s = steps / 4;
+// token splits of an outer launch with `cols` columns over all groups. Up to 4096 tokens the
+// waves split the tokens (TS), over the grid too from 2048 on (below, the reduce launch would
+// cost as much as it saves); beyond, about 768 workgroups side by side, each with eight steps at
+// least (the four launches and reductions of a layer: 4096 tokens, 1536 wide, 119 us with TS and
+// 156 without; 16384 tokens, 2560 wide, 516 us with TS and 443 without).
+constexpr int kOuterTsSteps = 64;
+int outer_splits(int M, int cols) {
+  const int steps = (M + LO_M - 1) / LO_M, ts = steps <= kOuterTsSteps, wide = ts ? LO_C : LO_C * LO_W;
+  if (steps <= 32) return 1;
+  const int cb = (cols + wide - 1) / wide;
+  int s = ((ts ? 1024 : 768) + cb - 1) / cb;
+  const int most = steps / (ts ? 4 * LO_W : 8);
+  if (s > most) s = most;
   if (s > 64) s = 64;
   return s < 1 ? 1 : s;
 }
@@ -308,15 +383,16 @@ bool same_input(const J* job, int n, const void* J::*x, int J::*ld, int J::*w) {
 
 }  // namespace
 
-size_t lora_outer_part_floats(int M, int cmax, int r, int njobs) {
-  // the most splits any grouping of the jobs uses (one workgroup column group per split)
-  const int s = outer_splits(M, cmax, 1);
-  return s > 1 ? (size_t)njobs * s * cmax * r : 0;
+size_t lora_outer_part_floats(int M, int cols, int r) {
+  const int s = outer_splits(M, cols);
+  return s > 1 ? (size_t)s * cols * r : 0;
 }
 
 hipError_t launch_lora_rows(const LoraRowsArgs& a, int xbf16, hipStream_t st) {
   const bool shared = same_input(a.job, a.njobs, &LoraRowsJob::X, &LoraRowsJob::ldx, &LoraRowsJob::K);
-  dim3 grid((a.M + LR_ROWS - 1) / LR_ROWS, shared ? 1 : a.njobs);
+  const int gy = shared ? 1 : a.njobs;
+  const int rt = (a.M + 63) / 64 * gy >= 256 ? 4 : (a.M + 31) / 32 * gy >= 256 ? 2 : 1;
+  const dim3 grid((a.M + 16 * rt - 1) / (16 * rt), gy);
   double flops = 0, bytes = 0;
   for (int i = 0; i < a.njobs; ++i) {
     flops += 2.0 * a.M * a.job[i].K * a.r;
@@ -324,7 +400,15 @@ hipError_t launch_lora_rows(const LoraRowsArgs& a, int xbf16, hipStream_t st) {
              (double)a.M * a.r * 4;
   }
   const dim3 blk(64 * LR_WAVES);
-#define LR_GO(OP, NJ) MEBP_TIMED(st, "lora_rows", flops, bytes, hipLaunchKernelGGL((k_lora_rows<OP, NJ>), grid, blk, 0, st, a))
+#define LR_GO(OP, NJ)                                                                                                  \
+  do {                                                                                                                 \
+    if (rt == 4)                                                                                                       \
+      MEBP_TIMED(st, "lora_rows", flops, bytes, hipLaunchKernelGGL((k_lora_rows<OP, NJ, 4>), grid, blk, 0, st, a));    \
+    else if (rt == 2)                                                                                                  \
+      MEBP_TIMED(st, "lora_rows", flops, bytes, hipLaunchKernelGGL((k_lora_rows<OP, NJ, 2>), grid, blk, 0, st, a));    \
+    else                                                                                                               \
+      MEBP_TIMED(st, "lora_rows", flops, bytes, hipLaunchKernelGGL((k_lora_rows<OP, NJ, 1>), grid, blk, 0, st, a));    \
+  } while (0)
   const int nj = shared ? a.njobs : 1;
   if (xbf16) {
     if (nj == 3) LR_GO(OpBF16, 3); else if (nj == 2) LR_GO(OpBF16, 2); else LR_GO(OpBF16, 1);
@@ -335,33 +419,46 @@ hipError_t launch_lora_rows(const LoraRowsArgs& a, int xbf16, hipStream_t st) {
   return hipGetLastError();
 }
 
-hipError_t launch_lora_outer(const LoraOuterArgs& a0, int mbf16, hipStream_t st) {
+hipError_t launch_lora_outer(const LoraOuterArgs& a0, hipStream_t st) {
   LoraOuterArgs a = a0;
-  const bool shared = same_input(a.job, a.njobs, &LoraOuterJob::Mx, &LoraOuterJob::ldm, &LoraOuterJob::C);
-  a.cmax = 0;
   double flops = 0, bytes = 0;
-  for (int i = 0; i < a.njobs; ++i) {
-    a.cmax = a.job[i].C > a.cmax ? a.job[i].C : a.cmax;
-    flops += 2.0 * a.M * a.job[i].C * a.r;
-    bytes += (i == 0 || !shared ? (double)a.M * a.job[i].C * 2 : 0.0) + (double)a.M * a.r * 4 +
-             (double)a.job[i].C * a.r * 4;
+  int cols = 0, blocks = 0, njmax = 1, jobs = 0, cmax = 0;
+  const bool ts = (a.M + LO_M - 1) / LO_M <= kOuterTsSteps;
+  for (int i = 0; i < a.ng; ++i) {
+    LoraOuterGroup& g = a.g[i];
+    g.blk0 = blocks;
+    blocks += ts ? (g.C + LO_C - 1) / LO_C : (g.C + LO_C * LO_W - 1) / (LO_C * LO_W);
+    cols += g.C * g.nj;
+    jobs += g.nj;
+    njmax = g.nj > njmax ? g.nj : njmax;
+    cmax = g.C > cmax ? g.C : cmax;
+    flops += 2.0 * a.M * g.C * a.r * g.nj;
+    bytes += (double)a.M * g.C * 2 + g.nj * ((double)a.M * a.r * 4 + (double)g.C * a.r * 4);
   }
-  const int groups = shared ? 1 : a.njobs;
-  int MS = outer_splits(a.M, a.cmax, groups);
-  if (MS > 1 && (!a.part || a.part_floats < (size_t)a.njobs * MS * a.cmax * a.r)) MS = 1;
-  dim3 grid((a.cmax + LO_C - 1) / LO_C, groups, MS);
-  const int nj = shared ? a.njobs : 1;
-#define LO_GO(F16, NJ) MEBP_TIMED(st, "lora_outer", flops, bytes, hipLaunchKernelGGL((k_lora_outer<F16, NJ>), grid, dim3(256), 0, st, a))
-  if (mbf16) {
-    if (nj == 3) LO_GO(false, 3); else if (nj == 2) LO_GO(false, 2); else LO_GO(false, 1);
-  } else {
-    if (nj == 3) LO_GO(true, 3); else if (nj == 2) LO_GO(true, 2); else LO_GO(true, 1);
+  if (!blocks) return hipSuccess;
+  int MS = outer_splits(a.M, cols);
+  if (MS > 1 && (!a.part || a.part_floats < (size_t)MS * cols * a.r)) MS = 1;
+  size_t p = 0;
+  for (int i = 0; i < a.ng; ++i) {
+    a.g[i].part0 = p;
+    p += (size_t)a.g[i].nj * MS * a.g[i].C * a.r;
   }
+  const dim3 grid(blocks, MS);
+#define LO_GO(NJ)                                                                                                   \
+  do {                                                                                                              \
+    if (ts)                                                                                                         \
+      MEBP_TIMED(st, "lora_outer", flops, bytes,                                                                    \
+                 hipLaunchKernelGGL((k_lora_outer<NJ, true>), grid, dim3(64 * LO_W), 0, st, a));                    \
+    else                                                                                                            \
+      MEBP_TIMED(st, "lora_outer", flops, bytes,                                                                    \
+                 hipLaunchKernelGGL((k_lora_outer<NJ, false>), grid, dim3(64 * LO_W), 0, st, a));                   \
+  } while (0)
+  if (njmax == 3) LO_GO(3); else if (njmax == 2) LO_GO(2); else LO_GO(1);
 #undef LO_GO
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || MS == 1) return e;
-  dim3 rg((a.cmax * a.r + 255) / 256, a.njobs);
-  MEBP_TIMED(st, "lora_outer_reduce", 0.0, 4.0 * MS * a.cmax * a.r * a.njobs,
+  const dim3 rg((cmax * a.r + 255) / 256, jobs);
+  MEBP_TIMED(st, "lora_outer_reduce", 0.0, 4.0 * MS * cols * a.r,
              hipLaunchKernelGGL(k_lora_outer_reduce, rg, dim3(256), 0, st, a, MS));
   return hipGetLastError();
 }

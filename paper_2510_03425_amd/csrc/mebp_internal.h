@@ -231,26 +231,28 @@ struct LoraRowsArgs {
   float s;
 };
 hipError_t launch_lora_rows(const LoraRowsArgs& a, int xbf16, hipStream_t st);
-// Outer: R(c, j) = s_job * sum_m Mx[m][c] * V[m][j] for each job, written as out[c*r + j]
-// (layout 0, dB [C][r]) or out[j*C + c] (layout 1, dA [r][C]). Mx [M][ldm] fp16 (mbf16 = 0)
-// or bf16 (mbf16 = 1), V fp32 [M][r]. Token-split partials use `part` when the token count
-// is large (lora_outer_part_floats).
-struct LoraOuterJob {
+// Outer: R(c, j) = s * sum_m Mx[m][c] V[m][j], written as out[c*r + j] (layout 0, dB [C][r]) or
+// out[j*C + c] (layout 1, dA [r][C]), for up to three jobs of a group that share Mx [M][ldm]
+// (fp16 when f16in, else bf16), V fp32 [M][r]; up to four groups in one launch. Token-split
+// partials use `part` when the token count is large (lora_outer_part_floats).
+struct LoraOuterGroup {
   const void* Mx;
-  int ldm, C;
-  const float* V;
-  float* out;
-  float s;
+  int ldm, C, f16in, layout, nj;
+  const float* V[3];
+  float* out[3];
+  float s[3];
+  int blk0;               // set by the launcher, as part0
+  size_t part0;
 };
 struct LoraOuterArgs {
-  LoraOuterJob job[3];
-  int njobs, M, r, layout;
+  LoraOuterGroup g[4];
+  int ng, M, r;
   float* part;
   size_t part_floats;
-  int cmax;               // set by the launcher
 };
-hipError_t launch_lora_outer(const LoraOuterArgs& a, int mbf16, hipStream_t st);
-size_t lora_outer_part_floats(int M, int cmax, int r, int njobs);
+hipError_t launch_lora_outer(const LoraOuterArgs& a, hipStream_t st);
+// cols: the columns of a launch, summed over its jobs
+size_t lora_outer_part_floats(int M, int cols, int r);
 hipError_t launch_fill_i32(int* p, int n, int v, hipStream_t st);
 
 // ---------------------------------------------------------------- attention

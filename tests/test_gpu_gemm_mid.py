@@ -83,3 +83,34 @@ def test_layer_backward_tiles(built_lib, gpu, case):
     say("rel-L2", {k: f"{v:.2e}" for k, v in errs.items()}, "worst row", row)
     assert max(errs.values()) <= TOL, errs
     assert row <= 2 * ROW_TOL  # (without the residual dy, which the other row checks include)
+
+
+# LoRA kernels over the token counts where their launch changes shape: rows of 16, 32 and 64 per
+# workgroup; outer products by waves over the tokens, over the grid as well (from 2049 tokens on)
+# and side by side with a shared u (from 4097 on), with token counts off every step and a rank
+# below the tile's 16.
+LORA_CASES = [(1, 15, 8), (1, 193, 16), (3, 683, 8), (4, 1023, 16), (3, 1366, 16), (9, 911, 16), (33, 497, 8)]
+
+
+@pytest.mark.parametrize("case", LORA_CASES, ids=lambda c: f"{c[0]}x{c[1]}-r{c[2]}")
+def test_layer_lora_token_counts(built_lib, gpu, case):
+    """Same bound as the tiles; a token left out or counted twice changes a gradient of N random
+    tokens by 1 / sqrt(N) of its size, so the last tokens are given 40 times the weight."""
+    b, t, r = case
+    cfg = Config(name="lora", n_layers=1, hidden=64, n_heads=1, n_kv_heads=1, head_dim=64, ffn=192, vocab=0,
+                 act="silu", lora_rank=r, lora_alpha=2.0 * r, lora_modules=ALL7, batch=b, seq=t)
+    inp = make_inputs(cfg, seed=5, norm="random")
+    x, dy = layer_input(cfg, 13)
+    dy[-3:] *= 40
+    dm = DeviceModel(inp, device=str(gpu))
+    tx, tdy = torch.from_numpy(x).to(gpu), torch.from_numpy(dy).to(gpu)
+    dx = torch.full_like(tx, float("nan"))
+    say("lora token counts", case)
+    dm.layer_backward(0, tx, tdy, dx)
+    torch.cuda.synchronize()
+    dx_ref, g_ref = O.layer_backward(cfg, 0, O.decompress_layer(cfg, inp, 0), x, dy)
+    errs = {"dx": rel_l2(to_np(dx) - dy, dx_ref - dy)}
+    for p, (dA, dB) in g_ref.items():
+        errs["dA_" + p], errs["dB_" + p] = rel_l2(to_np(dm.dA[0][p]), dA), rel_l2(to_np(dm.dB[0][p]), dB)
+    say("rel-L2", {k: f"{v:.2e}" for k, v in errs.items()})
+    assert max(errs.values()) <= TOL, errs
