@@ -841,6 +841,8 @@ __global__ __launch_bounds__(64 * NW, 1) void k_gemm_nt_lds(const NtArgs a) {
       const uint32_t off = (!tail || k0 + 8 * chunkA[i] < K) ? offA[i] + 2 * k0 : 0x80000000u;
       __builtin_amdgcn_raw_ptr_buffer_load_lds(rA, dst + 1024 * (wave + NW * i), 16, off, 0, 0, 0);
     }
+    // the counted wait below counts on the activation loads being issued before the weights'
+    __builtin_amdgcn_sched_barrier(0);
     if constexpr (W16) {
 #pragma unroll
       for (int j = 0; j < NJ; ++j)
@@ -942,11 +944,13 @@ __global__ __launch_bounds__(64 * NW, 1) void k_gemm_nt_lds(const NtArgs a) {
   // weights of k+1 and all of k+2, 2 NJ + 4 + 2 NJ) and meet the other waves at the barrier.
   // vector-memory instructions of one gload: 4 activation loads plus the weight loads
   constexpr int VMI = NA + (W16 ? 4 * NJ : 2 * NJ);
-  auto step = [&](auto I_, int k) {
+  // (the last two steps' weight loads are never used, so the compiler may drop them and they do
+  // not count: there everything is waited for)
+  auto step = [&](auto I_, int k, auto Last_) {
     constexpr int I = decltype(I_)::value;
     gload(IC<(I + 2) % LDS_STAGES>{}, min(k + 2, kt_end - 1));
     mma(IC<I>{});
-    wait_vmcnt<VMI + (W16 ? 4 * NJ : 2 * NJ)>();
+    wait_vmcnt<decltype(Last_)::value ? 0 : VMI + (W16 ? 4 * NJ : 2 * NJ)>();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");  // no LDS access moves across the barrier
   };
@@ -958,12 +962,12 @@ __global__ __launch_bounds__(64 * NW, 1) void k_gemm_nt_lds(const NtArgs a) {
     asm volatile("" ::: "memory");
     int k = kt_begin;
     for (; k + 3 <= kt_end; k += 3) {
-      step(IC<0>{}, k);
-      step(IC<1>{}, k + 1);
-      step(IC<2>{}, k + 2);
+      step(IC<0>{}, k, IC<0>{});
+      step(IC<1>{}, k + 1, IC<0>{});
+      step(IC<2>{}, k + 2, IC<0>{});
     }
-    if (k < kt_end) step(IC<0>{}, k);
-    if (k + 1 < kt_end) step(IC<1>{}, k + 1);
+    if (k < kt_end) step(IC<0>{}, k, IC<1>{});
+    if (k + 1 < kt_end) step(IC<1>{}, k + 1, IC<1>{});
   }
   if constexpr (GATED) {
     wait_vmcnt<0>();
