@@ -98,6 +98,7 @@ KERNEL_PATTERNS = {
     "attn_fwd": r"k_attn_fwd",
     "attn_bwd_dkdv": r"k_attn_bwd_(dkdv|kv32p?)<",
     "attn_bwd_dq": r"k_attn_bwd_dq<",
+    "attn_bwd_both": r"k_attn_bwd_both<",
 }
 
 

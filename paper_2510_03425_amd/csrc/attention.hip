@@ -654,15 +654,17 @@ __global__ void k_attn_delta(const bf16* dO, const f16* O, int ld, int B, int T,
 // stores fp32 partial dK / dV and k_attn_dkdv_reduce sums them in (chunk, head) order
 // (deterministic); otherwise the epilogue finishes dK (scale, RoPE backward) and dV itself.
 template <int DH, int QB>
-__global__ __launch_bounds__(256) void k_attn_bwd_dkdv(const AttnArgs a, float* part, int nck, int cq) {
+constexpr int kDkdvLds = (2 * QB * (DH + 8) + 2 * DH * (QB + 8)) * 2 + 2 * QB * 4;
+template <int DH, int QB>
+DEV void attn_bwd_dkdv(const AttnArgs& a, float* part, int nck, int cq, const TileId id, uint8_t* smem) {
   constexpr int LDN = DH + 8, LDT_ = QB + 8, NKS = DH / 32, NT = DH / 16, NQT = QB / 16;
-  __shared__ __attribute__((aligned(16))) u16 Qs[QB * LDN];   // fp16 (scores)
-  __shared__ __attribute__((aligned(16))) u16 dOs[QB * LDN];  // bf16
-  __shared__ __attribute__((aligned(16))) u16 Qt[DH * LDT_];  // bf16 (dK product)
-  __shared__ __attribute__((aligned(16))) u16 dOt[DH * LDT_]; // bf16
-  __shared__ float lse_s[QB], del_s[QB];
+  u16* Qs = (u16*)smem;           // [QB][LDN] fp16 (scores)
+  u16* dOs = Qs + QB * LDN;       // [QB][LDN] bf16
+  u16* Qt = dOs + QB * LDN;       // [DH][LDT_] bf16 (dK product)
+  u16* dOt = Qt + DH * LDT_;      // [DH][LDT_] bf16
+  float* lse_s = (float*)(dOt + DH * LDT_);
+  float* del_s = lse_s + QB;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const TileId id = attn_tile(nck);
   const int kblk = nck ? id.x / nck : id.x, chunk = nck ? id.x % nck : 0;
   const int T = a.T, h = id.y, b = id.z, grp = a.Hq / a.Hkv, kvh = h / grp, hh = h % grp;
   const int k0 = kblk * 64, kw = k0 + 16 * w, key = kw + (lane & 15);
@@ -806,14 +808,15 @@ __global__ __launch_bounds__(256) void k_attn_bwd_dkdv(const AttnArgs a, float* 
 // PF: the next key block is loaded into registers while the current one is multiplied.
 // Without it (head dim 256) the kernel stays within 256 registers per lane, so that two
 // workgroups share a compute unit and hide each other's load latency instead.
+template <int DH, int KB>
+constexpr int kDqLds = (2 * KB * (DH + 8) + DH * (KB + 4)) * 2;
 template <int DH, int KB, bool PF>
-__global__ __launch_bounds__(256, PF ? 1 : 2) void k_attn_bwd_dq(const AttnArgs a, float* part, int nck, int ck) {
+DEV void attn_bwd_dq(const AttnArgs& a, float* part, int nck, int ck, const TileId id, uint8_t* smem) {
   constexpr int LDN = DH + 8, LDT_ = KB + 4, NKS = DH / 32, NT = DH / 16, NKT = KB / 16;
-  __shared__ __attribute__((aligned(16))) u16 Ks[KB * LDN];   // fp16 (scores)
-  __shared__ __attribute__((aligned(16))) u16 Vs[KB * LDN];   // bf16 (dP)
-  __shared__ __attribute__((aligned(16))) u16 Kt[DH * LDT_];  // bf16 (dQ product)
+  u16* Ks = (u16*)smem;      // [KB][LDN] fp16 (scores)
+  u16* Vs = Ks + KB * LDN;   // [KB][LDN] bf16 (dP)
+  u16* Kt = Vs + KB * LDN;   // [DH][LDT_] bf16 (dQ product)
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const TileId id = attn_tile(nck);
   const int tile = nck ? id.x / nck : id.x, chunk = nck ? id.x % nck : 0;
   const int T = a.T, h = id.y, b = id.z, grp = a.Hq / a.Hkv, kvh = h / grp;
   const int q0 = tile * 64, qw = q0 + 16 * w, q = qw + (lane & 15);
@@ -919,12 +922,38 @@ __global__ __launch_bounds__(256, PF ? 1 : 2) void k_attn_bwd_dq(const AttnArgs 
   }
 }
 
+template <int DH, int KB, bool PF>
+__global__ __launch_bounds__(256, PF ? 1 : 2) void k_attn_bwd_dq(const AttnArgs a, float* part, int nck, int ck) {
+  __shared__ __attribute__((aligned(16))) uint8_t smem[kDqLds<DH, KB>];
+  attn_bwd_dq<DH, KB, PF>(a, part, nck, ck, attn_tile(nck), smem);
+}
+template <int DH, int QB>
+__global__ __launch_bounds__(256) void k_attn_bwd_dkdv(const AttnArgs a, float* part, int nck, int cq) {
+  __shared__ __attribute__((aligned(16))) uint8_t smem[kDkdvLds<DH, QB>];
+  attn_bwd_dkdv<DH, QB>(a, part, nck, cq, attn_tile(nck), smem);
+}
+
+// Both halves of a split backward in one launch: the first nkv workgroups along x run key blocks
+// (the longer ones first), the rest query blocks. At these sizes each half alone leaves compute
+// units idle and one launch behind the other costs more than either runs (256 tokens, 14 heads of
+// 64: 17 us one after the other, 14 in one launch; their two sums 12 us and 6).
+template <int DH, int QB, int KB, bool PF>
+__global__ __launch_bounds__(256) void k_attn_bwd_both(const AttnArgs a, float* kv_part, int kv_nck, int cq, int nkv,
+                                                       float* q_part, int q_nck, int ck) {
+  constexpr int LDS = kDkdvLds<DH, QB> > kDqLds<DH, KB> ? kDkdvLds<DH, QB> : kDqLds<DH, KB>;
+  __shared__ __attribute__((aligned(16))) uint8_t smem[LDS];
+  const int bx = (int)blockIdx.x;
+  if (bx < nkv)
+    attn_bwd_dkdv<DH, QB>(a, kv_part, kv_nck, cq, TileId{bx, (int)blockIdx.y, (int)blockIdx.z}, smem);
+  else
+    attn_bwd_dq<DH, KB, PF>(a, q_part, q_nck, ck, TileId{bx - nkv, (int)blockIdx.y, (int)blockIdx.z}, smem);
+}
+
 // Sum of the key-chunk partials of k_attn_bwd_dq in chunk order, scale 1/sqrt(dh), RoPE
 // backward, bf16 store. One thread per (token, head, 4 columns of the first half of the
 // head) and their partners e + dh/2.
-__global__ void k_attn_dq_reduce(const AttnArgs a, const float* part, int nck, int ck, int KB) {
+DEV void attn_dq_reduce(const AttnArgs& a, const float* part, int nck, int ck, int KB, size_t i) {
   const int half = a.dh / 2, q4 = half / 4;
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= (size_t)a.B * a.T * a.Hq * q4) return;
   const int e = (int)(i % q4) * 4;
   const int h = (int)((i / q4) % a.Hq);
@@ -1414,48 +1443,70 @@ __host__ __device__ inline int kv_block_chunks(int kblk, int T, int window, int 
   return hi > k0 ? (hi - k0 + cq - 1) / cq : 0;
 }
 
-// dK/dV from the partial planes of the key-block kernels: sum the query chunks (nck > 0;
+// dK or dV from the partial planes of the key-block kernels: sum the query chunks (nck > 0;
 // else one) and, within each, the query heads of the KV group, in that order; scale dK by
 // 1/sqrt(dh), rotate it back (RoPE backward), store bf16. One thread per (token, kv
-// head, 4 columns of the first half of the head) and their partners.
-__global__ void k_attn_dkdv_reduce(const AttnArgs a, const float* part, int nck, int cq) {
+// head, dK or dV, 4 columns of the first half of the head) and their partners; the planes are
+// read four at a time, so that the sum is not one load's latency per plane.
+DEV void attn_dkdv_reduce(const AttnArgs& a, const float* part, int nck, int cq, size_t i) {
   const int half = a.dh / 2, q4 = half / 4;
-  const size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const size_t total = (size_t)a.B * a.T * a.Hkv * q4;
+  const size_t total = (size_t)a.B * a.T * a.Hkv * q4 * 2;
   if (i >= total) return;
-  const int e = (int)(i % q4) * 4;
-  const int kvh = (int)((i / q4) % a.Hkv);
-  const size_t row = i / ((size_t)q4 * a.Hkv);
+  const int e = (int)(i % q4) * 4, isv = (int)((i / q4) & 1);
+  const size_t rk = i / (2 * (size_t)q4);
+  const int kvh = (int)(rk % a.Hkv);
+  const size_t row = rk / a.Hkv;
   const int t = (int)(row % a.T), grp = a.Hq / a.Hkv;
-  const int n = nck ? kv_block_chunks(t / 64, a.T, a.window, cq) : 1;
+  const int n = (nck ? kv_block_chunks(t / 64, a.T, a.window, cq) : 1) * grp;
   const size_t plane = (size_t)a.B * a.T * a.Hkv * a.dh;
   const size_t o = row * (size_t)(a.Hkv * a.dh) + kvh * a.dh + e;
-  float k1[4] = {0, 0, 0, 0}, k2[4] = {0, 0, 0, 0}, v1[4] = {0, 0, 0, 0}, v2[4] = {0, 0, 0, 0};
-  for (int c = 0; c < n; ++c) {
-    const float* base = part + (size_t)c * 2 * grp * plane;
-    for (int g = 0; g < grp; ++g) {
-      const float4 a1 = *(const float4*)(base + g * plane + o), a2 = *(const float4*)(base + g * plane + o + half);
-      const float4 b1 = *(const float4*)(base + (grp + g) * plane + o);
-      const float4 b2 = *(const float4*)(base + (grp + g) * plane + o + half);
-      k1[0] += a1.x; k1[1] += a1.y; k1[2] += a1.z; k1[3] += a1.w;
-      k2[0] += a2.x; k2[1] += a2.y; k2[2] += a2.z; k2[3] += a2.w;
-      v1[0] += b1.x; v1[1] += b1.y; v1[2] += b1.z; v1[3] += b1.w;
-      v2[0] += b2.x; v2[1] += b2.y; v2[2] += b2.z; v2[3] += b2.w;
+  const float* base = part + (isv ? (size_t)grp * plane : 0) + o;
+  float d1[4] = {0, 0, 0, 0}, d2[4] = {0, 0, 0, 0};
+  for (int j0 = 0; j0 < n; j0 += 4) {
+    float4 x[4], y[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int j = min(j0 + u, n - 1);  // plane j % grp of chunk j / grp
+      const float* p = base + (size_t)(j + j / grp * grp) * plane;
+      x[u] = *(const float4*)p;
+      y[u] = *(const float4*)(p + half);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (j0 + u < n) {
+        d1[0] += x[u].x; d1[1] += x[u].y; d1[2] += x[u].z; d1[3] += x[u].w;
+        d2[0] += y[u].x; d2[1] += y[u].y; d2[2] += y[u].z; d2[3] += y[u].w;
+      }
+  }
+  bf16* out = (isv ? a.dv : a.dk) + o;
+  if (!isv) {
+    const float scale = 1.0f / sqrtf((float)a.dh);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const float2 cs = *(const float2*)(a.cs + 2 * ((size_t)t * half + e + j));
+      const float u = d1[j] * scale, v = d2[j] * scale;
+      d1[j] = u * cs.x + v * cs.y;
+      d2[j] = v * cs.x - u * cs.y;
     }
   }
-  const float scale = 1.0f / sqrtf((float)a.dh);
-  float lo[4], hi[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const float2 cs = *(const float2*)(a.cs + 2 * ((size_t)t * half + e + j));
-    const float d1 = k1[j] * scale, d2 = k2[j] * scale;
-    lo[j] = d1 * cs.x + d2 * cs.y;
-    hi[j] = d2 * cs.x - d1 * cs.y;
-  }
-  *(uint2*)(a.dk + o) = make_uint2(pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3]));
-  *(uint2*)(a.dk + o + half) = make_uint2(pack_bf16x2(hi[0], hi[1]), pack_bf16x2(hi[2], hi[3]));
-  *(uint2*)(a.dv + o) = make_uint2(pack_bf16x2(v1[0], v1[1]), pack_bf16x2(v1[2], v1[3]));
-  *(uint2*)(a.dv + o + half) = make_uint2(pack_bf16x2(v2[0], v2[1]), pack_bf16x2(v2[2], v2[3]));
+  *(uint2*)out = make_uint2(pack_bf16x2(d1[0], d1[1]), pack_bf16x2(d1[2], d1[3]));
+  *(uint2*)(out + half) = make_uint2(pack_bf16x2(d2[0], d2[1]), pack_bf16x2(d2[2], d2[3]));
+}
+
+__global__ void k_attn_dq_reduce(const AttnArgs a, const float* part, int nck, int ck, int KB) {
+  attn_dq_reduce(a, part, nck, ck, KB, (size_t)blockIdx.x * blockDim.x + threadIdx.x);
+}
+__global__ void k_attn_dkdv_reduce(const AttnArgs a, const float* part, int nck, int cq) {
+  attn_dkdv_reduce(a, part, nck, cq, (size_t)blockIdx.x * blockDim.x + threadIdx.x);
+}
+// both sums of a backward that ran as one launch (the first nkv workgroups sum dK and dV)
+__global__ void k_attn_bwd_reduce(const AttnArgs a, const float* kv_part, int kv_nck, int cq, int nkv,
+                                  const float* q_part, int q_nck, int ck, int KB) {
+  const int bx = (int)blockIdx.x;
+  if (bx < nkv)
+    attn_dkdv_reduce(a, kv_part, kv_nck, cq, (size_t)bx * blockDim.x + threadIdx.x);
+  else
+    attn_dq_reduce(a, q_part, q_nck, ck, KB, (size_t)(bx - nkv) * blockDim.x + threadIdx.x);
 }
 
 }  // namespace
@@ -1595,6 +1646,27 @@ hipError_t launch_attn_bwd(const AttnArgs& a0, float* delta_ws, const SplitScrat
   // algorithmic: dV, dK and dP products in the key-block kernel, dQ in the query-block kernel
   const double f_kv = 6.0 * a.dh * pairs, f_q = 2.0 * a.dh * pairs;
   const double io = (double)a.B * a.T * (a.Hq * a.dh * 2.0 * 2 + a.Hkv * a.dh * 2.0 * 4);
+  const unsigned rq = (unsigned)(((size_t)a.B * a.T * a.Hq * (a.dh / 8) + 255) / 256);
+  const unsigned rkv = (unsigned)(((size_t)a.B * a.T * a.Hkv * (a.dh / 4) + 255) / 256);
+  // split plans: both halves in one launch, both sums in another (head dim 128 has no split
+  // key-block kernel)
+  if (p.q_nck && p.kv_nck) {
+    const dim3 gb(gkv.x + gq.x, a.Hq, a.B);
+    if (a.dh == 64)
+      MEBP_TIMED(st, "attn_bwd_both", f_kv + f_q, 2 * io,
+                 hipLaunchKernelGGL((k_attn_bwd_both<64, 64, 64, true>), gb, dim3(256), 0, st, a, kv_part, p.kv_nck,
+                                    p.kv_cq, (int)gkv.x, q_part, p.q_nck, p.q_ck));
+    else
+      MEBP_TIMED(st, "attn_bwd_both", f_kv + f_q, 2 * io,
+                 hipLaunchKernelGGL((k_attn_bwd_both<256, 32, 32, false>), gb, dim3(256), 0, st, a, kv_part, p.kv_nck,
+                                    p.kv_cq, (int)gkv.x, q_part, p.q_nck, p.q_ck));
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    MEBP_TIMED(st, "attn_bwd_reduce", 0.0,
+               (double)(p.kv_floats + p.q_floats) * 4 + (double)a.B * a.T * (a.Hkv * a.dh * 4 + a.Hq * a.dh * 2),
+               hipLaunchKernelGGL(k_attn_bwd_reduce, dim3(rkv + rq), dim3(256), 0, st, a, (const float*)kv_part, p.kv_nck,
+                                  p.kv_cq, (int)rkv, (const float*)q_part, p.q_nck, p.q_ck, a.dh == 256 ? 32 : 64));
+    return hipGetLastError();
+  }
   // dQ depends only on delta and the forward tensors: with an auxiliary stream it runs
   // there while dK / dV run here
   const bool split = aux && ev_go && ev_done;
@@ -1614,9 +1686,8 @@ hipError_t launch_attn_bwd(const AttnArgs& a0, float* delta_ws, const SplitScrat
 #undef DQ
   if ((e = hipGetLastError()) != hipSuccess) return e;
   if (p.q_nck) {
-    const size_t nr = (size_t)a.B * a.T * a.Hq * (a.dh / 8);
     MEBP_TIMED(sq, "attn_dq_reduce", 0.0, (double)p.q_floats * 4 + (double)a.B * a.T * a.Hq * a.dh * 2,
-               hipLaunchKernelGGL(k_attn_dq_reduce, dim3((unsigned)((nr + 255) / 256)), dim3(256), 0, sq, a,
+               hipLaunchKernelGGL(k_attn_dq_reduce, dim3(rq), dim3(256), 0, sq, a,
                                   (const float*)q_part, p.q_nck, p.q_ck, a.dh == 256 ? 32 : 64));
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
@@ -1651,9 +1722,8 @@ hipError_t launch_attn_bwd(const AttnArgs& a0, float* delta_ws, const SplitScrat
     if ((e = hipEventRecord(ev_done, aux)) != hipSuccess) return e;
   }
   if (p.kv_floats) {
-    const size_t nr = (size_t)a.B * a.T * a.Hkv * (a.dh / 8);
     MEBP_TIMED(st, "attn_dkdv_reduce", 0.0, (double)p.kv_floats * 4 + (double)a.B * a.T * a.Hkv * a.dh * 4,
-               hipLaunchKernelGGL(k_attn_dkdv_reduce, dim3((unsigned)((nr + 255) / 256)), dim3(256), 0, st, a,
+               hipLaunchKernelGGL(k_attn_dkdv_reduce, dim3(rkv), dim3(256), 0, st, a,
                                   (const float*)kv_part, p.kv_nck, p.kv_cq));
     e = hipGetLastError();
     if (e != hipSuccess) return e;
