@@ -94,6 +94,7 @@ KERNEL_PATTERNS = {
     "gemm_tn_probs_dh": r"k_gemm_tn(_big|_lds)?<(\d+, )?2(, (true|false))?>|k_gemm_tn_frag<(\d+, ){3}2>",
     "gemm_tn_bf16out": r"k_gemm_tn(_big|_lds)?<(\d+, )?3(, (true|false))?>|k_gemm_tn_frag<(\d+, ){3}3>",
     "lora_rows": r"k_lora_rows<",
+    "norm_lora": r"k_norm_lora<",
     "lora_outer": r"k_lora_outer<",
     "attn_fwd": r"k_attn_fwd",
     "attn_bwd_dkdv": r"k_attn_bwd_(dkdv|kv32p?)<",

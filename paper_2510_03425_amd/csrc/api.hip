@@ -476,6 +476,8 @@ struct Ctx {
   hipEvent_t ev_lr;  // recorded on st, waited for by aux
   hipEvent_t ev_du;  // recorded on aux, waited for by st
   bool* aux_used;
+  // > 0: the layer's first launch also fills the RoPE table (rope_table)
+  double rope_theta;
 };
 
 // The workspace slot `s` as seen by this context (its activation set and scratch copy).
@@ -600,6 +602,33 @@ hipError_t lora_down(const Ctx& x, const mebp_layer_lora* lora, const f16* X, in
   return on_aux(x, ready, [&](hipStream_t st) { return launch_lora_rows(a, 0, st); });
 }
 
+// dst = fp16(RMSNorm(src) * w) and lora_down of `ps` on it. `rope`: the table that this layer's
+// first launch fills when the context says so.
+hipError_t norm_lora_down(const Ctx& x, const mebp_layer_lora* lora, const float* src, const float* w, f16* dst,
+                          std::initializer_list<int> ps, float* rope, hipEvent_t* ready) {
+  *ready = nullptr;
+  if (!norm_lora_ok(x.D.N, x.D.d)) {
+    const hipError_t e = launch_rmsnorm_fwd(src, w, x.D.N, x.D.d, x.c->rms_eps, dst, nullptr, x.st);
+    return e != hipSuccess ? e : lora_down(x, lora, dst, x.D.d, ps, ready);
+  }
+  NormLoraArgs a{};
+  a.x = src; a.w = w; a.y = dst;
+  a.M = x.D.N; a.K = x.D.d; a.r = x.D.r; a.eps = x.c->rms_eps;
+  // (the recompute that runs beside a backward keeps two launches: the step of 24 layers at 256
+  // tokens takes 7.02 ms with them and 7.16 with one, whose 16 workgroups hold up the other stream)
+  const bool beside = x.split_set != 0;
+  for (int p : ps) {
+    if (beside || !adapted(x, p)) continue;
+    a.W[a.njobs] = lora->A[p];
+    a.out[a.njobs++] = lu(x, p);
+  }
+  if (rope && x.rope_theta > 0.0) {
+    a.rope_T = x.T; a.rope_dh = x.c->head_dim; a.rope_theta = x.rope_theta; a.rope_cs = rope;
+  }
+  const hipError_t e = launch_norm_lora(a, x.st);
+  return e != hipSuccess || !beside ? e : lora_down(x, lora, dst, x.D.d, ps, ready);
+}
+
 // LoRA backward of the adapted projections among `ps`, with output gradients G_p (bf16
 // [N][out_p]) and the shared input X (fp16 [N][in]): du = s G B, dB = s G^T u, dA = du^T X.
 // Two launches for all of them (and a reduce at many tokens). The input-gradient GEMM that adds du A waits for *ready;
@@ -647,10 +676,11 @@ hipError_t lora_bwd(const Ctx& x, const mebp_layer_lora* lora, const mebp_layer_
 // next_norm (forward loop only): the RMSNorm weights of the next block's input norm; the
 // down projection's split-K finalize then also writes that block's normalised input (into
 // `next_out`, default the activation slot `a`; one row kernel fewer per layer), and a_ready
-// tells the next layer to skip its own input norm.
+// tells the next layer to skip its own input norm. With next_pending a product without a
+// finalize leaves that norm to the next layer and says so there.
 int layer_forward(const Ctx& x, int l, const mebp_layer_base* base, const mebp_layer_lora* lora, const float* x_in,
-                  float* x_out, const float* rope, bool keep, const float* next_norm = nullptr,
-                  bool a_ready = false, f16* next_out = nullptr) {
+                  float* x_out, float* rope, bool keep, const float* next_norm = nullptr,
+                  bool a_ready = false, f16* next_out = nullptr, bool* next_pending = nullptr) {
   const mebp_config* c = x.c;
   const Dims& D = x.D;
   f16* a = xs<f16>(x, S_A);
@@ -664,9 +694,11 @@ int layer_forward(const Ctx& x, int l, const mebp_layer_base* base, const mebp_l
   f16* u = xs<f16>(x, S_U);
   f16* z = xs<f16>(x, S_Z);
 
-  if (!a_ready) HIP_TRY(launch_rmsnorm_fwd(x_in, base->norm_attn, D.N, D.d, c->rms_eps, a, nullptr, x.st));
   hipEvent_t lr;
-  HIP_TRY(lora_down(x, lora, a, D.d, {MEBP_Q, MEBP_K, MEBP_V}, &lr));
+  if (a_ready)
+    HIP_TRY(lora_down(x, lora, a, D.d, {MEBP_Q, MEBP_K, MEBP_V}, &lr));
+  else
+    HIP_TRY(norm_lora_down(x, lora, x_in, base->norm_attn, a, {MEBP_Q, MEBP_K, MEBP_V}, rope, &lr));
   // bias and per-head norm come between the projection and RoPE: then RoPE moves out of the
   // GEMM's follow-up into the kernel that applies them
   const bool qk_post = c->arch & (MEBP_ARCH_QKV_BIAS | MEBP_ARCH_QK_NORM);
@@ -683,13 +715,14 @@ int layer_forward(const Ctx& x, int l, const mebp_layer_base* base, const mebp_l
   }
   if (qk_post) {
     const bool bias = c->arch & MEBP_ARCH_QKV_BIAS, qkn = c->arch & MEBP_ARCH_QK_NORM;
-    HIP_TRY(launch_qkv_post(q, D.qd, D.N, x.T, c->n_heads, c->head_dim, bias ? base->bias[0] : nullptr,
-                            qkn ? base->q_norm : nullptr, c->rms_eps, xs<f16>(x, S_QPRE), rope, 1, x.st));
-    HIP_TRY(launch_qkv_post(k, D.kvd, D.N, x.T, c->n_kv_heads, c->head_dim, bias ? base->bias[1] : nullptr,
-                            qkn ? base->k_norm : nullptr, c->rms_eps, xs<f16>(x, S_KPRE), rope, 1, x.st));
-    if (bias)
-      HIP_TRY(launch_qkv_post(v, D.kvd, D.N, x.T, c->n_kv_heads, c->head_dim, base->bias[2], nullptr, c->rms_eps,
-                              nullptr, rope, 0, x.st));
+    QkvPostArgs pa{};
+    pa.n = D.N; pa.T = x.T; pa.dh = c->head_dim; pa.eps = c->rms_eps; pa.cs = rope;
+    pa.job[pa.njobs++] = QkvPostJob{q, D.qd, c->n_heads, bias ? base->bias[0] : nullptr, qkn ? base->q_norm : nullptr,
+                                    xs<f16>(x, S_QPRE), 1};
+    pa.job[pa.njobs++] = QkvPostJob{k, D.kvd, c->n_kv_heads, bias ? base->bias[1] : nullptr,
+                                    qkn ? base->k_norm : nullptr, xs<f16>(x, S_KPRE), 1};
+    if (bias) pa.job[pa.njobs++] = QkvPostJob{v, D.kvd, c->n_kv_heads, base->bias[2], nullptr, nullptr, 0};
+    HIP_TRY(launch_qkv_post(pa, x.st));
   }
   AttnArgs at{};
   at.q = q; at.k = k; at.v = v; at.ldq = D.qd; at.ldk = D.kvd;
@@ -698,21 +731,25 @@ int layer_forward(const Ctx& x, int l, const mebp_layer_base* base, const mebp_l
   at.o = o; at.lse = xs<float>(x, S_LSE);
   HIP_TRY(launch_attn_fwd(at, split_scratch(x), x.st));
   HIP_TRY(lora_down(x, lora, o, D.qd, {MEBP_O}, &lr));
+  bool norm_here = sandwich;  // c = RMSNorm(h) is still to be done, with its adapters
   if (sandwich) {
     // t = o-projection (kept for the backward), h = x + RMSNorm(t), c = RMSNorm(h)
     float* to = xs<float>(x, S_TO);
     HIP_TRY(launch_gemm_nt(nt_args(x, o, D.qd, {nt_seg(x, base, lora, MEBP_O, to, D.d, nullptr, 0)}), NT_STORE_F32, x.st,
                            lr));
     HIP_TRY(launch_resid_rmsnorm(x_in, to, base->post_attn_norm, D.N, D.d, c->rms_eps, h, x.st));
-    HIP_TRY(launch_rmsnorm_fwd(h, base->norm_mlp, D.N, D.d, c->rms_eps, cc, nullptr, x.st));
   } else {
     // h = x + o-projection, then c = RMSNorm(h)
     NtArgs na = nt_args(x, o, D.qd, {nt_seg(x, base, lora, MEBP_O, h, D.d, x_in, D.d)});
     na.norm_w = base->norm_mlp;
     na.norm_out = cc;
+    na.norm_pending = &norm_here;
     HIP_TRY(launch_gemm_nt(na, NT_STORE_F32, x.st, lr));
   }
-  HIP_TRY(lora_down(x, lora, cc, D.d, {MEBP_GATE, MEBP_UP}, &lr));
+  if (norm_here)
+    HIP_TRY(norm_lora_down(x, lora, h, base->norm_mlp, cc, {MEBP_GATE, MEBP_UP}, nullptr, &lr));
+  else
+    HIP_TRY(lora_down(x, lora, cc, D.d, {MEBP_GATE, MEBP_UP}, &lr));
   {
     // g, u projections and z = act(g) * u (g and u kept only for the backward)
     NtArgs na = nt_args(x, cc, D.d, {nt_seg(x, base, lora, MEBP_GATE, g, D.F, nullptr, 0),
@@ -735,6 +772,7 @@ int layer_forward(const Ctx& x, int l, const mebp_layer_base* base, const mebp_l
     if (next_norm) {
       na.norm_w = next_norm;  // y = h + down(z), and the next block's input RMSNorm(y)
       na.norm_out = next_out ? next_out : a;
+      na.norm_pending = next_pending;
     }
     HIP_TRY(launch_gemm_nt(na, NT_STORE_F32, x.st, lr));
   } else if (lr)
@@ -871,7 +909,7 @@ int layer_backward_only(const Ctx& x, int l, const mebp_layer_base* base, const 
 // Recompute (Algorithm 1's second loop: forward from the checkpoint) then backward.
 int layer_backward(const Ctx& x, int l, const mebp_layer_base* base, const mebp_layer_lora* lora,
                    const float* x_ckpt, const float* dy, float* dx, const mebp_layer_lora_grad* grads,
-                   const float* rope, bool dy_bf16_ready = false) {
+                   float* rope, bool dy_bf16_ready = false) {
   const int e = layer_forward(x, l, base, lora, x_ckpt, nullptr, rope, true);
   if (e) return e;
   return layer_backward_only(x, l, base, lora, x_ckpt, dy, dx, grads, rope, dy_bf16_ready);
@@ -958,13 +996,20 @@ Ctx make_ctx(const mebp_config* c, int B, int T, void* ws, mebp_stream_t stream,
   x.ev_lr = nullptr;
   x.ev_du = nullptr;
   x.aux_used = nullptr;
+  x.rope_theta = 0.0;
   return x;
 }
 
-int rope_table(const Ctx& x, int l, float** out) {
+// The RoPE table of a single layer's call: by the layer's first launch where that is the norm with
+// its adapters, else by a launch of its own.
+int rope_table(Ctx& x, int l, float** out) {
   const bool glob = is_global(x.c, l);
+  const double theta = glob ? x.c->rope_theta_global : x.c->rope_theta_local;
   float* cs = xs<float>(x, glob ? S_ROPE_G : S_ROPE_L);
-  HIP_TRY(launch_rope_table(x.T, x.c->head_dim, glob ? x.c->rope_theta_global : x.c->rope_theta_local, cs, x.st));
+  if (norm_lora_ok(x.D.N, x.D.d))
+    x.rope_theta = theta;
+  else
+    HIP_TRY(launch_rope_table(x.T, x.c->head_dim, theta, cs, x.st));
   *out = cs;
   return MEBP_OK;
 }
@@ -1106,8 +1151,9 @@ int train_step_impl(const mebp_config* cfg, const mebp_q4* emb, const mebp_layer
       xf.ev_lr = side->ev_lr;
       xf.ev_du = side->ev_du;
     }
+    bool pending = false;  // the previous layer left this one's input norm to it
     for (int l = 0; l < L; ++l) {
-      const float* rope = is_global(cfg, l) ? rope_g : rope_l;
+      float* rope = is_global(cfg, l) ? rope_g : rope_l;
       // the slot of x_{l+1} last held x_{l+1-R}: its copy to the host must be done
       if (off && l + 1 >= off->R) HIP_TRY(hipStreamWaitEvent(x.st, off->ev_out[(l + 1) % off->R], 0));
       // the next layer's input norm rides on this layer's down-projection finalize (not with
@@ -1115,7 +1161,10 @@ int train_step_impl(const mebp_config* cfg, const mebp_q4* emb, const mebp_layer
       const bool fuse = !(cfg->arch & MEBP_ARCH_SANDWICH);
       const float* nn = !fuse ? nullptr : l + 1 < L ? layers[l + 1].norm_attn : norm_final;
       f16* nout = l + 1 < L ? nullptr : slot<f16>(ws, x.L, S_HF);
-      if ((e = layer_forward(xf, l, &layers[l], &lora[l], ck(l), ck(l + 1), rope, false, nn, fuse && l > 0, nout)))
+      const bool a_ready = fuse && l > 0 && !pending;
+      pending = false;
+      if ((e = layer_forward(xf, l, &layers[l], &lora[l], ck(l), ck(l + 1), rope, false, nn, a_ready, nout,
+                             nout ? nullptr : &pending)))
         return e;
       if (off && (e = save(l + 1, x.st))) return e;
     }
@@ -1142,7 +1191,7 @@ int train_step_impl(const mebp_config* cfg, const mebp_q4* emb, const mebp_layer
     for (int l = L - 1; l >= 0; --l) {
       Ctx b = x;
       b.set = l & 1;
-      const float* rope = is_global(cfg, l) ? rope_g : rope_l;
+      float* rope = is_global(cfg, l) ? rope_g : rope_l;
       float* dxl = l > 0 ? g : dx0;
       if (!resident(l)) HIP_TRY(hipStreamWaitEvent(x.st, off->ev_in[l % off->R], 0));
       if ((e = layer_backward(b, l, &layers[l], &lora[l], ck(l), g, dxl, grads ? &grads[l] : nullptr, rope, true)))
@@ -1160,7 +1209,7 @@ int train_step_impl(const mebp_config* cfg, const mebp_q4* emb, const mebp_layer
     r.split_set = 1;
     auto recompute = [&](int l) -> int {
       r.set = l & 1;
-      const float* rope = is_global(cfg, l) ? rope_g : rope_l;
+      float* rope = is_global(cfg, l) ? rope_g : rope_l;
       if (!resident(l)) HIP_TRY(hipStreamWaitEvent(side->st, off->ev_in[l % off->R], 0));
       return layer_forward(r, l, &layers[l], &lora[l], ck(l), nullptr, rope, true);
     };
@@ -1187,7 +1236,7 @@ int train_step_impl(const mebp_config* cfg, const mebp_q4* emb, const mebp_layer
       b.ev_lr = side->ev_lr;
       b.ev_du = side->ev_du;
       b.aux_used = &aux_used;
-      const float* rope = is_global(cfg, l) ? rope_g : rope_l;
+      float* rope = is_global(cfg, l) ? rope_g : rope_l;
       float* dxl = l > 0 ? g : dx0;
       if ((e = layer_backward_only(b, l, &layers[l], &lora[l], ck(l), g, dxl, grads ? &grads[l] : nullptr, rope,
                                    true)))

@@ -86,6 +86,17 @@ DEV uint4 dequant8(uint32_t w, float s) {
   return r;
 }
 
+// entry i of the RoPE table: cs[t][j] = (cos, sin)(t * theta^(-2j/dh)), computed in fp64
+DEV void rope_table_entry(int i, int T, int dh, double theta, float* cs) {
+  const int half = dh >> 1;
+  if (i >= T * half) return;
+  const int t = i / half, j = i % half;
+  const double inv = pow(theta, -(2.0 * j) / (double)dh);
+  const double ang = (double)t * inv;
+  cs[2 * i] = (float)cos(ang);
+  cs[2 * i + 1] = (float)sin(ang);
+}
+
 DEV float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

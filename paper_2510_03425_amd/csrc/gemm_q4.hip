@@ -913,7 +913,9 @@ hipError_t launch_gemm_nt(const NtArgs& a0, int epi, hipStream_t st, hipEvent_t 
     if (em != hipSuccess || epi == NT_LOGITS) return em;
     if (S == 1) {
       // every follow-up but the row norm is in the product's epilogue
-      if (a.norm_w)
+      if (a.norm_w && a.norm_pending)
+        *a.norm_pending = true;
+      else if (a.norm_w)
         return launch_rmsnorm_fwd((const float*)a.seg[0].out, a.norm_w, a.M, a.seg[0].N, a.eps, a.norm_out, nullptr, st);
       return hipSuccess;
     }
@@ -949,7 +951,9 @@ hipError_t launch_gemm_nt(const NtArgs& a0, int epi, hipStream_t st, hipEvent_t 
     if (a.gated && !fused_act)
       return launch_act_fwd((const f16*)a.seg[0].out, (const f16*)a.seg[1].out, a.z_out, (size_t)a.M * a.seg[0].N,
                             a.act, st);
-    if (a.norm_w)
+    if (a.norm_w && a.norm_pending)
+      *a.norm_pending = true;
+    else if (a.norm_w)
       return launch_rmsnorm_fwd((const float*)a.seg[0].out, a.norm_w, a.M, a.seg[0].N, a.eps, a.norm_out, nullptr, st);
     return hipSuccess;
   }

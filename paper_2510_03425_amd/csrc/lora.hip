@@ -148,6 +148,178 @@ __global__ __launch_bounds__(64 * LR_WAVES) void k_lora_rows(const LoraRowsArgs 
   }
 }
 
+// ------------------------------------------------------------------------- norm and rows
+// A block's input RMSNorm with the down-projections that read it (the q, k, v or gate, up
+// adapters), for the sizes whose row products take 16-row workgroups: y = fp16(x w rstd) and
+// out_j = y A_j^T. Eight waves share 16 rows and split K as in k_lora_rows; a wave holds its
+// NS super-steps of x in registers in the layout of the product's operand, so the normalised
+// values go into it without another pass, and stores them on the way. The row statistics meet in
+// LDS (one barrier). The adapters' and the norm's weights of PD super-steps are in flight ahead:
+// the chain of a launch is one latency for x, one for the weights (512 tokens of 1152 with q, k,
+// v and the table: 23 us as three launches, 14 here; 128 tokens of 896: 16.5 and 9.5; 4096 tokens
+// of 1536: 27 and 20).
+// Workgroups past the rows fill the RoPE table (as k_rope_table, in fp64), which is first read by
+// the product behind this launch.
+template <int NJ, int NS>
+__global__ __launch_bounds__(64 * LR_WAVES) void k_norm_lora(const NormLoraArgs a) {
+  __shared__ float red[LR_WAVES][16][17];
+  __shared__ float sq[LR_WAVES][16];
+  const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if ((int)blockIdx.x >= a.nrow) {
+    rope_table_entry(((int)blockIdx.x - a.nrow) * 64 * LR_WAVES + tid, a.rope_T, a.rope_dh, a.rope_theta, a.rope_cs);
+    return;
+  }
+  constexpr int PD = NS <= 5 ? 2 : 1;
+  const int m0 = blockIdx.x * 16, M = a.M, K = a.K, r = a.r, j = lane & 15, ko = 8 * (lane >> 4);
+  const rsrc_t rX = make_rsrc(a.x + (size_t)m0 * K, (size_t)min(16, M - m0) * K * 4);
+  const rsrc_t rG = make_rsrc(a.w, (size_t)K * 4);
+  auto f32x8 = [](rsrc_t rs, uint32_t o, float (&f)[8]) {
+    const uint4 p = bload128(rs, o), q = bload128(rs, o + 16);
+    f[0] = __builtin_bit_cast(float, p.x); f[1] = __builtin_bit_cast(float, p.y);
+    f[2] = __builtin_bit_cast(float, p.z); f[3] = __builtin_bit_cast(float, p.w);
+    f[4] = __builtin_bit_cast(float, q.x); f[5] = __builtin_bit_cast(float, q.y);
+    f[6] = __builtin_bit_cast(float, q.z); f[7] = __builtin_bit_cast(float, q.w);
+  };
+  // chunk k of super-step s (K is a multiple of 8: wholly inside the row or wholly past it, where
+  // the offset gets the sign bit and reads 0)
+  auto kof = [&](int s, int hh) { return (w + LR_WAVES * s) * 64 + 32 * hh + ko; };
+  auto past = [&](int k) { return (uint32_t)(K - 1 - k) & 0x80000000u; };
+  float xv[NS][2][8], gv[PD][2][8], wv[PD][NJ][2][8];
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) f32x8(rX, (uint32_t)(j * K + kof(s, hh)) * 4 | past(kof(s, hh)), xv[s][hh]);
+  auto load_w = [&](int s, float (&g)[2][8], float (&wj)[NJ][2][8]) {
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      const int k = kof(s, hh);
+      f32x8(rG, (uint32_t)k * 4 | past(k), g[hh]);
+#pragma unroll
+      for (int q = 0; q < NJ; ++q)
+        f32x8(make_rsrc(a.W[q], (size_t)r * K * 4), (uint32_t)(j * K + k) * 4 | past(k), wj[q][hh]);
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < PD; ++s) load_w(s, gv[s], wv[s]);
+  float ss = 0.f;
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) ss += xv[s][hh][i] * xv[s][hh][i];
+  ss += __shfl_xor(ss, 16, 64);
+  ss += __shfl_xor(ss, 32, 64);
+  if (lane < 16) sq[w][lane] = ss;
+  __syncthreads();
+  ss = 0.f;
+#pragma unroll
+  for (int ww = 0; ww < LR_WAVES; ++ww) ss += sq[ww][j];
+  const float rs = 1.0f / sqrtf(ss / (float)K + a.eps);
+  f32x4 acc[NJ];
+#pragma unroll
+  for (int q = 0; q < NJ; ++q) acc[q] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int s = 0; s < NS; ++s) {
+    float (&g)[2][8] = gv[s % PD];
+    float (&wj)[NJ][2][8] = wv[s % PD];
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      const int k = kof(s, hh);
+      const float (&x)[8] = xv[s][hh];
+      uint4 h;
+      h.x = pack_f16x2(x[0] * rs * g[hh][0], x[1] * rs * g[hh][1]);
+      h.y = pack_f16x2(x[2] * rs * g[hh][2], x[3] * rs * g[hh][3]);
+      h.z = pack_f16x2(x[4] * rs * g[hh][4], x[5] * rs * g[hh][5]);
+      h.w = pack_f16x2(x[6] * rs * g[hh][6], x[7] * rs * g[hh][7]);
+      if (m0 + j < M && k < K) *(uint4*)(a.y + (size_t)(m0 + j) * K + k) = h;
+#pragma unroll
+      for (int q = 0; q < NJ; ++q) {
+        uint4 bh, bl;
+        split_hi_lo<OpF16>(wj[q][hh], bh, bl);
+        acc[q] = mfma16_raw<OpF16>(h, bh, acc[q]);
+        acc[q] = mfma16_raw<OpF16>(h, bl, acc[q]);
+      }
+    }
+    if (s + PD < NS) load_w(s + PD, g, wj);
+  }
+  // lane holds rows 4 (lane / 16) + rr, column j; one job at a time through the LDS tile
+#pragma unroll
+  for (int q = 0; q < NJ; ++q) {
+    if (q) __syncthreads();  // the previous job's sums have been read
+#pragma unroll
+    for (int rr = 0; rr < 4; ++rr) red[w][4 * (lane >> 4) + rr][j] = acc[q][rr];
+    __syncthreads();
+    if (tid < 256) {
+      const int mm = tid >> 4, jj = tid & 15, m = m0 + mm;
+      if (m < M && jj < r) {
+        float v = 0.f;
+#pragma unroll
+        for (int ww = 0; ww < LR_WAVES; ++ww) v += red[ww][mm][jj];
+        a.out[q][(size_t)m * r + jj] = v;
+      }
+    }
+  }
+}
+
+// The same norm where no adapter reads it, two rows per wave: lane 4 v + g of a row's 32 sums what
+// wave v and lane group g sum above, and the sums meet in the same order, so that an adapter of
+// zeros changes no bit (256 tokens of 896: 4 us; the kernel above without products 7).
+template <int NS>
+__global__ __launch_bounds__(256) void k_norm_plain(const NormLoraArgs a) {
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  if ((int)blockIdx.x >= a.nrow) {
+    rope_table_entry(((int)blockIdx.x - a.nrow) * 256 + tid, a.rope_T, a.rope_dh, a.rope_theta, a.rope_cs);
+    return;
+  }
+  const int m = blockIdx.x * 8 + 2 * w + (lane >> 5), K = a.K, v = (lane >> 2) & 7, ko = 8 * (lane & 3);
+  const bool ok = m < a.M;
+  const rsrc_t rX = make_rsrc(a.x + (size_t)blockIdx.x * 8 * K, (size_t)min(8, a.M - (int)blockIdx.x * 8) * K * 4);
+  const rsrc_t rG = make_rsrc(a.w, (size_t)K * 4);
+  auto kof = [&](int s, int hh) { return (v + LR_WAVES * s) * 64 + 32 * hh + ko; };
+  float4 x[NS][2][2], g[NS][2][2];
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        const int k = kof(s, hh);
+        const uint32_t past = (uint32_t)(K - 1 - k) & 0x80000000u;
+        x[s][hh][u] = __builtin_bit_cast(float4, bload128(rX, (uint32_t)((2 * w + (lane >> 5)) * K + k + 4 * u) * 4 | past));
+        g[s][hh][u] = __builtin_bit_cast(float4, bload128(rG, (uint32_t)(k + 4 * u) * 4 | past));
+      }
+  float ss = 0.f;
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh)
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        ss += x[s][hh][u].x * x[s][hh][u].x;
+        ss += x[s][hh][u].y * x[s][hh][u].y;
+        ss += x[s][hh][u].z * x[s][hh][u].z;
+        ss += x[s][hh][u].w * x[s][hh][u].w;
+      }
+  ss += __shfl_xor(ss, 1, 64);
+  ss += __shfl_xor(ss, 2, 64);
+  float t = 0.f;
+#pragma unroll
+  for (int ww = 0; ww < LR_WAVES; ++ww) t += __shfl(ss, (lane & 32) + 4 * ww, 64);
+  const float rs = 1.0f / sqrtf(t / (float)K + a.eps);
+#pragma unroll
+  for (int s = 0; s < NS; ++s)
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      const int k = kof(s, hh);
+      const float4 x0 = x[s][hh][0], x1 = x[s][hh][1], g0 = g[s][hh][0], g1 = g[s][hh][1];
+      if (ok && k < K)
+        *(uint4*)(a.y + (size_t)m * K + k) =
+            make_uint4(pack_f16x2(x0.x * rs * g0.x, x0.y * rs * g0.y), pack_f16x2(x0.z * rs * g0.z, x0.w * rs * g0.w),
+                       pack_f16x2(x1.x * rs * g1.x, x1.y * rs * g1.y), pack_f16x2(x1.z * rs * g1.z, x1.w * rs * g1.w));
+    }
+}
+
 // ----------------------------------------------------------------------------- outer
 // R(c, j) = s * sum_m Mx[m][c] V[m][j] for every job of a stage in one launch (dB and dA; jobs
 // that share Mx, such as dA of q, k, v, form a group that reads it once). A wave owns 64 columns
@@ -416,6 +588,38 @@ hipError_t launch_lora_rows(const LoraRowsArgs& a, int xbf16, hipStream_t st) {
     if (nj == 3) LR_GO(OpF16, 3); else if (nj == 2) LR_GO(OpF16, 2); else LR_GO(OpF16, 1);
   }
 #undef LR_GO
+  return hipGetLastError();
+}
+
+bool norm_lora_ok(int M, int K) { return (M + 31) / 32 < 256 && (K & 7) == 0 && K <= 64 * LR_WAVES * 8; }
+
+hipError_t launch_norm_lora(const NormLoraArgs& a0, hipStream_t st) {
+  NormLoraArgs a = a0;
+  if (!norm_lora_ok(a.M, a.K) || a.njobs < 0 || a.njobs > 3) return hipErrorInvalidValue;
+  const int per = a.njobs ? 64 * LR_WAVES : 256;
+  a.nrow = a.njobs ? (a.M + 15) / 16 : (a.M + 7) / 8;
+  const int nrope = a.rope_cs ? (a.rope_T * (a.rope_dh / 2) + per - 1) / per : 0;
+  const dim3 grid(a.nrow + nrope), blk(per);
+  const double flops = 2.0 * a.M * a.K * a.r * a.njobs;
+  const double bytes = (double)a.M * a.K * 6 + a.njobs * ((double)a.K * a.r * 4 + (double)a.M * a.r * 4);
+  const int ns = (a.K + 64 * LR_WAVES - 1) / (64 * LR_WAVES);
+#define NL_GO(NJ, NS) \
+  MEBP_TIMED(st, "norm_lora", flops, bytes, hipLaunchKernelGGL((k_norm_lora<NJ, NS>), grid, blk, 0, st, a))
+#define NL_NS(NJ)                \
+  do {                           \
+    if (ns <= 2) NL_GO(NJ, 2);   \
+    else if (ns == 3) NL_GO(NJ, 3); \
+    else if (ns <= 5) NL_GO(NJ, 5); \
+    else NL_GO(NJ, 8);           \
+  } while (0)
+  if (a.njobs == 3) NL_NS(3); else if (a.njobs == 2) NL_NS(2); else if (a.njobs == 1) NL_NS(1);
+  else {
+#define NP_GO(NS) MEBP_TIMED(st, "rmsnorm_fwd", 0.0, bytes, hipLaunchKernelGGL(k_norm_plain<NS>, grid, blk, 0, st, a))
+    if (ns <= 2) NP_GO(2); else if (ns == 3) NP_GO(3); else if (ns <= 5) NP_GO(5); else NP_GO(8);
+#undef NP_GO
+  }
+#undef NL_NS
+#undef NL_GO
   return hipGetLastError();
 }
 

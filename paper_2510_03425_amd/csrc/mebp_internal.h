@@ -62,6 +62,7 @@ struct NtArgs {
   int store_gu;           // gated: also store g and u (fp16) into seg[0].out / seg[1].out
   const float* norm_w;    // single fp32-output segment h: c = fp16(rmsnorm(h) * w) into norm_out
   f16* norm_out;
+  bool* norm_pending;     // (host) given: an unsplit product leaves the norm to the caller and sets it
   float eps;
 };
 // lora_ready (optional): an event the launch waits on right before the first kernel that
@@ -191,10 +192,22 @@ hipError_t launch_embed(const uint8_t* q4, const uint16_t* scale, int d, int gro
 // out = resid + RMSNorm(t) * w (row-wise)
 hipError_t launch_resid_rmsnorm(const float* resid, const float* t, const float* w, int n, int d, float eps,
                                 float* out, hipStream_t st);
-// in place on fp16 q or k heads [n][ld]: + bias (if any), per-head RMSNorm with weight nw (if
-// any; pre-norm values to `pre`, same layout), RoPE (if rope); for v: bias only
-hipError_t launch_qkv_post(f16* x, int ld, int n, int T, int H, int dh, const float* bias, const float* nw, float eps,
-                           f16* pre, const float* cs, int rope, hipStream_t st);
+// in place on fp16 q, k or v heads [n][ld], one job each: + bias (if any), per-head RMSNorm with
+// weight nw (if any; pre-norm values to `pre`, same layout), RoPE (if rope)
+struct QkvPostJob {
+  f16* x;
+  int ld, H;
+  const float *bias, *nw;
+  f16* pre;
+  int rope;
+};
+struct QkvPostArgs {
+  QkvPostJob job[3];
+  int njobs, n, T, dh;
+  float eps;
+  const float* cs;
+};
+hipError_t launch_qkv_post(const QkvPostArgs& a, hipStream_t st);
 // per-head RMSNorm backward in place on bf16 g [n][ldg] from pre-norm values pre [n][ld]
 hipError_t launch_headnorm_bwd(const f16* pre, int ld, int n, int H, int dh, const float* nw, float eps, bf16* g,
                                int ldg, hipStream_t st);
@@ -231,6 +244,22 @@ struct LoraRowsArgs {
   float s;
 };
 hipError_t launch_lora_rows(const LoraRowsArgs& a, int xbf16, hipStream_t st);
+// y = fp16(rmsnorm(x) * w) [M][K] and out_j = y W_j^T (W_j [r][K]) of up to three jobs, for the
+// sizes that norm_lora_ok takes; with rope_cs also the RoPE table of rope_T positions.
+struct NormLoraArgs {
+  const float *x, *w;
+  f16* y;
+  int M, K, r, njobs;
+  float eps;
+  const float* W[3];
+  float* out[3];
+  int rope_T, rope_dh;
+  double rope_theta;
+  float* rope_cs;
+  int nrow;  // set by the launcher
+};
+bool norm_lora_ok(int M, int K);
+hipError_t launch_norm_lora(const NormLoraArgs& a, hipStream_t st);
 // Outer: R(c, j) = s * sum_m Mx[m][c] V[m][j], written as out[c*r + j] (layout 0, dB [C][r]) or
 // out[j*C + c] (layout 1, dA [r][C]), for up to three jobs of a group that share Mx [M][ldm]
 // (fp16 when f16in, else bf16), V fp32 [M][r]; up to four groups in one launch. Token-split

@@ -55,3 +55,34 @@ def test_attention_backward_in_one_launch(built_lib, gpu, case):
     say("attention backward", case)
     errs = _layer_errors(gpu, cfg, 0, 21)
     assert max(errs.values()) <= TOL, errs
+
+
+# a block's input norm with the adapters that read it (and the RoPE table) in one launch: one to
+# eight 64-wide super-steps per wave (waves without any; a last one half full; the first width
+# past the kernel), one row, one row past a workgroup, and one, two or none of the adapters
+NORM_CASES = [
+    # hidden, batch, tokens, modules, rank, arch
+    (64, 1, 17, "all", 8, {}),
+    (96, 1, 2, "all", 16, dict(qkv_bias=True)),
+    (512, 3, 11, "qv", 8, dict(sandwich_norm=True)),
+    (544, 1, 40, "kg", 16, {}),
+    (1088, 1, 33, "all", 16, dict(qk_norm=True, qkv_bias=True)),
+    (1568, 2, 16, "qvu", 8, {}),
+    (2592, 1, 15, "all", 8, {}),
+    (4096, 1, 18, "all", 16, dict(sandwich_norm=True)),
+    (4160, 1, 18, "all", 8, {}),
+    (320, 1, 70, "od", 8, dict(qkv_bias=True)),
+]
+
+
+@pytest.mark.parametrize("case", NORM_CASES, ids=lambda c: f"d{c[0]}-{c[1]}x{c[2]}-{c[3]}")
+def test_norm_and_adapters_in_one_launch(built_lib, gpu, case):
+    """Bound: as in every layer test; a wrong chunk of K or row is an error of order one."""
+    d, b, t, mods, r, arch = case
+    names = dict(q="q", k="k", v="v", o="o", g="gate", u="up", d="down")
+    cfg = Config(name="norm", n_layers=1, hidden=d, n_heads=2, n_kv_heads=1, head_dim=64, ffn=192, vocab=0, act="silu",
+                 lora_rank=r, lora_alpha=2.0 * r, lora_modules=ALL7 if mods == "all" else tuple(names[m] for m in mods),
+                 batch=b, seq=t, **arch)
+    say("norm and adapters", case)
+    errs = _layer_errors(gpu, cfg, 0, 22)
+    assert max(errs.values()) <= TOL, errs
