@@ -2,7 +2,7 @@
 // gradient projection du = s dY B (both "rows": r <= 16 outputs per token, reduction over
 // the model dimension), and the weight gradients dB = s dY^T u, dA = du^T X ("outer":
 // reduction over tokens). Up to three projections that share a stage of the layer (q, k,
-// v; gate, up) run in one launch (blockIdx.y selects the projection).
+// v; gate, up) run in one launch.
 //
 // The 16-bit activation / gradient operand is used as stored; the fp32 adapter weights
 // (A, B) and fp32 u / du enter the MFMA as a hi + lo pair of 16-bit values (two MFMAs),
@@ -10,7 +10,7 @@
 //
 // "rows" keeps the whole reduction inside one workgroup (its waves split K, partial
 // tiles summed through LDS in wave order). "outer" splits the token range over
-// blockIdx.z when there are many tokens; the split partials are then summed in split
+// the grid when there are many tokens; the split partials are then summed in split
 // order by a small reduce kernel. Both are deterministic.
 #include "device_common.h"
 #include "mebp_internal.h"
