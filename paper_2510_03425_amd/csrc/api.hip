@@ -102,7 +102,9 @@ struct Layout {
   int32_t g_tag[kMaxGuards];
   size_t status_off;          // one word: the smallest tag of an overwritten guard
   int lm_chunk;   // vocabulary columns per LM-head chunk
-  int lm_splits;  // split-K factor of a whole chunk's dH product (narrower chunks use fewer)
+  // split-K factor of the dH product of a whole chunk and of the last one, which may be narrower
+  // and split further; lm_planes, the larger one, is what the plane buffer holds
+  int lm_splits, lm_last_splits, lm_planes;
   int ntiles;     // statistics tiles of a whole chunk (the stats row pitch)
   size_t split_floats, split_floats1;  // of the split-K scratch, and of its second copy
   size_t lora_part_floats;
@@ -154,6 +156,8 @@ bool make_layout(const mebp_config* c, int B, int T, Layout* L, bool w16 = true)
   L->lm_chunk = V ? lm_chunk_cols(N, (int)V) : 0;
   const size_t Vc = L->lm_chunk;
   L->lm_splits = V ? lm_head_splits((int)N, (int)d, (int)Vc) : 0;
+  L->lm_last_splits = V && V % Vc ? lm_head_splits((int)N, (int)d, (int)(V % Vc)) : L->lm_splits;
+  L->lm_planes = std::max(L->lm_splits, L->lm_last_splits);
   L->ntiles = V ? gemm_logit_stat_tiles((int)Vc) : 0;
   size_t sz[S_COUNT] = {};
   sz[S_A] = N * d * 2;
@@ -190,7 +194,7 @@ bool make_layout(const mebp_config* c, int B, int T, Layout* L, bool w16 = true)
   sz[S_TGTLOGIT] = V ? N * 4 : 0;
   sz[S_ROWLOSS] = V ? N * 4 : 0;
   sz[S_DHF] = V ? N * d * 4 : 0;
-  sz[S_LMPART] = (size_t)L->lm_splits * N * d * 4;
+  sz[S_LMPART] = (size_t)L->lm_planes * N * d * 4;
   sz[S_GRAD] = N * d * 4;
   sz[S_CEMAX] = V ? N * 4 : 0;
   sz[S_CESUM] = V ? N * 4 : 0;
@@ -965,7 +969,8 @@ int lm_head(const Ctx& x, const mebp_q4* emb, const float* norm_final, const flo
       t.M = N; t.Kout = d; t.nseg = 1; t.r = 0;
       t.seg[0].G = (const bf16*)logits; t.seg[0].ldg = Vc;
       t.seg[0].q4 = eq4; t.seg[0].scale = esc; t.seg[0].N = w;
-      t.out = part; t.ldo = d; t.splits = lm_head_splits(N, d, w);
+      t.out = part; t.ldo = d; t.splits = w == Vc ? x.L.lm_splits : x.L.lm_last_splits;
+      t.part_floats = (size_t)x.L.lm_planes * N * d;
       uint16_t* wf = slot<uint16_t>(x.ws, x.L, S_W16);
       FragArgs f{};
       f.seg[f.nseg++] = FragSeg{eq4, esc, w, d, wf, 0};

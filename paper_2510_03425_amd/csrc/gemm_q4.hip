@@ -999,6 +999,7 @@ hipError_t launch_gemm_tn(const TnArgs& a0, int epi, int amode, hipStream_t st, 
   int S;
   if (epi == TN_PARTIAL_F32) {
     S = a.splits;
+    if (S < 1 || a.part_floats < (size_t)S * a.M * a.ldo) return hipErrorInvalidValue;
   } else {
     S = a.w16 ? gemm_tn_frag_splits(a.M, a.Kout, Ns, a.nseg, kMaxSplits, tn_followup(a, epi)) : plan.splits;
     if (S > 1 && (!a.part || a.part_floats < gemm_part_floats(a.M, a.Kout, S))) S = 1;

@@ -133,7 +133,8 @@ struct TnArgs {
   const f16* delta_o;
   float* delta;
   int delta_T, delta_dh;
-  // split-K scratch for the stored epilogues (unused with one split)
+  // split-K scratch for the stored epilogues (unused with one split); TN_PARTIAL_F32: the floats
+  // that `out` has room for, which a launch of more planes is refused beyond
   float* part;
   size_t part_floats;
   // TN_STORE_F32 follow-up: out2 = resid2 + rmsnorm_bwd(norm_x, norm_w, v), plus a bf16 copy
