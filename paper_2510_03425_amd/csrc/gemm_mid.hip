@@ -46,16 +46,28 @@ DEV f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
                                                    0, 0);
 }
 
-// v (8 fp32) -> bf16 hi and lo parts with v ~ hi + lo
-DEV void split_bf16(const float (&v)[8], uint4& hi, uint4& lo) {
-  float h[8], l[8];
+// v (8 fp32) in three bf16 parts, v = p[0] + p[1] + p[2] up to 2^-24: each part is the rounding of
+// what the ones before leave
+struct Split3 {
+  uint4 p[3];
+};
+DEV Split3 split3_bf16(const float (&v)[8]) {
+  float x[8];
+  Split3 s;
 #pragma unroll
-  for (int e = 0; e < 8; ++e) {
-    h[e] = (float)(bf16)v[e];
-    l[e] = v[e] - h[e];
+  for (int e = 0; e < 8; ++e) x[e] = v[e];
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    float h[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      h[e] = (float)(bf16)x[e];
+      x[e] -= h[e];
+    }
+    s.p[q] = make_uint4(pack_bf16x2(h[0], h[1]), pack_bf16x2(h[2], h[3]), pack_bf16x2(h[4], h[5]),
+                        pack_bf16x2(h[6], h[7]));
   }
-  hi = make_uint4(pack_bf16x2(h[0], h[1]), pack_bf16x2(h[2], h[3]), pack_bf16x2(h[4], h[5]), pack_bf16x2(h[6], h[7]));
-  lo = make_uint4(pack_bf16x2(l[0], l[1]), pack_bf16x2(l[2], l[3]), pack_bf16x2(l[4], l[5]), pack_bf16x2(l[6], l[7]));
+  return s;
 }
 
 // 8 int4 codes of a dword times scale into fp16 pairs (k0,k1),(k2,k3),(k4,k5),(k6,k7): the
@@ -89,24 +101,32 @@ DEV void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
-// One accumulator's LoRA term: acc[i][j] += s * U[m][:r] . V_j(lane)[:r] on three bf16 MFMAs
-// (hi*hi + hi*lo + lo*hi); u: 8 values of row 32 i + lane % 32, v: of column lane % 32 of block
-// j, both for the ranks 8 (lane / 32) .. + 8 (zero past r).
+// c += u v^T of fp32 factors: the six products of parts that reach 2^-24 of the result, the
+// smallest first; `two`: the three of two parts (2^-17: 4e-6 of the term instead of 1e-7)
+DEV f32x16 mfma32_f32(const Split3& u, const Split3& v, f32x16 c, bool two) {
+  if (!two) {
+    c = mfma32<OpBF16>(u.p[2], v.p[0], c);
+    c = mfma32<OpBF16>(u.p[1], v.p[1], c);
+    c = mfma32<OpBF16>(u.p[0], v.p[2], c);
+  }
+  c = mfma32<OpBF16>(u.p[1], v.p[0], c);
+  c = mfma32<OpBF16>(u.p[0], v.p[1], c);
+  return mfma32<OpBF16>(u.p[0], v.p[0], c);
+}
+
+// One accumulator's LoRA term: acc[i][j] += s * U[m][:r] . V_j(lane)[:r]; u: 8 values of row
+// 32 i + lane % 32, v: of column lane % 32 of block j, both for the ranks 8 (lane / 32) .. + 8
+// (zero past r).
 template <int MI, int NJ>
-DEV void lora_acc(f32x16 (&acc)[MI][NJ], const float (&u)[MI][8], const float (&v)[NJ][8]) {
-  uint4 bh[NJ], bl[NJ];
+DEV void lora_acc(f32x16 (&acc)[MI][NJ], const float (&u)[MI][8], const float (&v)[NJ][8], bool two) {
+  Split3 b[NJ];
 #pragma unroll
-  for (int j = 0; j < NJ; ++j) split_bf16(v[j], bh[j], bl[j]);
+  for (int j = 0; j < NJ; ++j) b[j] = split3_bf16(v[j]);
 #pragma unroll
   for (int i = 0; i < MI; ++i) {
-    uint4 ah, al;
-    split_bf16(u[i], ah, al);
+    const Split3 a = split3_bf16(u[i]);
 #pragma unroll
-    for (int j = 0; j < NJ; ++j) {
-      acc[i][j] = mfma32<OpBF16>(ah, bh[j], acc[i][j]);
-      acc[i][j] = mfma32<OpBF16>(ah, bl[j], acc[i][j]);
-      acc[i][j] = mfma32<OpBF16>(al, bh[j], acc[i][j]);
-    }
+    for (int j = 0; j < NJ; ++j) acc[i][j] = mfma32_f32(a, b[j], acc[i][j], two);
   }
 }
 
@@ -353,26 +373,17 @@ __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_nt_mid(const NtArgs a)
       for (int i = 0; i < MI; ++i)
         load8(rU0, (uint32_t)(((m0 + 32 * i + l32) * r + q0) * 4), keep, a.lora_s, u[i]);
       if constexpr (EPI != MID_GATED) {
-        lora_acc<MI, NJ>(acc, u, v);
+        lora_acc<MI, NJ>(acc, u, v, a.lora_two);
       } else {
         // gate and up have their own u
         const rsrc_t rU1 = make_rsrc(a.seg[1].lora_u, lora1 ? (size_t)a.M * r * 4 : 0);
-        uint4 bh[NJ], bl[NJ];
-#pragma unroll
-        for (int j = 0; j < NJ; ++j) split_bf16(v[j], bh[j], bl[j]);
+        const Split3 b0 = split3_bf16(v[0]), b1 = split3_bf16(v[1]);
 #pragma unroll
         for (int i = 0; i < MI; ++i) {
           float u1[8];
           load8(rU1, (uint32_t)(((m0 + 32 * i + l32) * r + q0) * 4), keep, a.lora_s, u1);
-          uint4 ah, al;
-          split_bf16(u[i], ah, al);
-          acc[i][0] = mfma32<OpBF16>(ah, bh[0], acc[i][0]);
-          acc[i][0] = mfma32<OpBF16>(ah, bl[0], acc[i][0]);
-          acc[i][0] = mfma32<OpBF16>(al, bh[0], acc[i][0]);
-          split_bf16(u1, ah, al);
-          acc[i][1] = mfma32<OpBF16>(ah, bh[1], acc[i][1]);
-          acc[i][1] = mfma32<OpBF16>(ah, bl[1], acc[i][1]);
-          acc[i][1] = mfma32<OpBF16>(al, bh[1], acc[i][1]);
+          acc[i][0] = mfma32_f32(split3_bf16(u[i]), b0, acc[i][0], a.lora_two);
+          acc[i][1] = mfma32_f32(split3_bf16(u1), b1, acc[i][1], a.lora_two);
         }
       }
     }
@@ -778,7 +789,7 @@ __global__ __launch_bounds__(64 * WN * WK, MI > 4 ? 1 : 2) void k_gemm_tn_frag(c
         }
 #pragma unroll
         for (int i = 0; i < MI; ++i) load8(rU, (uint32_t)(((m0 + 32 * i + l32) * r + q0) * 4), keep, 1.f, u[i]);
-        lora_acc<MI, NJ>(acc, u, v);
+        lora_acc<MI, NJ>(acc, u, v, a.lora_two);
       }
     }
     wait_vmcnt<0>();
@@ -1017,6 +1028,17 @@ MidPlan mid_plan(const MidCfg* cfgs, int n, int M, int ksteps, int unit, int max
   return best;
 }
 
+// Whether a product's LoRA terms take two bf16 parts of each factor instead of three. They have fp32
+// bits wherever the sums of split planes or the 128 x 128 kernels give them those (in fp32
+// instructions); from 160 tiles of 256 x 128 and 1024 tokens on, where the large tiles multiply two
+// parts, a third would cost 1 .. 1.5 % of a layer (4 x 1024 tokens of 1536 forward: 564 -> 572 us,
+// 8 x 2048 of 2560: 3473 -> 3518) below the fp16 and bf16 roundings of the product beside it.
+bool mid_lora_two(int M, const int* Ns, int nseg) {
+  long long t = 0;
+  for (int s = 0; s < nseg; ++s) t += (Ns[s] + 127) / 128;
+  return M >= 1024 && t * ((M + 255) / 256) >= 160;
+}
+
 MidPlan mid_plan_nt(int M, const int* Ns, int nseg, int K, bool gated, bool logits, bool followup) {
   int width = 0;
   for (int s = 0; s < nseg; ++s) width += Ns[s];
@@ -1079,6 +1101,7 @@ hipError_t launch_gemm_nt_mid(const NtArgs& a0, int epi, int S, double flops, do
     p = mid_plan(kMidNt, logits ? 1 : (int)(sizeof(kMidNt) / sizeof(MidCfg)), a.M, a.K / BK, 2, 1, width, true,
                  [&](const MidCfg& c) { return mid_columns(c, Ns, a.nseg, gated); });
   }
+  a.lora_two = mid_lora_two(a.M, Ns, a.nseg);
   const MidCfg& c = kMidNt[p.cfg];
   int t = 0;
   for (int s = 0; s < a.nseg; ++s) {
@@ -1132,6 +1155,7 @@ hipError_t launch_gemm_tn_frag(const TnArgs& a, int epi, int S, double flops, do
   const MidCfg& c = kMidTn[p.cfg];
   const int e = S > 1 ? TN_PARTIAL_F32 : epi;
   TnArgs b = a;
+  b.lora_two = mid_lora_two(a.M, &a.Kout, 1);
   if (S > 1 && epi != TN_PARTIAL_F32) {
     b.out = a.part;
     b.ldo = a.Kout;

@@ -40,6 +40,7 @@ struct NtArgs {
   NtSeg seg[3];
   float lora_s;
   int r;
+  int lora_two;           // set by launch_gemm_nt_mid: LoRA factors in two bf16 parts, not three
   // NT_LOGITS: per (row, 64-column tile) the maximum and the sum of exp(logit - max) into
   // `stats` [M][ntiles] float2 (ntiles = row pitch), the logits minus their tile's maximum
   // as fp16 into seg[0].out, and the fp32 logit of the target into tgt_logit[m] (target ids
@@ -118,6 +119,7 @@ struct TnArgs {
   int nseg;
   TnSeg seg[3];
   int r;
+  int lora_two;            // set by launch_gemm_tn_frag: LoRA factors in two bf16 parts, not three
   float* out;              // fp32 [M][ldo] (TN_STORE_F32); partials [splits][M][ldo]
   bf16* outb;              // bf16 [M][ldo] (TN_STORE_BF16)
   int ldo;
