@@ -1079,6 +1079,12 @@ hipError_t launch_frag_weights(FragArgs a, hipStream_t st) {
 
 bool gemm_nt_mid_ok(int K) { return K % BK == 0; }
 
+bool gemm_nt_mid_aligned(const NtArgs& a) {
+  bool ok = true;
+  for (int s = 0; s < a.nseg; ++s) ok = ok && ((uintptr_t)a.seg[s].scale & 3) == 0;
+  return ok;
+}
+
 int gemm_nt_mid_splits(int M, const int* Ns, int nseg, int K, bool gated, bool followup) {
   return mid_plan_nt(M, Ns, nseg, K, gated, false, followup).splits;
 }
@@ -1089,7 +1095,7 @@ int gemm_tn_frag_splits(int M, int Kout, const int* Ns, int nseg, int max_s, boo
 
 hipError_t launch_gemm_nt_mid(const NtArgs& a0, int epi, int S, double flops, double bytes, hipStream_t st) {
   NtArgs a = a0;
-  if (a.K % BK || a.lda % 8 || ((uintptr_t)a.X & 15)) return hipErrorInvalidValue;
+  if (a.K % BK || a.lda % 8 || ((uintptr_t)a.X & 15) || !gemm_nt_mid_aligned(a)) return hipErrorInvalidValue;
   int Ns[3];
   for (int s = 0; s < a.nseg; ++s) Ns[s] = a.seg[s].N;
   const bool logits = epi == NT_LOGITS, gated = a.gated && S == 1;

@@ -851,7 +851,6 @@ int gemm_splits(int tiles, int ktiles) {
 size_t gemm_part_floats(int M, int ncols, int splits) { return splits > 1 ? (size_t)splits * M * ncols : 0; }
 
 GemmPlan plan_nt(int M, const int* Ns, int nseg, int K, int epi) {
-  if (gemm_nt_mid_ok(K)) return GemmPlan{0, 0, 1};
   int t256 = 0, t128 = 0;
   for (int s = 0; s < nseg; ++s) {
     t256 += (Ns[s] + 255) / 256;
@@ -897,7 +896,7 @@ hipError_t launch_gemm_nt(const NtArgs& a0, int epi, hipStream_t st, hipEvent_t 
   int Ns[3];
   for (int s = 0; s < a.nseg; ++s) Ns[s] = a.seg[s].N;
   const GemmPlan plan = plan_nt(a.M, Ns, a.nseg, a.K, epi);
-  const bool mid = gemm_nt_mid_ok(a.K);
+  const bool mid = gemm_nt_mid_ok(a.K) && gemm_nt_mid_aligned(a);
   int S = !mid ? plan.splits : epi == NT_LOGITS ? 1 : gemm_nt_mid_splits(a.M, Ns, a.nseg, a.K, a.gated, a.norm_w);
   if (S > 1 && (!a.part || a.part_floats < gemm_part_floats(a.M, ncat, S))) S = 1;
   if (a.norm_w && a.seg[0].N > 4096) S = 1;  // the fused row norm keeps a row in one workgroup
@@ -919,7 +918,7 @@ hipError_t launch_gemm_nt(const NtArgs& a0, int epi, hipStream_t st, hipEvent_t 
         return launch_rmsnorm_fwd((const float*)a.seg[0].out, a.norm_w, a.M, a.seg[0].N, a.eps, a.norm_out, nullptr, st);
       return hipSuccess;
     }
-  } else   if (plan.big) {
+  } else if (plan.big) {
     fused_act = nt_gated_fused(a, epi, plan.bn, S);
     hipError_t eb = launch_gemm_nt_big(a, epi, plan.bn, S, flops, bytes, st);
     if (eb != hipSuccess) return eb;

@@ -89,6 +89,9 @@ hipError_t launch_gemm_nt_big(const NtArgs& a, int epi, int bn, int S, double fl
 // the products of gemm_mid.hip (reductions that are a multiple of 64): one launch with every
 // epilogue of the arguments fused except the row norm
 bool gemm_nt_mid_ok(int K);
+// ... whose scales are 4-byte aligned: they are loaded 16 bytes at a time, which a buffer load takes
+// from any dword; others go to the kernels that load them one by one
+bool gemm_nt_mid_aligned(const NtArgs& a);
 hipError_t launch_gemm_nt_mid(const NtArgs& a, int epi, int S, double flops, double bytes, hipStream_t st);
 // planes that the reduction of such a product is split into (followup: its finalize kernel
 // replaces a row-norm launch)
