@@ -91,6 +91,9 @@ std::atomic<int> g_guards{[] {
 constexpr size_t kGuardBytes = 256;
 constexpr int kMaxGuards = 2 * S_COUNT;
 
+// A layer's weights as fragments: none, one product's at a time, or all at once.
+enum Frag { FRAG_NONE = 0, FRAG_EACH, FRAG_LAYER };
+
 struct Layout {
   size_t off[S_COUNT];
   size_t off1[S_COUNT];  // second copy of the per-set slots (equal to off[] for the others)
@@ -108,29 +111,51 @@ struct Layout {
   int ntiles;     // statistics tiles of a whole chunk (the stats row pitch)
   size_t split_floats, split_floats1;  // of the split-K scratch, and of its second copy
   size_t lora_part_floats;
-  // bf16 weights of the transposed products in fragment order: a layer's seven matrices, or one
-  // vocabulary chunk's; 0: left out (the products then decompress the int4 weights themselves)
-  size_t w16_elems;
+  // whether the transposed products of a layer, and the LM head's, read a bf16 copy of their
+  // weights in fragment order (else they decompress the int4 weights themselves), and the slot of
+  // a layer's copy
+  Frag frag;
+  bool lm_frag;
+  int frag_slot;
 };
 
-// Split planes of a forward product: gated (gate, up) and q | k | v have no row-norm follow-up,
-// the others may have one or not; of a transposed product: all but the activation backward have
-// one (see gemm_nt_mid_splits and gemm_tn_frag_splits).
-size_t nt_part(int M, int K, std::initializer_list<int> Ns, bool gated = false) {
+// Split planes of a forward product on the kernels of gemm_mid.hip (where the reduction is one of
+// theirs): gated (gate, up) and q | k | v have no row-norm follow-up, the others may have one or not;
+// of a transposed product on fragments: all but the activation backward have one (see
+// gemm_nt_mid_splits and gemm_tn_frag_splits). The *_q4 figures are those of the other kernels.
+struct PlaneFloats {
+  size_t nt, nt_q4, tn, tn_q4;
+};
+void add_nt(PlaneFloats* p, int M, int K, std::initializer_list<int> Ns, bool gated = false) {
   int v[3], n = 0, ncat = 0;
   for (int x : Ns) {
     v[n++] = x;
     ncat += x;
   }
-  if (!gemm_nt_mid_ok(K)) return gemm_part_floats(M, ncat, plan_nt(M, v, n, K, NT_STORE_F32).splits);
-  const int s0 = gemm_nt_mid_splits(M, v, n, K, gated, false), s1 = n > 1 ? s0 : gemm_nt_mid_splits(M, v, n, K, false, true);
-  return gemm_part_floats(M, ncat, s0 > s1 ? s0 : s1);
+  const size_t q4 = gemm_part_floats(M, ncat, plan_nt(M, v, n, K, NT_STORE_F32).splits);
+  p->nt_q4 = std::max(p->nt_q4, q4);
+  size_t m = q4;
+  if (gemm_nt_mid_ok(K)) {
+    const int s0 = gemm_nt_mid_splits(M, v, n, K, gated, false), s1 = n > 1 ? s0 : gemm_nt_mid_splits(M, v, n, K, false, true);
+    m = gemm_part_floats(M, ncat, std::max(s0, s1));
+  }
+  p->nt = std::max(p->nt, m);
 }
-size_t tn_part(int M, int Kout, std::initializer_list<int> Ns, bool followup, bool w16) {
+void add_tn(PlaneFloats* p, int M, int Kout, std::initializer_list<int> Ns, bool followup) {
   int v[3], n = 0;
   for (int x : Ns) v[n++] = x;
-  return gemm_part_floats(M, Kout, w16 ? gemm_tn_frag_splits(M, Kout, v, n, kMaxSplits, followup)
-                                       : plan_tn(M, Kout, v, n, false).splits);
+  p->tn = std::max(p->tn, gemm_part_floats(M, Kout, gemm_tn_frag_splits(M, Kout, v, n, kMaxSplits, followup)));
+  p->tn_q4 = std::max(p->tn_q4, gemm_part_floats(M, Kout, plan_tn(M, Kout, v, n, false).splits));
+}
+// elements of the 16-bit weights of a product that runs on the large tiles (0 if it does not)
+size_t large_tile_elems(int M, int Kout, std::initializer_list<int> Ns, bool softmax) {
+  int v[3], n = 0;
+  size_t e = 0;
+  for (int x : Ns) {
+    v[n++] = x;
+    e += (size_t)x * Kout;
+  }
+  return plan_tn(M, Kout, v, n, softmax).big ? e : 0;
 }
 
 // Columns of one LM-head vocabulary chunk: the chunk's fp16 logits [N][chunk] take at most
@@ -147,17 +172,51 @@ int lm_chunk_cols(size_t N, int V) {
   return c >= (size_t)V ? V : (int)c;
 }
 
-int lm_head_splits(int N, int d, int V) { return gemm_tn_frag_splits(N, d, &V, 1, kMaxHeadSplits, true); }
+// planes of the dH product over V columns on the kernels that decompress int4 weights
+int lm_q4_splits(int N, int d, int V) {
+  // token tiles are 256 rows in the large-tile kernel, 128 in the other
+  const int bm = plan_tn(N, d, &V, 1, true).big ? 256 : 128;
+  const int tiles = ((d + 127) / 128) * ((N + bm - 1) / bm);
+  return std::max(1, std::min({(512 + tiles - 1) / tiles, ((V + 63) / 64 + 7) / 8, kMaxHeadSplits}));
+}
 
-bool make_layout(const mebp_config* c, int B, int T, Layout* L, bool w16 = true) {
+// What a layout chooses: weights as fragments or not (see Layout) and the scratch that goes with it.
+struct Route {
+  Frag frag;
+  bool lm_frag;
+  size_t split, split1;  // floats of the split-K scratch and of its second copy
+  int lm_splits, lm_last;
+  int planes() const { return std::max(lm_splits, lm_last); }
+};
+
+bool lm_slot(int s) {
+  switch (s) {
+    case S_HF: case S_LOGITS: case S_STATS: case S_LSEV: case S_TGTLOGIT: case S_ROWLOSS: case S_DHF: case S_LMPART:
+    case S_CEMAX: case S_CESUM: case S_CEALPHA:
+      return true;
+    default:
+      return false;
+  }
+}
+
+// static_call: the layout of mebp_layer_recompute_backward_static (the layer's slots alone, one copy
+// of each), on the route that the workspace call takes.
+//
+// Route: the bf16 fragments make the backward faster and cost memory, which the method is there to
+// save. They are used where the workspace gets no larger for them than the products that decompress
+// int4 weights make it, with their split planes and, where they run on large tiles, a 16-bit copy of
+// the largest product's weights. Their planes are fewer, which pays for a layer's fragments at a few
+// hundred tokens (0.5B shape, 256 tokens: 30 MB of fragments, 24 MB fewer planes); where the LM head
+// itself has none, a layer's lie in its logits, which are idle then. Where a layer's have no room,
+// one product's at a time may (three launches more). A layer that the static call takes is on the
+// same route there, so one whose fragments its buffer has no room for uses none.
+bool make_layout(const mebp_config* c, int B, int T, Layout* L, bool static_call = false) {
   const size_t N = (size_t)B * T, d = c->hidden, qd = (size_t)c->n_heads * c->head_dim,
                kvd = (size_t)c->n_kv_heads * c->head_dim, F = c->ffn, r = c->lora_rank > 0 ? c->lora_rank : 16,
                V = c->vocab, H = c->n_heads;
+  const int M = (int)N, D = (int)d, Q = (int)qd, KV = (int)kvd, FF = (int)F, R = (int)r;
   L->lm_chunk = V ? lm_chunk_cols(N, (int)V) : 0;
   const size_t Vc = L->lm_chunk;
-  L->lm_splits = V ? lm_head_splits((int)N, (int)d, (int)Vc) : 0;
-  L->lm_last_splits = V && V % Vc ? lm_head_splits((int)N, (int)d, (int)(V % Vc)) : L->lm_splits;
-  L->lm_planes = std::max(L->lm_splits, L->lm_last_splits);
   L->ntiles = V ? gemm_logit_stat_tiles((int)Vc) : 0;
   size_t sz[S_COUNT] = {};
   sz[S_A] = N * d * 2;
@@ -188,13 +247,11 @@ bool make_layout(const mebp_config* c, int B, int T, Layout* L, bool w16 = true)
   sz[S_ROPE_L] = (size_t)T * c->head_dim * 4;
   sz[S_TGT] = N * 4;
   sz[S_HF] = V ? N * d * 2 : 0;
-  sz[S_LOGITS] = N * Vc * 2;
   sz[S_STATS] = N * (size_t)L->ntiles * 8;
   sz[S_LSEV] = V ? N * 4 : 0;
   sz[S_TGTLOGIT] = V ? N * 4 : 0;
   sz[S_ROWLOSS] = V ? N * 4 : 0;
   sz[S_DHF] = V ? N * d * 4 : 0;
-  sz[S_LMPART] = (size_t)L->lm_planes * N * d * 4;
   sz[S_GRAD] = N * d * 4;
   sz[S_CEMAX] = V ? N * 4 : 0;
   sz[S_CESUM] = V ? N * 4 : 0;
@@ -206,48 +263,128 @@ bool make_layout(const mebp_config* c, int B, int T, Layout* L, bool w16 = true)
   sz[S_TD] = sw ? N * d * 4 : 0;
   sz[S_DTB] = sw ? N * d * 2 : 0;
   sz[S_DTOB] = sw ? N * d * 2 : 0;
-  {
-    const int M = (int)N, D = (int)d, Q = (int)qd, KV = (int)kvd, FF = (int)F, R = (int)r;
-    size_t m = 0;
-    auto mx = [&](size_t v) { m = v > m ? v : m; };
-    mx(nt_part(M, D, {Q, KV, KV}));
-    mx(nt_part(M, Q, {D}));
-    mx(nt_part(M, D, {FF, FF}, true));
-    mx(nt_part(M, FF, {D}));
-    // attention scratch for the sliding-window layers and the global ones
-    mx(attn_plan(B, T, c->n_heads, c->n_kv_heads, c->head_dim, c->window).fwd_floats);
-    mx(attn_plan(B, T, c->n_heads, c->n_kv_heads, c->head_dim, 0).fwd_floats);
-    // (the second copy serves a recompute: forward products and attention only)
-    L->split_floats1 = m;
-    mx(attn_part_floats(B, T, c->n_heads, c->n_kv_heads, c->head_dim, c->window));
-    mx(attn_part_floats(B, T, c->n_heads, c->n_kv_heads, c->head_dim, 0));
-    mx(tn_part(M, FF, {D}, false, w16));
-    mx(tn_part(M, D, {FF, FF}, true, w16));
-    mx(tn_part(M, Q, {D}, true, w16));
-    mx(tn_part(M, D, {Q, KV, KV}, true, w16));
-    L->split_floats = m;
-    sz[S_SPLIT] = m * 4;
-    // the dB and dA launch of each stage of a layer, for any of its projections adapted
-    size_t lp = 0;
-    for (uint32_t mask = 1; mask < 8; ++mask) {
-      const int out[3] = {Q, KV, KV};
-      int cols = 0;
-      for (int p = 0; p < 3; ++p)
-        if (mask >> p & 1) cols += out[p] + D;
-      for (int v : {cols, mask & 1 ? FF + D : 0, mask == 3 ? 2 * (FF + D) : 0, Q + D})
-        if (v) lp = std::max(lp, lora_outer_part_floats(M, v, R));
-    }
-    L->lora_part_floats = lp;
-    sz[S_PART] = lp * 4;
-    size_t w = 0;
-    if (w16) {
-      w = frag_elems(D, FF) + 2 * frag_elems(FF, D) + frag_elems(D, Q) + frag_elems(Q, D) + 2 * frag_elems(KV, D);
-      const size_t lm = V ? frag_elems((int)Vc, D) : 0;
-      w = lm > w ? lm : w;
-    }
-    L->w16_elems = w;
-    sz[S_W16] = w * 2;
+  // the dB and dA launch of each stage of a layer, for any of its projections adapted
+  size_t lp = 0;
+  for (uint32_t mask = 1; mask < 8; ++mask) {
+    const int out[3] = {Q, KV, KV};
+    int cols = 0;
+    for (int p = 0; p < 3; ++p)
+      if (mask >> p & 1) cols += out[p] + D;
+    for (int v : {cols, mask & 1 ? FF + D : 0, mask == 3 ? 2 * (FF + D) : 0, Q + D})
+      if (v) lp = std::max(lp, lora_outer_part_floats(M, v, R));
   }
+  size_t most_lp = 0;
+  for (size_t v : {lora_outer_group_floats(M, std::max(Q, KV), R, 3), lora_outer_group_floats(M, D, R, 3),
+                   lora_outer_group_floats(M, Q, R, 1), lora_outer_group_floats(M, FF, R, 2)})
+    most_lp = std::max(most_lp, v);
+  lp = std::min(lp, most_lp);
+  L->lora_part_floats = lp;
+  sz[S_PART] = lp * 4;
+
+  // split planes of a layer's products, and the attention scratch of the sliding-window layers and
+  // the global ones
+  PlaneFloats pl{};
+  add_nt(&pl, M, D, {Q, KV, KV});
+  add_nt(&pl, M, Q, {D});
+  add_nt(&pl, M, D, {FF, FF}, true);
+  add_nt(&pl, M, FF, {D});
+  add_tn(&pl, M, FF, {D}, false);
+  add_tn(&pl, M, D, {FF, FF}, true);
+  add_tn(&pl, M, Q, {D}, true);
+  add_tn(&pl, M, D, {Q, KV, KV}, true);
+  size_t attn = 0, attn_fwd = 0;
+  for (int w : {c->window, 0}) {
+    attn_fwd = std::max(attn_fwd, attn_plan(B, T, c->n_heads, c->n_kv_heads, c->head_dim, w).fwd_floats);
+    attn = std::max(attn, attn_part_floats(B, T, c->n_heads, c->n_kv_heads, c->head_dim, w));
+  }
+  const size_t q4_split = std::max({pl.nt_q4, pl.tn_q4, attn});
+
+  // fragments of a layer and of a vocabulary chunk; a product's are one buffer resource, below 4 GiB
+  const size_t gu = 2 * frag_elems(FF, D), qkv = frag_elems(Q, D) + 2 * frag_elems(KV, D),
+               elems[3] = {0, std::max({gu, qkv, frag_elems(D, FF), frag_elems(D, Q)}),
+                           frag_elems(D, FF) + gu + frag_elems(D, Q) + qkv},
+               lm_elems = V ? frag_elems((int)Vc, D) : 0, most = 0xffffffffu / 2;
+  const bool can = elems[FRAG_EACH] <= most;
+  const int Vl = V ? (int)(V % Vc ? V % Vc : Vc) : 0;
+  const bool lm_can = V && lm_elems <= most && large_tile_elems(M, D, {(int)Vc}, true);
+
+  // bytes of the route's own slots, and of a whole layout (without guards)
+  auto set_route = [&](const Route& k, bool lm) {
+    sz[S_LOGITS] = !lm ? 0 : std::max(N * Vc * 2, k.lm_frag ? 0 : elems[k.frag] * 2);
+    sz[S_LMPART] = lm ? (size_t)k.planes() * N * d * 4 : 0;
+    sz[S_SPLIT] = k.split * 4;
+    sz[S_W16] = 2 * (!lm ? elems[k.frag] : k.lm_frag ? std::max(lm_elems, elems[k.frag]) : 0);
+  };
+  auto pad = [](size_t n) { return (n + 255) & ~(size_t)255; };
+  auto total = [&](const Route& k, bool lm, bool two_sets) {
+    set_route(k, lm);
+    size_t t = 0;
+    for (int i = 0; i < S_COUNT; ++i) {
+      if (!lm && lm_slot(i)) continue;
+      t += pad(sz[i]);
+      if (two_sets && per_set(i)) t += pad(i == S_SPLIT ? k.split1 * 4 : sz[i]);
+    }
+    return t;
+  };
+  auto pick = [&](bool lm, Frag frag_most) {
+    const int q4_lm = lm ? lm_q4_splits(M, D, (int)Vc) : 0, q4_last = lm ? lm_q4_splits(M, D, Vl) : 0;
+    const Route q4{FRAG_NONE, false, q4_split, std::min(q4_split, std::max({pl.nt, pl.nt_q4, attn_fwd})), q4_lm, q4_last};
+    Route full = q4;
+    full.split1 = q4_split;
+    size_t w = std::max({large_tile_elems(M, FF, {D}, false), large_tile_elems(M, D, {FF, FF}, false),
+                         large_tile_elems(M, Q, {D}, false), large_tile_elems(M, D, {Q, KV, KV}, false)});
+    if (lm) w = std::max(w, large_tile_elems(M, D, {(int)Vc}, true));
+    const size_t budget = total(full, lm, true) + pad(2 * w);
+    Route tries[5];
+    for (int i = 0; i < 4; ++i) {
+      Route& k = tries[i] = q4;
+      k.frag = i < 2 ? FRAG_LAYER : FRAG_EACH;
+      k.split = std::max({pl.nt, pl.tn, attn});
+      k.split1 = std::max(pl.nt, attn_fwd);
+      if (i & 1) {  // planes beyond the other kernels' left out
+        k.split = std::min(k.split, q4_split);
+        k.split1 = std::min(k.split1, q4_split);
+      }
+    }
+    tries[4] = q4;
+    for (int i = 0; i < 5; ++i) {
+      if (tries[i].frag > frag_most) continue;
+      Route k = tries[i];
+      if (lm && lm_can) {
+        k.lm_frag = true;
+        auto plan = [&](int most_planes) {
+          const int cols = (int)Vc;
+          k.lm_splits = gemm_tn_frag_splits(M, D, &cols, 1, most_planes, true);
+          k.lm_last = gemm_tn_frag_splits(M, D, &Vl, 1, most_planes, true);
+        };
+        plan(q4_lm);
+        const size_t t = total(k, lm, true), plane = N * d * 4;
+        if (t > budget) continue;
+        // (as many planes more as the budget leaves room for)
+        const size_t cap = k.planes() + (budget - t) / plane;
+        if (cap > (size_t)q4_lm) plan((int)std::min(cap, (size_t)kMaxHeadSplits));
+      }
+      if (total(k, lm, true) <= budget) return k;
+    }
+    return q4;
+  };
+  Route k = pick(V > 0, can ? FRAG_LAYER : FRAG_NONE);
+  const bool in_static = total(V ? pick(false, k.frag) : k, false, true) <= MEBP_STATIC_SCRATCH_BYTES;
+  while (in_static && k.frag && total(k, false, false) > MEBP_STATIC_SCRATCH_BYTES) k = pick(V > 0, (Frag)(k.frag - 1));
+  const bool lm = V && !static_call;
+  set_route(k, lm);
+  if (!lm)
+    for (int i = 0; i < S_COUNT; ++i)
+      if (lm_slot(i)) sz[i] = 0;
+  L->frag = k.frag;
+  L->lm_frag = k.lm_frag;
+  L->frag_slot = lm && !k.lm_frag ? S_LOGITS : S_W16;
+  L->lm_splits = k.lm_splits;
+  L->lm_last_splits = k.lm_last;
+  L->lm_planes = k.planes();
+  L->split_floats = k.split;
+  L->split_floats1 = k.split1;
+
   size_t o = 0;
   L->guards = g_guards.load() != 0;
   L->nguard = 0;
@@ -264,7 +401,7 @@ bool make_layout(const mebp_config* c, int B, int T, Layout* L, bool w16 = true)
     return at;
   };
   for (int i = 0; i < S_COUNT; ++i) L->off[i] = place(i, 0);
-  for (int i = 0; i < S_COUNT; ++i) L->off1[i] = per_set(i) ? place(i, 1) : L->off[i];
+  for (int i = 0; i < S_COUNT; ++i) L->off1[i] = per_set(i) && !static_call ? place(i, 1) : L->off[i];
   L->status_off = o;
   if (L->guards) o += 256;
   L->total = o;
@@ -342,10 +479,10 @@ int guard_verdict(const Layout& L, void* ws, hipStream_t st) {
 // Runs `body` (the launches of one entry point on `stream`) between a fill and a check of
 // the guards when the layout has them; otherwise just runs it.
 template <class F>
-int guarded(const mebp_config* c, int B, int T, void* ws, mebp_stream_t stream, F&& body, bool w16 = true) {
+int guarded(const mebp_config* c, int B, int T, void* ws, mebp_stream_t stream, F&& body, bool static_call = false) {
   if (!g_guards.load()) return body();
   Layout L;
-  make_layout(c, B, T, &L, w16);
+  make_layout(c, B, T, &L, static_call);
   if (!L.guards) return body();
   int e = guard_launch(L, ws, (hipStream_t)stream, true);
   if (e || (e = body())) return e;
@@ -541,21 +678,22 @@ void set_scratch(const Ctx& x, TnArgs& t) {
 
 // The layer's weights in fragment order (one copy: the transposed products run on the context's
 // main stream, one after another), in the order down | gate, up | o | q, k, v: where the product
-// of projection p starts.
+// that starts with projection p finds its own.
 const uint16_t* frag_weights(const Ctx& x, int p) {
-  if (!x.L.w16_elems) return nullptr;
+  if (!x.L.frag) return nullptr;
   static const int order[MEBP_NPROJ] = {MEBP_DOWN, MEBP_GATE, MEBP_UP, MEBP_O, MEBP_Q, MEBP_K, MEBP_V};
-  const uint16_t* w = slot<uint16_t>(x.ws, x.L, S_W16);
-  for (int i = 0; order[i] != p; ++i) w += frag_elems(x.D.out[order[i]], x.D.in[order[i]]);
+  const uint16_t* w = slot<uint16_t>(x.ws, x.L, x.L.frag_slot);
+  for (int i = 0; x.L.frag == FRAG_LAYER && order[i] != p; ++i) w += frag_elems(x.D.out[order[i]], x.D.in[order[i]]);
   return w;
 }
-hipError_t write_frag_weights(const Ctx& x, const mebp_layer_base* base, bool qkv) {
-  if (!x.L.w16_elems) return hipSuccess;
+// writes those of `ps`, which follow one another; `when`: the mode that this call is for
+hipError_t write_frag_weights(const Ctx& x, const mebp_layer_base* base, std::initializer_list<int> ps, Frag when) {
+  if (x.L.frag != when) return hipSuccess;
   FragArgs f{};
-  for (int p : {MEBP_DOWN, MEBP_GATE, MEBP_UP, MEBP_O, MEBP_Q, MEBP_K, MEBP_V}) {
-    if (!qkv && p <= MEBP_V) continue;
-    f.seg[f.nseg++] = FragSeg{base->w[p].q4, base->w[p].scale, x.D.out[p], x.D.in[p],
-                              const_cast<uint16_t*>(frag_weights(x, p)), 0};
+  uint16_t* w = const_cast<uint16_t*>(frag_weights(x, *ps.begin()));
+  for (int p : ps) {
+    f.seg[f.nseg++] = FragSeg{base->w[p].q4, base->w[p].scale, x.D.out[p], x.D.in[p], w, 0};
+    w += frag_elems(x.D.out[p], x.D.in[p]);
   }
   return launch_frag_weights(f, x.st);
 }
@@ -818,7 +956,10 @@ int layer_backward_only(const Ctx& x, int l, const mebp_layer_base* base, const 
   float* da = xs<float>(x, S_DA);
 
   const bool sandwich = c->arch & MEBP_ARCH_SANDWICH;
-  HIP_TRY(write_frag_weights(x, base, dx != nullptr));
+  if (dx)
+    HIP_TRY(write_frag_weights(x, base, {MEBP_DOWN, MEBP_GATE, MEBP_UP, MEBP_O, MEBP_Q, MEBP_K, MEBP_V}, FRAG_LAYER));
+  else
+    HIP_TRY(write_frag_weights(x, base, {MEBP_DOWN, MEBP_GATE, MEBP_UP, MEBP_O}, FRAG_LAYER));
   // y = h + down(z)   (sandwich: y = h + RMSNorm(t), t = down(z): the down projection's
   // gradient is the norm's backward of dy)
   bf16* gdown = dyb;
@@ -835,6 +976,7 @@ int layer_backward_only(const Ctx& x, int l, const mebp_layer_base* base, const 
     TnArgs t{};
     set_scratch(x, t);
     t.M = D.N; t.Kout = D.F; t.nseg = 1; t.r = D.r;
+    HIP_TRY(write_frag_weights(x, base, {MEBP_DOWN}, FRAG_EACH));
     t.w16 = frag_weights(x, MEBP_DOWN);
     t.seg[0] = tn_seg(x, base, lora, MEBP_DOWN, gdown);
     t.g = g; t.u = u; t.ldgu = D.F; t.act = c->act;
@@ -848,6 +990,7 @@ int layer_backward_only(const Ctx& x, int l, const mebp_layer_base* base, const 
     TnArgs t{};
     set_scratch(x, t);
     t.M = D.N; t.Kout = D.d; t.nseg = 2; t.r = D.r;
+    HIP_TRY(write_frag_weights(x, base, {MEBP_GATE, MEBP_UP}, FRAG_EACH));
     t.w16 = frag_weights(x, MEBP_GATE);
     t.seg[0] = tn_seg(x, base, lora, MEBP_GATE, dg);
     t.seg[1] = tn_seg(x, base, lora, MEBP_UP, dup);
@@ -868,6 +1011,7 @@ int layer_backward_only(const Ctx& x, int l, const mebp_layer_base* base, const 
     TnArgs t{};
     set_scratch(x, t);
     t.M = D.N; t.Kout = D.qd; t.nseg = 1; t.r = D.r;
+    HIP_TRY(write_frag_weights(x, base, {MEBP_O}, FRAG_EACH));
     t.w16 = frag_weights(x, MEBP_O);
     t.seg[0] = tn_seg(x, base, lora, MEBP_O, go);
     t.outb = dO; t.ldo = D.qd;
@@ -898,6 +1042,7 @@ int layer_backward_only(const Ctx& x, int l, const mebp_layer_base* base, const 
     TnArgs t{};
     set_scratch(x, t);
     t.M = D.N; t.Kout = D.d; t.nseg = 3; t.r = D.r;
+    HIP_TRY(write_frag_weights(x, base, {MEBP_Q, MEBP_K, MEBP_V}, FRAG_EACH));
     t.w16 = frag_weights(x, MEBP_Q);
     t.seg[0] = tn_seg(x, base, lora, MEBP_Q, dq);
     t.seg[1] = tn_seg(x, base, lora, MEBP_K, dk);
@@ -971,11 +1116,13 @@ int lm_head(const Ctx& x, const mebp_q4* emb, const float* norm_final, const flo
       t.seg[0].q4 = eq4; t.seg[0].scale = esc; t.seg[0].N = w;
       t.out = part; t.ldo = d; t.splits = w == Vc ? x.L.lm_splits : x.L.lm_last_splits;
       t.part_floats = (size_t)x.L.lm_planes * N * d;
-      uint16_t* wf = slot<uint16_t>(x.ws, x.L, S_W16);
-      FragArgs f{};
-      f.seg[f.nseg++] = FragSeg{eq4, esc, w, d, wf, 0};
-      HIP_TRY(launch_frag_weights(f, x.st));
-      t.w16 = wf;
+      if (x.L.lm_frag) {
+        uint16_t* wf = slot<uint16_t>(x.ws, x.L, S_W16);
+        FragArgs f{};
+        f.seg[f.nseg++] = FragSeg{eq4, esc, w, d, wf, 0};
+        HIP_TRY(launch_frag_weights(f, x.st));
+        t.w16 = wf;
+      }
       HIP_TRY(launch_gemm_tn(t, TN_PARTIAL_F32, TN_A_BF16, x.st));
       HIP_TRY(launch_ce_dh_accum(part, t.splits, N, d, alpha, first, dhf, x.st));
     }
@@ -986,14 +1133,14 @@ int lm_head(const Ctx& x, const mebp_q4* emb, const float* norm_final, const flo
   return MEBP_OK;
 }
 
-Ctx make_ctx(const mebp_config* c, int B, int T, void* ws, mebp_stream_t stream, bool w16 = true) {
+Ctx make_ctx(const mebp_config* c, int B, int T, void* ws, mebp_stream_t stream, bool static_call = false) {
   Ctx x;
   x.c = c;
   x.D = dims(c, B, T);
   x.B = B;
   x.T = T;
   x.ws = ws;
-  make_layout(c, B, T, &x.L, w16);
+  make_layout(c, B, T, &x.L, static_call);
   x.st = (hipStream_t)stream;
   x.set = 0;
   x.split_set = 0;
@@ -1380,29 +1527,27 @@ int mebp_layer_recompute_backward_static(const mebp_config* cfg, int32_t layer, 
     return e;
   if (dx && !aligned(dx, 16)) return fail(MEBP_EINVAL, "dx not 16-byte aligned");
   if (dx && dx == x_ckpt) return fail(MEBP_EINVAL, "dx must not alias x_ckpt");
-  // the layer's own slots only: the LM head's are not part of this call
+  // it fits if the workspace of its own slots does (the LM head's are not part of this call)
   mebp_config c0 = *cfg;
   c0.vocab = 0;
-  // (without the fragment-ordered weights where the layer fits only then)
   Layout L;
-  make_layout(&c0, B, T, &L);
-  const bool w16 = L.total <= MEBP_STATIC_SCRATCH_BYTES;
-  if (!w16) make_layout(&c0, B, T, &L, false);
-  if (L.total > MEBP_STATIC_SCRATCH_BYTES)
-    return fail(MEBP_EWORKSPACE, "layer needs %zu bytes of scratch, more than the %zu the library holds", L.total,
+  make_layout(cfg, B, T, &L, true);
+  const size_t need = std::max(L.total, mebp_workspace_bytes(&c0, B, T));
+  if (need > MEBP_STATIC_SCRATCH_BYTES)
+    return fail(MEBP_EWORKSPACE, "layer needs %zu bytes of scratch, more than the %zu the library holds", need,
                 (size_t)MEBP_STATIC_SCRATCH_BYTES);
   void* ws = static_scratch();
   if (!ws) return MEBP_EHIP;
   return guarded(
-      &c0, B, T, ws, stream,
+      cfg, B, T, ws, stream,
       [&] {
-        Ctx x = make_ctx(&c0, B, T, ws, stream, w16);
+        Ctx x = make_ctx(cfg, B, T, ws, stream, true);
         float* rope;
         int e2;
         if ((e2 = rope_table(x, layer, &rope))) return e2;
         return layer_backward(x, layer, base, lora, x_ckpt, dy, dx, grads, rope);
       },
-      w16);
+      true);
 }
 
 int mebp_lm_head_ce_backward(const mebp_config* cfg, const mebp_q4* emb, const float* norm_final,

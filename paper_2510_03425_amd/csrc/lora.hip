@@ -12,6 +12,8 @@
 // tiles summed through LDS in wave order). "outer" splits the token range over
 // the grid when there are many tokens; the split partials are then summed in split
 // order by a small reduce kernel. Both are deterministic.
+#include <algorithm>
+
 #include "device_common.h"
 #include "mebp_internal.h"
 
@@ -560,6 +562,12 @@ size_t lora_outer_part_floats(int M, int cols, int r) {
   return s > 1 ? (size_t)s * cols * r : 0;
 }
 
+size_t lora_outer_group_floats(int M, int cols, int r, int jobs) {
+  const int cb = (cols + 127) / 128, steps = (M + LO_M - 1) / LO_M;
+  const int s = steps < 16 ? 1 : std::max(1, std::min({(512 + cb - 1) / cb, steps / 4, 64}));
+  return s > 1 ? (size_t)jobs * s * cols * r : 0;
+}
+
 hipError_t launch_lora_rows(const LoraRowsArgs& a, int xbf16, hipStream_t st) {
   const bool shared = same_input(a.job, a.njobs, &LoraRowsJob::X, &LoraRowsJob::ldx, &LoraRowsJob::K);
   const int gy = shared ? 1 : a.njobs;
@@ -641,7 +649,8 @@ hipError_t launch_lora_outer(const LoraOuterArgs& a0, hipStream_t st) {
   }
   if (!blocks) return hipSuccess;
   int MS = outer_splits(a.M, cols);
-  if (MS > 1 && (!a.part || a.part_floats < (size_t)MS * cols * a.r)) MS = 1;
+  // (as many as the partials have room for)
+  if (MS > 1) MS = (int)std::max<size_t>(1, std::min<size_t>(MS, a.part ? a.part_floats / ((size_t)cols * a.r) : 0));
   size_t p = 0;
   for (int i = 0; i < a.ng; ++i) {
     a.g[i].part0 = p;

@@ -288,6 +288,9 @@ struct LoraOuterArgs {
 hipError_t launch_lora_outer(const LoraOuterArgs& a, hipStream_t st);
 // cols: the columns of a launch, summed over its jobs
 size_t lora_outer_part_floats(int M, int cols, int r);
+// partials of one group's jobs on 512 workgroups of 128 columns: what a layout gives a launch at
+// most (a launch splits into as many as it has room for)
+size_t lora_outer_group_floats(int M, int cols, int r, int jobs);
 hipError_t launch_fill_i32(int* p, int n, int v, hipStream_t st);
 
 // ---------------------------------------------------------------- attention

@@ -46,6 +46,8 @@ def test_lora_terms_keep_fp32(built_lib, gpu, case):
         B[:] = np.random.default_rng(PROJ.index(p)).standard_normal(B.shape) * 0.1
     x, dy = layer_input(cfg, 14)
     x = (x * 1e-3).astype(np.float32)  # (so that x is small beside the terms that are added to it)
+    # (a vocabulary sizes the workspace so that the transposed products read their weights' bf16 copy)
+    inp.cfg = cfg.with_(vocab=262144)
     dm = DeviceModel(inp, device=str(gpu))
     dm.ws.fill_(255)  # NaNs
     tx, tdy = torch.from_numpy(x).to(gpu), torch.from_numpy(dy).to(gpu)
