@@ -84,11 +84,11 @@ def measured_traffic(kernel, workload):
 # rocprofv3 output of the same run.
 KERNEL_PATTERNS = {
     "gemm_nt_f16out": r"k_gemm_nt(_big|_lds)?<(\d+, \d+, )?0(, (true|false))?(, \d+)?(, (true|false))?>"
-                      r"|k_gemm_nt_mid<(\d+, ){5}[03]>",
+                      r"|k_gemm_nt_mid<(\d+, ){3}[03]>",
     "gemm_nt_f32out": r"k_gemm_nt(_big|_lds)?<(\d+, \d+, )?1(, (true|false))?(, \d+)?(, (true|false))?>"
-                      r"|k_gemm_nt_mid<(\d+, ){5}1>",
+                      r"|k_gemm_nt_mid<(\d+, ){3}1>",
     "gemm_nt_logits": r"k_gemm_nt(_big|_lds)?<(\d+, \d+, )?2(, (true|false))?(, \d+)?(, (true|false))?>"
-                      r"|k_gemm_nt_mid<(\d+, ){5}2>",
+                      r"|k_gemm_nt_mid<(\d+, ){3}2>",
     "gemm_tn_f32out": r"k_gemm_tn(_big|_lds)?<(\d+, )?0(, (true|false))?>|k_gemm_tn_frag<(\d+, ){3}0>",
     "gemm_tn_act_bwd": r"k_gemm_tn(_big|_lds)?<(\d+, )?1(, (true|false))?>|k_gemm_tn_frag<(\d+, ){3}1>",
     "gemm_tn_probs_dh": r"k_gemm_tn(_big|_lds)?<(\d+, )?2(, (true|false))?>|k_gemm_tn_frag<(\d+, ){3}2>",

@@ -372,7 +372,6 @@ __global__ void k_attn_fwd_combine(const AttnArgs a, const float* part, int nck,
 // {4h..4h+3, 8+4h..8+4h+3} of a 16-key step, and the V^T fragment is read with the same
 // key order (two 8-byte LDS reads). The next K / V block is loaded into registers while
 // the current one is multiplied.
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 DEV f32x16 mfma32_f16(uint4 a, uint4 b, f32x16 c) {
   return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0, 0);
 }

@@ -9,8 +9,17 @@ typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef _Float16 f16;
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef __attribute__((address_space(3))) uint8_t lds_u8;
 
 #define DEV static __device__ __forceinline__
+
+// a number as a type: compile-time arguments of generic lambdas
+template <int N>
+struct IC {
+  static constexpr int value = N;
+};
 
 DEV int lane_id() { return threadIdx.x & 63; }
 
@@ -27,7 +36,6 @@ DEV float bf16_hi(uint32_t w) { return __builtin_bit_cast(float, w & 0xffff0000u
 DEV float half_bits_to_f32(uint16_t h) { return (float)__builtin_bit_cast(_Float16, h); }
 // fp32 -> fp16, round to nearest even.
 DEV uint32_t pack_f16x2(float lo, float hi) {
-  typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
   f16x2 p = {(_Float16)lo, (_Float16)hi};
   return __builtin_bit_cast(uint32_t, p);
 }
@@ -67,6 +75,25 @@ __device__ __forceinline__ f32x4 mfma16_raw(uint4 a, uint4 b, f32x4 c) {
     return mfma16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c);
 }
 
+// One 32x32x16 MFMA: lane l supplies A[l%32][8*(l/32) .. +8] and B likewise; it receives
+// D[8*(q/4) + 4*(l/32) + q%4][l%32], q = 0..15.
+template <class Op>
+DEV f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
+  if constexpr (__is_same(Op, OpF16))
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0,
+                                                  0);
+  else
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                                   0, 0);
+}
+
+// vmcnt-only wait (expcnt and lgkmcnt left open), gfx9 encoding
+template <int N>
+DEV void wait_vmcnt() {
+  static_assert(N >= 0 && N < 64, "vmcnt range");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
+}
+
 // Signed 4-bit code j (bits [4j, 4j+4)) of a packed dword (v_bfe_i32).
 DEV int nib_s(uint32_t w, int j) { return (int)(w << (28 - 4 * j)) >> 28; }
 
@@ -84,6 +111,24 @@ DEV uint4 dequant8(uint32_t w, float s) {
   r.z = Op::pack(f[4], f[5]);
   r.w = Op::pack(f[6], f[7]);
   return r;
+}
+
+// 8 int4 codes of a dword times scale into fp16 pairs (k0,k1),(k2,k3),(k4,k5),(k6,k7): the
+// offset-binary nibbles (code ^ 8) of the even and odd elements as bytes, one of each placed
+// in the two halves by a byte permute, 0x6400 | (q + 8) is the fp16 value 1024 + q + 8, so one
+// packed subtraction of 1032 gives q exactly and one packed multiply rounds q * s to nearest.
+DEV uint4 dequant8_natural(uint32_t w, f16x2 s2) {
+  const uint32_t x = w ^ 0x88888888u;
+  const uint32_t ev = x & 0x0F0F0F0Fu, od = (x >> 4) & 0x0F0F0F0Fu;
+  const f16x2 off = {(_Float16)1032.0f, (_Float16)1032.0f};
+  uint32_t o[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    // byte 0 <- even byte j, byte 2 <- odd byte j, bytes 1 and 3 <- 0
+    const uint32_t t = __builtin_amdgcn_perm(od, ev, (uint32_t)j | 0x0C00u | ((4u + j) << 16) | 0x0C000000u) | 0x64006400u;
+    o[j] = __builtin_bit_cast(uint32_t, (__builtin_bit_cast(f16x2, t) - off) * s2);
+  }
+  return make_uint4(o[0], o[1], o[2], o[3]);
 }
 
 // entry i of the RoPE table: cs[t][j] = (cos, sin)(t * theta^(-2j/dh)), computed in fp64
@@ -113,9 +158,10 @@ DEV float wave_max(float v) {
 // contiguous range of logical tiles (numbered x fastest, then y, then z): tiles that read
 // the same row block of the large operand then share one L2 instead of fetching it once per
 // XCD. A bijection for any grid size. Used by the large-tile transposed GEMM, whose gradient
-// row blocks (up to 20480 wide) are the large operand; the forward GEMMs and the 128x128
-// kernels for few tokens keep the plain order, which measured faster there (each XCD then
-// touches few weight column blocks; at few tokens everything stays in the last-level cache).
+// row blocks (up to 20480 wide) are the large operand, and under the bands of the transposed
+// products on fragments; the forward GEMMs and the 128x128 kernels for few tokens keep the plain
+// order (each XCD then touches few weight column blocks; at few tokens everything stays in the
+// last-level cache).
 struct TileId {
   int x, y, z;
 };
@@ -128,7 +174,9 @@ DEV TileId xcd_tile() {
 }
 
 // Raw buffer resources: loads through them return 0 past `bytes` (no per-element bounds
-// branches), and offsets are 32-bit VGPR values. Every resource is based at the first row
+// branches), stores past it are dropped, and offsets are 32-bit VGPR values. The check is on the
+// sum of the lane's and the scalar offset, also where the scalar one alone is past the end, and by
+// dwords: a 16-byte load across the end gets those inside. Every resource is based at the first row
 // a workgroup touches, so a region stays far below 4 GiB.
 typedef __amdgpu_buffer_rsrc_t rsrc_t;
 DEV rsrc_t make_rsrc(const void* base, size_t bytes) {

@@ -26,22 +26,6 @@ namespace {
 
 constexpr int BM = 256, BK = 64, LDT = BK + 8, NTH = 256;
 typedef uint16_t u16;
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-
-template <int N>
-struct IC {
-  static constexpr int value = N;
-};
-
-template <class Op>
-DEV f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
-  if constexpr (__is_same(Op, OpF16))
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0,
-                                                  0);
-  else
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
-                                                   0, 0);
-}
 
 template <int NJ>
 DEV void zero_acc(f32x16 (&acc)[4][NJ]) {
@@ -200,7 +184,6 @@ DEV void store_a_tile(u16* As, int tid, const uint4 (&ra)[8]) {
 // 8 int4 codes (two's complement, element i in bits 4i..4i+3) times scale into fp16 pairs
 // (k0,k4),(k1,k5),(k2,k6),(k3,k7): 0x6400 | (q + 8) is the fp16 value 1024 + q + 8, so one
 // packed subtraction of 1032 gives q exactly and one packed multiply rounds q * s to nearest.
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 DEV uint4 dequant8_paired(uint32_t w, f16x2 s2) {
   const uint32_t x = w ^ 0x88888888u;
   const f16x2 off = {(_Float16)1032.0f, (_Float16)1032.0f};
@@ -673,32 +656,6 @@ __global__ __launch_bounds__(128 * WNW, 1) void k_gemm_nt_big(const NtArgs a) {
 
 
 // ---------------------------------------------------------------- forward, LDS-direct tiles
-// Natural-order decompression: 8 int4 codes k0..k7 of a dword times scale into fp16 pairs
-// (k0,k1),(k2,k3),(k4,k5),(k6,k7). Offset-binary nibbles (code ^ 8) of the even and the odd
-// elements are gathered into bytes, a byte permute places one even and one odd code in the
-// two halves, 0x6400 | (q + 8) is the fp16 value 1024 + q + 8, and one packed subtraction of
-// 1032 and one packed multiply give q exactly and then q * s rounded to nearest.
-DEV uint4 dequant8_natural(uint32_t w, f16x2 s2) {
-  const uint32_t ev = (w & 0x0F0F0F0Fu) ^ 0x08080808u;         // k0, k2, k4, k6
-  const uint32_t od = ((w >> 4) & 0x0F0F0F0Fu) ^ 0x08080808u;  // k1, k3, k5, k7
-  const f16x2 off = {(_Float16)1032.0f, (_Float16)1032.0f};
-  uint32_t o[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    // byte 0 <- even byte j, byte 2 <- odd byte j, bytes 1 and 3 <- 0
-    const uint32_t t = __builtin_amdgcn_perm(od, ev, (uint32_t)j | 0x0C00u | ((4u + j) << 16) | 0x0C000000u) | 0x64006400u;
-    o[j] = __builtin_bit_cast(uint32_t, (__builtin_bit_cast(f16x2, t) - off) * s2);
-  }
-  return make_uint4(o[0], o[1], o[2], o[3]);
-}
-
-// vmcnt-only wait (expcnt and lgkmcnt left open), gfx9 encoding
-template <int N>
-DEV void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
-}
-
 // Forward product with 256 x 256 tiles, K step 64, on NW waves: 4 waves of 256 x 64 (one
 // wave per SIMD, 256 accumulator registers each; the fp16 and fp32 outputs) or 8 waves of
 // 128 x 64 (2 along m x 4 along n; the LM head's logits, whose epilogue takes 128-row waves).
@@ -799,7 +756,6 @@ __global__ __launch_bounds__(64 * NW, 1) void k_gemm_nt_lds(const NtArgs a) {
       for (int q = 0; q < 16; ++q) acc[i][j][q] = 0.f;
   const bool tail = (K % BK) != 0;
   // (the rank is 8 or 16 whenever a LoRA factor is given)
-  typedef __attribute__((address_space(3))) uint8_t lds_u8;
   if constexpr (GATED) {
     // per segment: BM u rows (r KiB) and the tile's 128 B rows (r / 2 KiB), 1 KiB per wave
     // and instruction

@@ -18,8 +18,6 @@
 // one 16384-column chunk of its logits 1613 -> 1298; at 4096 tokens of the 1536-wide shape qkv
 // 57 -> 40, down 188 -> 159; at 999 tokens of the 896-wide shape gate/up 93 -> 35; at 256 tokens
 // qkv 17 -> 7, logits 193 -> 105.
-#include <stdlib.h>
-
 #include "device_common.h"
 #include "mebp_internal.h"
 
@@ -28,23 +26,6 @@ namespace {
 
 constexpr int BK = 64;
 typedef uint16_t u16;
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef __attribute__((address_space(3))) uint8_t lds_u8;
-
-template <int N>
-struct IC {
-  static constexpr int value = N;
-};
-
-template <class Op>
-DEV f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
-  if constexpr (__is_same(Op, OpF16))
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0,
-                                                  0);
-  else
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
-                                                   0, 0);
-}
 
 // v (8 fp32) in three bf16 parts, v = p[0] + p[1] + p[2] up to 2^-24: each part is the rounding of
 // what the ones before leave
@@ -70,35 +51,10 @@ DEV Split3 split3_bf16(const float (&v)[8]) {
   return s;
 }
 
-// 8 int4 codes of a dword times scale into fp16 pairs (k0,k1),(k2,k3),(k4,k5),(k6,k7): the
-// offset-binary nibbles (code ^ 8) of the even and odd elements as bytes, one of each placed
-// in the two halves by a byte permute, 0x6400 | (q + 8) is the fp16 value 1024 + q + 8, so one
-// packed subtraction of 1032 gives q exactly and one packed multiply rounds q * s to nearest.
-typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
-DEV uint4 dequant8_natural(uint32_t w, f16x2 s2) {
-  const uint32_t x = w ^ 0x88888888u;
-  const uint32_t ev = x & 0x0F0F0F0Fu, od = (x >> 4) & 0x0F0F0F0Fu;
-  const f16x2 off = {(_Float16)1032.0f, (_Float16)1032.0f};
-  uint32_t o[4];
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    // byte 0 <- even byte j, byte 2 <- odd byte j, bytes 1 and 3 <- 0
-    const uint32_t t = __builtin_amdgcn_perm(od, ev, (uint32_t)j | 0x0C00u | ((4u + j) << 16) | 0x0C000000u) | 0x64006400u;
-    o[j] = __builtin_bit_cast(uint32_t, (__builtin_bit_cast(f16x2, t) - off) * s2);
-  }
-  return make_uint4(o[0], o[1], o[2], o[3]);
-}
-
 // 16 bytes per lane from a buffer (per-lane and wave-uniform byte offsets) into LDS at
 // dst + 16 lane, without passing through registers
 DEV void load_lds16(rsrc_t r, lds_u8* dst, uint32_t voff, int soff) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, dst, 16, (int)voff, soff, 0, 0);
-}
-
-template <int N>
-DEV void wait_vmcnt() {
-  static_assert(N >= 0 && N < 64, "vmcnt range");
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4) | (15 << 8));
 }
 
 // c += u v^T of fp32 factors: the six products of parts that reach 2^-24 of the result, the
@@ -159,7 +115,7 @@ DEV T sel(bool c, T x, T y) {
 // ------------------------------------------------------------------------------ forward
 // C[m][n] = sum_k X[m][k] W[n][k], fp16 operands, on 32 MI x 64 WN output tiles: WN waves of
 // 32 MI x 64 side by side, WK groups of them that split the reduction inside the workgroup.
-//  * Activations go from global memory straight into a ring of ST LDS stages of 32 MI x 64
+//  * Activations go from global memory straight into a ring of two LDS stages of 32 MI x 64
 //    (rows of 128 bytes, 16-byte chunk c at position c ^ ((row / 2) % 8): the 16 lanes of one
 //    LDS read cycle hit 16 distinct bank groups), one ring per group.
 //  * Each wave loads the int4 codes and scales of its own 64 columns into registers and
@@ -174,43 +130,28 @@ DEV T sel(bool c, T x, T y) {
 enum MidEpi { MID_F16 = 0, MID_F32 = 1, MID_LOGITS = 2, MID_GATED = 3, MID_PARTIAL = 4 };
 
 // The waits of the loop count vector-memory instructions, so every load that it issues must
-// have a use (the compiler drops the others): code rows (of CS) and scales (0 or 1) that step j
-// loads, in the eight-step body and in the tail of up to seven steps behind it, which loads
-// only what its own steps 4 .. 6 (scales) and j + CS .. 6 (codes) use.
-constexpr int code_rows(int j, int CS, bool tail) {
-  if (j % CS) return 0;
-  const int left = 7 - (j % 8 + CS);
-  return !tail || left >= CS ? CS : left > 0 ? left : 0;
+// have a use (the compiler drops the others): code rows (two steps' every two steps) and scales
+// (four steps' every four) that step j loads, in the eight-step body and in the tail of up to seven
+// steps behind it, which loads only what its own steps j + 2 .. 6 (codes) and 4 .. 6 (scales) use.
+constexpr int code_rows(int j, bool tail) {
+  if (j % 2) return 0;
+  const int left = 7 - (j % 8 + 2);
+  return !tail || left >= 2 ? 2 : left > 0 ? left : 0;
 }
 constexpr int scale_rows(int j, bool tail) { return j % 4 == 0 && (!tail || j % 8 == 0); }
-constexpr int weight_loads(int j, int CS, bool tail) { return 2 * (code_rows(j, CS, tail) + scale_rows(j, tail)); }
-// instructions issued after the activation tile of step j + 1 when step j ends (tiles are issued
-// D steps ahead; the steps before a tail are the last ones of the body)
-constexpr int after_tile(int j, int D, int NA, int CS, bool tail) {
-  int n = 0;
-  for (int t = j + 1 - D; t <= j; ++t)
-    n += (t > j + 1 - D ? NA : 0) + weight_loads((t + 8) % 8, CS, tail && t >= 0);
-  return n;
-}
+constexpr int weight_loads(int j, bool tail) { return 2 * (code_rows(j, tail) + scale_rows(j, tail)); }
 
-template <int MI, int WN, int WK, int ST, int CS, int EPI>
+template <int MI, int WN, int WK, int EPI>
 __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_nt_mid(const NtArgs a) {
   constexpr int NJ = 2, BM = 32 * MI, NA = 4 * MI / WN, STB = BM * BK * 2;
-  static_assert(ST == 2 || (ST == 4 && CS == 4), "ring stages");
-  static_assert(CS == 2 || CS == 4, "K steps per load of the codes");
   static_assert(WN == 1 || WK == 1, "a shared ring and a split reduction are not combined");
   static_assert(4 * MI % WN == 0, "the waves of a shared ring load equal parts of a stage");
-  static_assert(WK == 1 || (4 * MI) % WK == 0 || WK % (4 * MI) == 0, "waves finish whole row groups");
+  static_assert((4 * MI) % WK == 0, "waves finish whole row groups");
   __shared__ __attribute__((aligned(1024))) uint8_t lds0[WK * STB];
   __shared__ __attribute__((aligned(1024))) uint8_t lds1[WK * STB];
-  __shared__ __attribute__((aligned(1024))) uint8_t lds2[ST == 4 ? WK * STB : 16];
-  __shared__ __attribute__((aligned(1024))) uint8_t lds3[ST == 4 ? WK * STB : 16];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wn = WN > 1 ? wave : 0, wk = WK > 1 ? wave : 0, h = lane >> 5, l32 = lane & 31;
-  auto stage = [&](auto S_) -> uint8_t* {
-    constexpr int st = decltype(S_)::value;
-    return (st == 0 ? lds0 : st == 1 ? lds1 : st == 2 ? lds2 : lds3) + wk * STB;
-  };
+  auto stage = [&](auto S_) -> uint8_t* { return (decltype(S_)::value == 0 ? lds0 : lds1) + wk * STB; };
   // (plain order: every XCD keeps a few columns' weights; bands measured the same here)
   const int m0 = blockIdx.y * BM, K = a.K, Kh = K >> 1, kgroups = K >> 5;
   // this wave's two column blocks: weight rows c[j] .. c[j] + 32 of segment sj
@@ -254,7 +195,7 @@ __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_nt_mid(const NtArgs a)
   }
   const uint32_t offB = (uint32_t)(l32 * Kh + 16 * h), offS = (uint32_t)(l32 * kgroups * 2);
   const uint32_t ssel = h ? 0x03020302u : 0x01000100u;  // this half's scale, twice
-  uint4 rb[2][CS][NJ];  // codes of CS steps, two buffers
+  uint4 rb[2][2][NJ];   // codes of two steps, two buffers
   uint4 rsc[2][NJ];     // fp16 scales of four steps (eight groups), two buffers
   auto load_a = [&](auto S_, int kt) {
     lds_u8* dst = (lds_u8*)stage(S_);
@@ -325,27 +266,26 @@ __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_nt_mid(const NtArgs a)
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  // Step j (mod 8) of the loop issues the activation tile ST - 1 steps ahead, then (every CS
-  // steps) the next CS steps' codes and (every four) the next four steps' scales, then
-  // multiplies. It ends when this wave's loads of the next tile have landed (counting what was
-  // issued after them) and, with a shared ring, so have the other waves'.
-  constexpr int D = ST - 1;
+  // Step j (mod 8) of the loop issues the next activation tile, then (every two steps) the next two
+  // steps' codes and (every four) the next four steps' scales, then multiplies. It ends when this
+  // wave's loads of the next tile have landed (counting what was issued after them) and, with a
+  // shared ring, so have the other waves'.
   auto sync = [&](auto J_, auto T_) {
-    wait_vmcnt<after_tile(decltype(J_)::value, D, NA, CS, decltype(T_)::value != 0)>();
+    wait_vmcnt<weight_loads(decltype(J_)::value, decltype(T_)::value != 0)>();
     if constexpr (WN > 1) __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
   auto step = [&](auto J_, auto T_, int k) {
-    constexpr int j = decltype(J_)::value, cb = (j / CS) & 1, sb = (j / 4) & 1;
+    constexpr int j = decltype(J_)::value, cb = (j / 2) & 1, sb = (j / 4) & 1;
     constexpr bool tail = decltype(T_)::value != 0;
-    load_a(IC<(j + D) % ST>{}, min(k + D, kt_end - 1));
-    load_codes(IC<1 - cb>{}, IC<code_rows(j, CS, tail)>{}, k + CS);
+    load_a(IC<1 - j % 2>{}, min(k + 1, kt_end - 1));
+    load_codes(IC<1 - cb>{}, IC<code_rows(j, tail)>{}, k + 2);
     if constexpr (scale_rows(j, tail) > 0) load_scales(IC<1 - sb>{}, k + 4);
     uint32_t sw[NJ];
 #pragma unroll
     for (int q = 0; q < NJ; ++q)
       sw[q] = j % 4 == 0 ? rsc[sb][q].x : j % 4 == 1 ? rsc[sb][q].y : j % 4 == 2 ? rsc[sb][q].z : rsc[sb][q].w;
-    mma(IC<j % ST>{}, rb[cb][j % CS], sw);
+    mma(IC<j % 2>{}, rb[cb][j % 2], sw);
     sync(J_, T_);
   };
   if (kt_begin < kt_end) {
@@ -353,13 +293,9 @@ __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_nt_mid(const NtArgs a)
     // reduction: those of the last group, whose range is never empty)
     const bool lora0 = (WK == 1 || wk == WK - 1) && EPI != MID_LOGITS && EPI != MID_PARTIAL && SEG(s0, lora_B);
     const bool lora1 = EPI == MID_GATED ? (WK == 1 || wk == WK - 1) && a.seg[1].lora_B : lora0;
-    load_codes(IC<0>{}, IC<CS>{}, kt_begin);
+    load_codes(IC<0>{}, IC<2>{}, kt_begin);
     load_scales(IC<0>{}, kt_begin);
     load_a(IC<0>{}, kt_begin);
-    if constexpr (ST == 4) {
-      load_a(IC<1>{}, min(kt_begin + 1, kt_end - 1));
-      load_a(IC<2>{}, min(kt_begin + 2, kt_end - 1));
-    }
     if (lora0 || lora1) {
       const int q0 = 8 * h, r = a.r;
       const bool keep = q0 < r;
@@ -387,7 +323,7 @@ __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_nt_mid(const NtArgs a)
         }
       }
     }
-    wait_vmcnt<(D - 1) * NA>();
+    wait_vmcnt<0>();
     if constexpr (WN > 1) __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     int k = kt_begin;
@@ -573,11 +509,7 @@ __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_nt_mid(const NtArgs a)
         p0[(i * 16 + q) * 64] = acc[i][0][q];
         p1[(i * 16 + q) * 64] = acc[i][1][q];
       }
-    constexpr int GPW = WK > 4 * MI ? 1 : 4 * MI / WK;  // row groups per wave
-    if (WK > 4 * MI && wk >= 4 * MI) {
-      __syncthreads();
-      return;
-    }
+    constexpr int GPW = 4 * MI / WK;  // row groups per wave
     Extra x[GPW];
 #pragma unroll
     for (int gi = 0; gi < GPW; ++gi) fetch((wk * GPW + gi) >> 2, (wk * GPW + gi) & 3, x[gi]);
@@ -673,11 +605,11 @@ __global__ __launch_bounds__(256) void k_frag_weights(const FragArgs a) {
 // WK = 1 the 16-bit ones go through LDS, 16 rows at a time, so that a lane moves 8 consecutive
 // columns of a row (16-byte accesses instead of 2-byte ones in the MFMA layout).
 template <int MI, int WN, int WK, int EPI>
-__global__ __launch_bounds__(64 * WN * WK, MI > 4 ? 1 : 2) void k_gemm_tn_frag(const TnArgs a) {
+__global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_tn_frag(const TnArgs a) {
   constexpr int NJ = 2, BM = 32 * MI, NA = 4 * MI / WN, STB = BM * BK * 2;
   static_assert(WN == 1 || WK == 1, "a shared ring and a split reduction are not combined");
   static_assert(4 * MI % WN == 0, "the waves of a shared ring load equal parts of a stage");
-  static_assert(WK == 1 || (4 * MI) % WK == 0 || WK % (4 * MI) == 0, "waves finish whole row groups");
+  static_assert((4 * MI) % WK == 0, "waves finish whole row groups");
   __shared__ __attribute__((aligned(1024))) uint8_t lds0[WK * STB];
   __shared__ __attribute__((aligned(1024))) uint8_t lds1[WK * STB];
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -938,8 +870,7 @@ __global__ __launch_bounds__(64 * WN * WK, MI > 4 ? 1 : 2) void k_gemm_tn_frag(c
         p1[(i * 16 + q) * 64] = acc[i][1][q];
       }
     __syncthreads();
-    constexpr int GPW = WK > 4 * MI ? 1 : 4 * MI / WK;
-    if (WK > 4 * MI && wk >= 4 * MI) return;
+    constexpr int GPW = 4 * MI / WK;
 #pragma unroll
     for (int gi = 0; gi < GPW; ++gi) {
       const int g = wk * GPW + gi, i = g >> 2, qg = g & 3;
@@ -1118,7 +1049,7 @@ hipError_t launch_gemm_nt_mid(const NtArgs& a0, int epi, int S, double flops, do
   const char* name = epi == NT_STORE_F16 ? "gemm_nt_f16out" : epi == NT_STORE_F32 ? "gemm_nt_f32out" : "gemm_nt_logits";
 #define MID_GO(MI, WN, WK, EPI) \
   MEBP_TIMED(st, name, flops, bytes, \
-             hipLaunchKernelGGL((k_gemm_nt_mid<MI, WN, WK, 2, 2, EPI>), grid, dim3(64 * WN * WK), 0, st, a))
+             hipLaunchKernelGGL((k_gemm_nt_mid<MI, WN, WK, EPI>), grid, dim3(64 * WN * WK), 0, st, a))
 #define MID_EPI(MI, WN, WK)              \
   do {                                   \
     if (S > 1)                           \
