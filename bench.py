@@ -467,17 +467,15 @@ def experiments(cfg, seqs=(128, 256, 512, 1024, 2048, 4096)):
 
 def decompression_overhead(cfg, reps=5):
     """Counterpart of the paper's decompression-share table for this design, on the
-    workload's projection shapes (M = B*T tokens). Forward products: the decompression is
-    fused into the GEMM; the production kernel runs once on the int4 weights and once on
-    the same weights already decompressed to fp16 (the same kernel with the decompression
-    taken out; mebp_test_gemm kinds NT_LDS / NT_LDS_W16). Input-gradient products: the
-    training path decompresses the weights into a transient bf16 copy right before the
-    large-tile kernel reads them, so int4 = that pass (mebp_dequant_q4 to bf16) plus the
-    kernel on the copy (TN_BIG_W16) and 16-bit = the kernel alone; the int4-fused variant
-    of the same kernel (TN_BIG) is reported beside them. Per step every projection runs
+    workload's projection shapes (M = B*T tokens), on the kernels and tiles that training
+    runs. Forward products: the decompression is fused into the kernel, which has no 16-bit
+    form; 16-bit = the library's fp16 product of the same weights already decompressed (with
+    fp16 outputs, half the bytes of the kernel's fp32 ones here).
+    Input-gradient products: the training path writes a bf16 copy of the weights in operand
+    order and multiplies that, so int4 = copy and kernel (mebp_test_gemm kind TN_FRAG) and
+    16-bit = the kernel alone on the copy (TN_FRAG_AGAIN). Per step every projection runs
     twice forward (forward pass and recompute) and once backward, in each of the L layers.
-    overhead = t_int4 / t_16bit - 1 (negative: the int4 path is faster, its weight operand
-    being a quarter of the bytes)."""
+    overhead = t_int4 / t_16bit - 1 (negative: the int4 path is faster)."""
     import numpy as np
     import torch
     from mebp_inputs import PROJ, quantize_q4
@@ -496,7 +494,7 @@ def decompression_overhead(cfg, reps=5):
         return e0.elapsed_time(e1) / reps
 
     M, st = cfg.n_tokens, stream_handle()
-    rows, tot = {}, {"fwd_int4": 0.0, "fwd_16": 0.0, "bwd_int4": 0.0, "bwd_16": 0.0, "bwd_int4_fused": 0.0}
+    rows, tot = {}, {"fwd_int4": 0.0, "fwd_16": 0.0, "bwd_int4": 0.0, "bwd_16": 0.0}
     for p in PROJ:
         n_out, n_in = cfg.proj_shape(p)
         rng = np.random.default_rng(0)
@@ -505,35 +503,27 @@ def decompression_overhead(cfg, reps=5):
         wq = L.MebpQ4(q4=tq.data_ptr(), scale=ts.data_ptr())
         wf = torch.empty((n_out, n_in), dtype=torch.float32, device="cuda")
         L.mebp_dequant_q4(wq, n_out, n_in, cfg.group, wf.data_ptr(), 0, st)
-        w_h, w_b = wf.half().contiguous(), wf.bfloat16().contiguous()
+        w_h = wf.half().t()
         x = (torch.randn(M, n_in, device="cuda") * 0.5).half()
         g = (torch.randn(M, n_out, device="cuda") * 0.01).bfloat16()
         out_f = torch.empty(M, n_out, device="cuda")
         out_b = torch.empty(M, n_in, device="cuda")
-        w16 = L.MebpQ4(q4=w_h.data_ptr(), scale=0)
-        b16 = L.MebpQ4(q4=w_b.data_ptr(), scale=0)
-        w_t = torch.empty((n_out, n_in), dtype=torch.int16, device="cuda")  # the transient bf16 copy
-        t16 = L.MebpQ4(q4=w_t.data_ptr(), scale=0)
-        r = {"fwd_int4": timed(lambda: L.mebp_test_gemm(L.TEST_GEMM_NT_LDS, wq, n_out, n_in, x.data_ptr(), M,
-                                                         out_f.data_ptr(), st)),
-             "fwd_16": timed(lambda: L.mebp_test_gemm(L.TEST_GEMM_NT_LDS_W16, w16, n_out, n_in, x.data_ptr(), M,
-                                                       out_f.data_ptr(), st)),
-             "bwd_int4": timed(lambda: (L.mebp_dequant_q4(wq, n_out, n_in, cfg.group, 0, w_t.data_ptr(), st),
-                                        L.mebp_test_gemm(L.TEST_GEMM_TN_BIG_W16, t16, n_out, n_in, g.data_ptr(), M,
-                                                         out_b.data_ptr(), st))),
-             "bwd_16": timed(lambda: L.mebp_test_gemm(L.TEST_GEMM_TN_BIG_W16, b16, n_out, n_in, g.data_ptr(), M,
-                                                       out_b.data_ptr(), st)),
-             "bwd_int4_fused": timed(lambda: L.mebp_test_gemm(L.TEST_GEMM_TN_BIG, wq, n_out, n_in, g.data_ptr(), M,
-                                                               out_b.data_ptr(), st))}
+
+        def run(kind, a, out):
+            L.mebp_test_gemm(kind + L.TEST_GEMM_PLANNED, wq, n_out, n_in, a.data_ptr(), M, out.data_ptr(), st)
+
+        r = {"fwd_int4": timed(lambda: run(L.TEST_GEMM_NT_MID, x, out_f)),
+             "fwd_16": timed(lambda: x @ w_h),
+             "bwd_int4": timed(lambda: run(L.TEST_GEMM_TN_FRAG, g, out_b)),
+             "bwd_16": timed(lambda: run(L.TEST_GEMM_TN_FRAG_AGAIN, g, out_b))}
         rows[p] = {k: round(v, 4) for k, v in r.items()}
         for k in tot:
             tot[k] += r[k] * cfg.n_layers * (2 if k.startswith("fwd") else 1)
-        del tq, ts, wf, w_h, w_b, w_t, x, g, out_f, out_b
+        del tq, ts, wf, w_h, x, g, out_f, out_b
         torch.cuda.empty_cache()
     res = {"tokens": M, "per_projection_ms": rows,
-           "forward_ms_per_step": {"int4": round(tot["fwd_int4"], 2), "16bit": round(tot["fwd_16"], 2)},
-           "backward_ms_per_step": {"int4": round(tot["bwd_int4"], 2), "16bit": round(tot["bwd_16"], 2),
-                                    "int4_fused_kernel": round(tot["bwd_int4_fused"], 2)},
+           "forward_ms_per_step": {"int4": round(tot["fwd_int4"], 2), "library_16bit": round(tot["fwd_16"], 2)},
+           "backward_ms_per_step": {"int4": round(tot["bwd_int4"], 2), "16bit": round(tot["bwd_16"], 2)},
            "overhead_forward": round(tot["fwd_int4"] / tot["fwd_16"] - 1, 4),
            "overhead_backward": round(tot["bwd_int4"] / tot["bwd_16"] - 1, 4)}
     log(f"decompression inside the GEMMs ({cfg.name}): forward {res['overhead_forward']:+.1%}, backward "

@@ -279,7 +279,7 @@ int mebp_workspace_guard_check(const mebp_config* cfg, int32_t B, int32_t T, voi
 int mebp_dequant_q4(const mebp_q4* w, int32_t rows, int32_t cols, int32_t group, float* out_f32,
                     uint16_t* out_bf16, mebp_stream_t stream);
 
-/* One production dequant-GEMM kernel on caller operands (test aid for the bit-exact check of
+/* One dequant-GEMM kernel of the library on caller operands (test aid for the bit-exact check of
  * the decompression fused into the products, Algorithm 1's LazyLoadAndDecompressWeights):
  * one split, no LoRA term, no residual, fp32 outputs.
  *   forward kinds (the layer projections and the LM-head logits):
@@ -300,7 +300,16 @@ enum {
   MEBP_TEST_GEMM_NT_LDS_W16 = 6, /* MEBP_TEST_GEMM_NT_LDS on plain fp16 weights: w->q4      */
                                  /* points at W fp16 [n_out][n_in], w->scale is unused (the */
                                  /* same kernel without the decompression, to measure it)   */
-  MEBP_TEST_GEMM_TN_BIG_W16 = 7  /* MEBP_TEST_GEMM_TN_BIG on plain bf16 weights, likewise   */
+  MEBP_TEST_GEMM_TN_BIG_W16 = 7, /* MEBP_TEST_GEMM_TN_BIG on plain bf16 weights, likewise   */
+  /* the kernels that the configured shapes run on: add the tile configuration (0 .. 5       */
+  /* forward, 0 .. 6 transposed) or MEBP_TEST_GEMM_PLANNED for the one the library picks     */
+  MEBP_TEST_GEMM_NT_MID = 16,    /* forward; n_in a multiple of 64, scales 4-byte aligned    */
+  MEBP_TEST_GEMM_TN_FRAG = 32,   /* transposed, on a bf16 copy of the weights in operand     */
+                                 /* order that the call writes into the library's buffer     */
+                                 /* (MEBP_STATIC_SCRATCH_BYTES; shared as described there)   */
+  MEBP_TEST_GEMM_TN_FRAG_AGAIN = 48, /* the same without writing the copy: on the one that   */
+                                 /* the previous call of that kind left                      */
+  MEBP_TEST_GEMM_PLANNED = 15
 };
 int mebp_test_gemm(int32_t kind, const mebp_q4* w, int32_t n_out, int32_t n_in, const void* x, int32_t M,
                    float* out, mebp_stream_t stream);

@@ -32,6 +32,9 @@ STATIC_SCRATCH_BYTES = 64 << 20  # MEBP_STATIC_SCRATCH_BYTES
 # mebp_test_gemm kinds
 (TEST_GEMM_NT, TEST_GEMM_NT_BIG128, TEST_GEMM_NT_BIG256, TEST_GEMM_NT_LDS, TEST_GEMM_TN, TEST_GEMM_TN_BIG,
  TEST_GEMM_NT_LDS_W16, TEST_GEMM_TN_BIG_W16) = range(8)
+# ... plus a tile configuration (TEST_GEMM_NT_TILES, TEST_GEMM_TN_TILES of them) or the planned one
+TEST_GEMM_NT_MID, TEST_GEMM_TN_FRAG, TEST_GEMM_TN_FRAG_AGAIN, TEST_GEMM_PLANNED = 16, 32, 48, 15
+TEST_GEMM_NT_TILES, TEST_GEMM_TN_TILES = 6, 7
 
 
 class MebpConfig(C.Structure):

@@ -1743,7 +1743,11 @@ int mebp_dequant_q4(const mebp_q4* w, int32_t rows, int32_t cols, int32_t group,
 int mebp_test_gemm(int32_t kind, const mebp_q4* w, int32_t n_out, int32_t n_in, const void* x, int32_t M, float* out,
                    mebp_stream_t stream) {
   int e;
-  if (kind < MEBP_TEST_GEMM_NT || kind > MEBP_TEST_GEMM_TN_BIG_W16) return fail(MEBP_EINVAL, "unknown GEMM kind %d", kind);
+  const int mid = kind & ~15, tile = (kind & 15) == MEBP_TEST_GEMM_PLANNED ? -1 : kind & 15;
+  const bool nt_mid = mid == MEBP_TEST_GEMM_NT_MID && tile < 6;
+  const bool tn_frag = (mid == MEBP_TEST_GEMM_TN_FRAG || mid == MEBP_TEST_GEMM_TN_FRAG_AGAIN) && tile < 7;
+  if ((kind < MEBP_TEST_GEMM_NT || kind > MEBP_TEST_GEMM_TN_BIG_W16) && !nt_mid && !tn_frag)
+    return fail(MEBP_EINVAL, "unknown GEMM kind %d", kind);
   if (kind == MEBP_TEST_GEMM_NT_LDS_W16 || kind == MEBP_TEST_GEMM_TN_BIG_W16) {
     if (!w || !w->q4 || !aligned(w->q4, 16)) return fail(MEBP_EINVAL, "16-bit weight NULL or not 16-byte aligned");
   } else if ((e = check_q4(w, "weight"))) {
@@ -1753,6 +1757,21 @@ int mebp_test_gemm(int32_t kind, const mebp_q4* w, int32_t n_out, int32_t n_in, 
   if (M > 65536 || n_out > 65536 || n_in > 65536) return fail(MEBP_EUNSUPPORTED, "size above 65536");
   if (n_in % 16 || n_out % 16) return fail(MEBP_EUNSUPPORTED, "n_in %d / n_out %d not multiples of 16", n_in, n_out);
   if ((e = check_act(x, "x")) || (e = check_act(out, "out"))) return e;
+  if (nt_mid) {
+    if (!gemm_nt_mid_ok(n_in) || !aligned(w->scale, 4))
+      return fail(MEBP_EUNSUPPORTED, "n_in %d not a multiple of 64 or scales not 4-byte aligned", n_in);
+    HIP_TRY(launch_gemm_nt_probe(tile, w->q4, w->scale, n_out, n_in, x, M, out, (hipStream_t)stream));
+    return MEBP_OK;
+  }
+  if (tn_frag) {
+    if (frag_elems(n_out, n_in) * 2 > MEBP_STATIC_SCRATCH_BYTES)
+      return fail(MEBP_EUNSUPPORTED, "%d x %d weights exceed the library's buffer in bf16", n_out, n_in);
+    void* frags = static_scratch();
+    if (!frags) return MEBP_EHIP;
+    HIP_TRY(launch_gemm_tn_probe(tile, w->q4, w->scale, n_out, n_in, x, M, out, (uint16_t*)frags,
+                                 mid == MEBP_TEST_GEMM_TN_FRAG, (hipStream_t)stream));
+    return MEBP_OK;
+  }
   HIP_TRY(launch_gemm_probe(kind, w->q4, w->scale, n_out, n_in, x, M, out, (hipStream_t)stream));
   return MEBP_OK;
 }

@@ -126,8 +126,8 @@ DEV T sel(bool c, T x, T y) {
 // The two 32-column blocks of a wave are chosen by the epilogue that pairs them in registers:
 // the halves (e, e + dh/2) of a RoPE head, the gate and up columns of the same features, or
 // simply 64 consecutive columns.
-// MID_PARTIAL: raw fp32 tiles into plane blockIdx.z of `part` (grid-split reductions).
-enum MidEpi { MID_F16 = 0, MID_F32 = 1, MID_LOGITS = 2, MID_GATED = 3, MID_PARTIAL = 4 };
+// MID_PLANES: raw fp32 tiles into plane blockIdx.z of `part` (grid-split reductions).
+enum MidEpi { MID_F16 = 0, MID_F32 = 1, MID_LOGITS = 2, MID_GATED = 3, MID_PLANES = 4 };
 
 // The waits of the loop count vector-memory instructions, so every load that it issues must
 // have a use (the compiler drops the others): code rows (two steps' every two steps) and scales
@@ -183,7 +183,7 @@ __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_nt_mid(const NtArgs a)
   const rsrc_t rS1 = make_rsrc(SEG(s1, scale) + (size_t)min(c1, Nn) * kgroups, (size_t)r1 * kgroups * 2);
   // (ranges of a split reduction start on even steps: whole 64-byte pieces of the code rows)
   const int nk = K / BK, np = (nk + 1) >> 1;
-  const int z = EPI == MID_PARTIAL ? (int)blockIdx.z * WK + wk : wk, Z = EPI == MID_PARTIAL ? (int)gridDim.z * WK : WK;
+  const int z = EPI == MID_PLANES ? (int)blockIdx.z * WK + wk : wk, Z = EPI == MID_PLANES ? (int)gridDim.z * WK : WK;
   const int kt_begin = 2 * (np * z / Z), kt_end = min(nk, 2 * (np * (z + 1) / Z));
 
   // activation loads: instruction i fills rows 8 (wn + WN i) .. + 8 of the group's stage
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_nt_mid(const NtArgs a)
   if (kt_begin < kt_end) {
     // the LoRA term starts the accumulators while the first tiles are in flight (of a split
     // reduction: those of the last group, whose range is never empty)
-    const bool lora0 = (WK == 1 || wk == WK - 1) && EPI != MID_LOGITS && EPI != MID_PARTIAL && SEG(s0, lora_B);
+    const bool lora0 = (WK == 1 || wk == WK - 1) && EPI != MID_LOGITS && EPI != MID_PLANES && SEG(s0, lora_B);
     const bool lora1 = EPI == MID_GATED ? (WK == 1 || wk == WK - 1) && a.seg[1].lora_B : lora0;
     load_codes(IC<0>{}, IC<2>{}, kt_begin);
     load_scales(IC<0>{}, kt_begin);
@@ -406,12 +406,12 @@ __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_nt_mid(const NtArgs a)
   // residual) go through buffer resources based at row m0: rows past M and columns past the
   // segment are dropped (or read 0) by the bounds check, without branches.
   const int n0 = c0 + l32, n1 = c1 + l32, rows = min(BM, a.M - m0);
-  constexpr int ESZ = EPI == MID_F32 || EPI == MID_PARTIAL ? 4 : 2;
-  const int ldo = EPI == MID_PARTIAL ? a.ldp : SEG(s0, ldo), rope = EPI == MID_F16 ? SEG(s0, rope) : 0;
+  constexpr int ESZ = EPI == MID_F32 || EPI == MID_PLANES ? 4 : 2;
+  const int ldo = EPI == MID_PLANES ? a.ldp : SEG(s0, ldo), rope = EPI == MID_F16 ? SEG(s0, rope) : 0;
   auto out_rsrc = [&](void* base, int ld) {
     return make_rsrc((char*)base + (size_t)m0 * ld * ESZ, ((size_t)(rows - 1) * ld + Nn) * ESZ);
   };
-  const rsrc_t rO = out_rsrc(EPI == MID_PARTIAL ? (void*)(a.part + (size_t)blockIdx.z * a.M * a.ldp + SEG(s0, col0)) : SEG(s0, out), ldo);
+  const rsrc_t rO = out_rsrc(EPI == MID_PLANES ? (void*)(a.part + (size_t)blockIdx.z * a.M * a.ldp + SEG(s0, col0)) : SEG(s0, out), ldo);
   const uint32_t o0 = n0 < Nn ? (uint32_t)(4 * h * ldo + n0) * ESZ : 0x80000000u;
   const uint32_t o1 = n1 < Nn ? (uint32_t)(4 * h * ldo + n1) * ESZ : 0x80000000u;
   const rsrc_t rO1 = EPI == MID_GATED ? out_rsrc(a.seg[1].out, a.seg[1].ldo) : rO;
@@ -607,6 +607,7 @@ __global__ __launch_bounds__(256) void k_frag_weights(const FragArgs a) {
 template <int MI, int WN, int WK, int EPI>
 __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_tn_frag(const TnArgs a) {
   constexpr int NJ = 2, BM = 32 * MI, NA = 4 * MI / WN, STB = BM * BK * 2;
+  constexpr bool RAW = EPI == TN_PARTIAL_F32 || EPI == TN_PLANES;  // fp32 tiles into planes
   static_assert(WN == 1 || WK == 1, "a shared ring and a split reduction are not combined");
   static_assert(4 * MI % WN == 0, "the waves of a shared ring load equal parts of a stage");
   static_assert((4 * MI) % WK == 0, "waves finish whole row groups");
@@ -703,7 +704,7 @@ __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_tn_frag(const TnArgs a
     load_a(IC<0>{}, t_begin);
     load_b(IC<0>{}, t_begin);
     // the LoRA term du A of every segment starts the accumulators (of the last K range)
-    if (EPI != TN_PARTIAL_F32 && z == Z - 1) {
+    if (!RAW && z == Z - 1) {
       const int q0 = 8 * h, r = a.r;
       const bool keep = q0 < r;
       for (int s = 0; s < a.nseg; ++s) {
@@ -805,12 +806,12 @@ __global__ __launch_bounds__(64 * WN * WK, 2) void k_gemm_tn_frag(const TnArgs a
       run(IC<0>{});
     return;
   }
-  const size_t plane = EPI == TN_PARTIAL_F32 ? (size_t)tl.z * a.M * ldo : 0;
+  const size_t plane = RAW ? (size_t)tl.z * a.M * ldo : 0;
   const rsrc_t rO = EPI == TN_ACT_BWD      ? make_rsrc((u16*)a.g + (size_t)m0 * ldo, osz * 2)
                     : EPI == TN_STORE_BF16 ? make_rsrc((u16*)a.outb + (size_t)m0 * ldo, osz * 2)
                                            : make_rsrc(a.out + plane + (size_t)m0 * ldo, osz * 4);
   const rsrc_t rU = EPI == TN_ACT_BWD ? make_rsrc((u16*)a.u + (size_t)m0 * ldo, osz * 2) : rO;
-  constexpr int ESZ = EPI == TN_STORE_F32 || EPI == TN_PARTIAL_F32 ? 4 : 2;
+  constexpr int ESZ = RAW || EPI == TN_STORE_F32 ? 4 : 2;
   const uint32_t o0 = n0 < Kout ? (uint32_t)(4 * h * ldo + n0) * ESZ : 0x80000000u;
   const uint32_t o1 = n1 < Kout ? (uint32_t)(4 * h * ldo + n1) * ESZ : 0x80000000u;
   auto st16 = [&](rsrc_t r, uint32_t vo, int so, float v) {
@@ -923,6 +924,7 @@ constexpr MidCfg kMidTn[] = {
     {2, 1, 2, 4.0f, 0.65f, 0.37f, 0.7f}, {1, 1, 4, 3.5f, 0.50f, 0.52f, 0.0f},
     {2, 4, 1, 5.0f, 0.54f, 0.57f, 1.0f},  // 64 x 256
 };
+constexpr int kNtTiles = sizeof(kMidNt) / sizeof(MidCfg), kTnTiles = sizeof(kMidTn) / sizeof(MidCfg);
 struct MidPlan {
   int cfg, splits;
 };
@@ -974,14 +976,14 @@ MidPlan mid_plan_nt(int M, const int* Ns, int nseg, int K, bool gated, bool logi
   int width = 0;
   for (int s = 0; s < nseg; ++s) width += Ns[s];
   // (the logits' statistics take whole rows of a wave: the widest tile)
-  return mid_plan(kMidNt, logits ? 1 : (int)(sizeof(kMidNt) / sizeof(MidCfg)), M, K / BK, 2, logits ? 1 : kMaxSplits, width,
+  return mid_plan(kMidNt, logits ? 1 : kNtTiles, M, K / BK, 2, logits ? 1 : kMaxSplits, width,
                   followup, [&](const MidCfg& c) { return mid_columns(c, Ns, nseg, gated); });
 }
 
 MidPlan mid_plan_tn(int M, int Kout, const int* Ns, int nseg, int max_s, bool followup) {
   int kt = 0;
   for (int s = 0; s < nseg; ++s) kt += (Ns[s] + BK - 1) / BK;
-  return mid_plan(kMidTn, (int)(sizeof(kMidTn) / sizeof(MidCfg)), M, kt, 1, max_s, Kout, followup,
+  return mid_plan(kMidTn, kTnTiles, M, kt, 1, max_s, Kout, followup,
                   [&](const MidCfg& c) { return (Kout + 64 * c.wn - 1) / (64 * c.wn); });
 }
 
@@ -1024,48 +1026,44 @@ int gemm_tn_frag_splits(int M, int Kout, const int* Ns, int nseg, int max_s, boo
   return mid_plan_tn(M, Kout, Ns, nseg, max_s, followup).splits;
 }
 
-hipError_t launch_gemm_nt_mid(const NtArgs& a0, int epi, int S, double flops, double bytes, hipStream_t st) {
-  NtArgs a = a0;
-  if (a.K % BK || a.lda % 8 || ((uintptr_t)a.X & 15) || !gemm_nt_mid_aligned(a)) return hipErrorInvalidValue;
-  int Ns[3];
-  for (int s = 0; s < a.nseg; ++s) Ns[s] = a.seg[s].N;
-  const bool logits = epi == NT_LOGITS, gated = a.gated && S == 1;
-  // the tile for S planes was planned with them; without (or after the caller dropped them) plan anew
-  MidPlan p = mid_plan_nt(a.M, Ns, a.nseg, a.K, a.gated, logits, a.norm_w != nullptr);
-  if (p.splits != S) {
-    int width = 0;
-    for (int s = 0; s < a.nseg; ++s) width += Ns[s];
-    p = mid_plan(kMidNt, logits ? 1 : (int)(sizeof(kMidNt) / sizeof(MidCfg)), a.M, a.K / BK, 2, 1, width, true,
-                 [&](const MidCfg& c) { return mid_columns(c, Ns, a.nseg, gated); });
+namespace {
+
+int nt_planes_width(const NtArgs& a) {
+  int w = 0;
+  for (int s = 0; s < a.nseg; ++s) w += a.seg[s].N;
+  return w;
+}
+
+// one forward product on tile configuration `cfg`, over S planes
+hipError_t run_nt(NtArgs a, int cfg, MidEpi epi, int S, const char* name, double flops, double bytes, hipStream_t st) {
+  const MidCfg& c = kMidNt[cfg];
+  int Ns[3], t = 0;
+  for (int s = 0; s < a.nseg; ++s) {
+    Ns[s] = a.seg[s].N;
+    a.seg[s].tile0 = t;
+    t += (Ns[s] + 64 * c.wn - 1) / (64 * c.wn);
   }
   a.lora_two = mid_lora_two(a.M, Ns, a.nseg);
-  const MidCfg& c = kMidNt[p.cfg];
-  int t = 0;
-  for (int s = 0; s < a.nseg; ++s) {
-    a.seg[s].tile0 = t;
-    t += (a.seg[s].N + 64 * c.wn - 1) / (64 * c.wn);
-  }
-  const dim3 grid(mid_columns(c, Ns, a.nseg, gated), (a.M + 32 * c.mi - 1) / (32 * c.mi), S);
-  const char* name = epi == NT_STORE_F16 ? "gemm_nt_f16out" : epi == NT_STORE_F32 ? "gemm_nt_f32out" : "gemm_nt_logits";
-#define MID_GO(MI, WN, WK, EPI) \
+  const dim3 grid(mid_columns(c, Ns, a.nseg, epi == MID_GATED), (a.M + 32 * c.mi - 1) / (32 * c.mi), S);
+#define MID_GO(MI, WN, WK, EPI)      \
   MEBP_TIMED(st, name, flops, bytes, \
              hipLaunchKernelGGL((k_gemm_nt_mid<MI, WN, WK, EPI>), grid, dim3(64 * WN * WK), 0, st, a))
-#define MID_EPI(MI, WN, WK)              \
-  do {                                   \
-    if (S > 1)                           \
-      MID_GO(MI, WN, WK, MID_PARTIAL);   \
-    else if (gated)                      \
-      MID_GO(MI, WN, WK, MID_GATED);     \
-    else if (epi == NT_STORE_F16)        \
-      MID_GO(MI, WN, WK, MID_F16);       \
-    else                                 \
-      MID_GO(MI, WN, WK, MID_F32);       \
+#define MID_EPI(MI, WN, WK)                             \
+  do {                                                  \
+    switch (epi) {                                      \
+      case MID_PLANES: MID_GO(MI, WN, WK, MID_PLANES); break; \
+      case MID_GATED: MID_GO(MI, WN, WK, MID_GATED); break;   \
+      case MID_F16: MID_GO(MI, WN, WK, MID_F16); break;       \
+      case MID_F32: MID_GO(MI, WN, WK, MID_F32); break;       \
+      default: return hipErrorInvalidValue;                   \
+    }                                                         \
   } while (0)
-  if (logits) {
+  if (epi == MID_LOGITS) {
+    if (cfg) return hipErrorInvalidValue;
     MID_GO(4, 4, 1, MID_LOGITS);
     return hipGetLastError();
   }
-  switch (p.cfg) {
+  switch (cfg) {
     case 0: MID_EPI(4, 4, 1); break;
     case 1: MID_EPI(4, 1, 4); break;
     case 2: MID_EPI(2, 1, 8); break;
@@ -1078,45 +1076,26 @@ hipError_t launch_gemm_nt_mid(const NtArgs& a0, int epi, int S, double flops, do
   return hipGetLastError();
 }
 
-hipError_t launch_gemm_tn_frag(const TnArgs& a, int epi, int S, double flops, double bytes, hipStream_t st) {
-  int Ns[3];
-  for (int s = 0; s < a.nseg; ++s) {
-    Ns[s] = a.seg[s].N;
-    if (a.seg[s].N % 8 || a.seg[s].ldg % 8 || ((uintptr_t)a.seg[s].G & 15)) return hipErrorInvalidValue;
-  }
-  if (a.Kout % 8 || !a.w16) return hipErrorInvalidValue;
-  // the tile from the plan that chose S planes; a plan of one plane where the caller dropped them
-  MidPlan p = mid_plan_tn(a.M, a.Kout, Ns, a.nseg, epi == TN_PARTIAL_F32 ? kMaxHeadSplits : kMaxSplits,
-                          epi == TN_PARTIAL_F32 || tn_followup(a, epi));
-  if (p.splits != S) p = mid_plan_tn(a.M, a.Kout, Ns, a.nseg, 1, true);
-  const MidCfg& c = kMidTn[p.cfg];
-  const int e = S > 1 ? TN_PARTIAL_F32 : epi;
-  TnArgs b = a;
-  b.lora_two = mid_lora_two(a.M, &a.Kout, 1);
-  if (S > 1 && epi != TN_PARTIAL_F32) {
-    b.out = a.part;
-    b.ldo = a.Kout;
-  }
+// one transposed product on tile configuration `cfg`, over S planes
+hipError_t run_tn(TnArgs a, int cfg, int epi, int S, const char* name, double flops, double bytes, hipStream_t st) {
+  const MidCfg& c = kMidTn[cfg];
+  a.lora_two = mid_lora_two(a.M, &a.Kout, 1);
   const dim3 grid((a.Kout + 64 * c.wn - 1) / (64 * c.wn), (a.M + 32 * c.mi - 1) / (32 * c.mi), S);
-  const char* name = epi == TN_PARTIAL_F32 ? "gemm_tn_probs_dh"
-                     : epi == TN_STORE_F32  ? "gemm_tn_f32out"
-                     : epi == TN_ACT_BWD    ? "gemm_tn_act_bwd"
-                                            : "gemm_tn_bf16out";
-#define FRAG_GO(MI, WN, WK, EPI) \
+#define FRAG_GO(MI, WN, WK, EPI)     \
   MEBP_TIMED(st, name, flops, bytes, \
-             hipLaunchKernelGGL((k_gemm_tn_frag<MI, WN, WK, EPI>), grid, dim3(64 * WN * WK), 0, st, b))
-#define FRAG_EPI(MI, WN, WK)                   \
-  do {                                         \
-    if (e == TN_PARTIAL_F32)                   \
-      FRAG_GO(MI, WN, WK, TN_PARTIAL_F32);     \
-    else if (e == TN_STORE_F32)                \
-      FRAG_GO(MI, WN, WK, TN_STORE_F32);       \
-    else if (e == TN_ACT_BWD)                  \
-      FRAG_GO(MI, WN, WK, TN_ACT_BWD);         \
-    else                                       \
-      FRAG_GO(MI, WN, WK, TN_STORE_BF16);      \
+             hipLaunchKernelGGL((k_gemm_tn_frag<MI, WN, WK, EPI>), grid, dim3(64 * WN * WK), 0, st, a))
+#define FRAG_EPI(MI, WN, WK)                                            \
+  do {                                                                  \
+    switch (epi) {                                                      \
+      case TN_PARTIAL_F32: FRAG_GO(MI, WN, WK, TN_PARTIAL_F32); break;  \
+      case TN_PLANES: FRAG_GO(MI, WN, WK, TN_PLANES); break;            \
+      case TN_STORE_F32: FRAG_GO(MI, WN, WK, TN_STORE_F32); break;      \
+      case TN_ACT_BWD: FRAG_GO(MI, WN, WK, TN_ACT_BWD); break;          \
+      case TN_STORE_BF16: FRAG_GO(MI, WN, WK, TN_STORE_BF16); break;    \
+      default: return hipErrorInvalidValue;                             \
+    }                                                                   \
   } while (0)
-  switch (p.cfg) {
+  switch (cfg) {
     case 0: FRAG_EPI(4, 4, 1); break;
     case 1: FRAG_EPI(4, 1, 4); break;
     case 2: FRAG_EPI(2, 1, 8); break;
@@ -1128,6 +1107,77 @@ hipError_t launch_gemm_tn_frag(const TnArgs& a, int epi, int S, double flops, do
 #undef FRAG_EPI
 #undef FRAG_GO
   return hipGetLastError();
+}
+
+MidPlan unsplit_nt(const NtArgs& a, const int* Ns, bool gated, bool logits) {
+  return mid_plan(kMidNt, logits ? 1 : kNtTiles, a.M, a.K / BK, 2, 1, nt_planes_width(a), true,
+                  [&](const MidCfg& c) { return mid_columns(c, Ns, a.nseg, gated); });
+}
+
+}  // namespace
+
+hipError_t launch_gemm_nt_mid(const NtArgs& a, int epi, int S, double flops, double bytes, hipStream_t st) {
+  if (a.K % BK || a.lda % 8 || ((uintptr_t)a.X & 15) || !gemm_nt_mid_aligned(a)) return hipErrorInvalidValue;
+  int Ns[3];
+  for (int s = 0; s < a.nseg; ++s) Ns[s] = a.seg[s].N;
+  const bool logits = epi == NT_LOGITS, gated = a.gated && S == 1;
+  // the tile for S planes was planned with them; without (or after the caller dropped them) plan anew
+  MidPlan p = mid_plan_nt(a.M, Ns, a.nseg, a.K, a.gated, logits, a.norm_w != nullptr);
+  if (p.splits != S) p = unsplit_nt(a, Ns, gated, logits);
+  const MidEpi e = logits ? MID_LOGITS : S > 1 ? MID_PLANES : gated ? MID_GATED : epi == NT_STORE_F16 ? MID_F16 : MID_F32;
+  const char* name = logits ? "gemm_nt_logits" : S > 1 ? "gemm_nt_planes" : epi == NT_STORE_F16 ? "gemm_nt_f16out" : "gemm_nt_f32out";
+  return run_nt(a, p.cfg, e, S, name, flops, bytes, st);
+}
+
+hipError_t launch_gemm_tn_frag(const TnArgs& a, int epi, int S, double flops, double bytes, hipStream_t st) {
+  int Ns[3];
+  for (int s = 0; s < a.nseg; ++s) {
+    Ns[s] = a.seg[s].N;
+    if (a.seg[s].N % 8 || a.seg[s].ldg % 8 || ((uintptr_t)a.seg[s].G & 15)) return hipErrorInvalidValue;
+  }
+  if (a.Kout % 8 || !a.w16) return hipErrorInvalidValue;
+  // the tile from the plan that chose S planes; a plan of one plane where the caller dropped them
+  MidPlan p = mid_plan_tn(a.M, a.Kout, Ns, a.nseg, epi == TN_PARTIAL_F32 ? kMaxHeadSplits : kMaxSplits,
+                          epi == TN_PARTIAL_F32 || tn_followup(a, epi));
+  if (p.splits != S) p = mid_plan_tn(a.M, a.Kout, Ns, a.nseg, S, true);
+  TnArgs b = a;
+  const bool planes = S > 1 && epi != TN_PARTIAL_F32;
+  if (planes) {
+    b.out = a.part;
+    b.ldo = a.Kout;
+  }
+  const char* name = planes                 ? "gemm_tn_planes"
+                     : epi == TN_PARTIAL_F32 ? "gemm_tn_probs_dh"
+                     : epi == TN_STORE_F32  ? "gemm_tn_f32out"
+                     : epi == TN_ACT_BWD    ? "gemm_tn_act_bwd"
+                                            : "gemm_tn_bf16out";
+  return run_tn(b, p.cfg, planes ? TN_PLANES : epi, S, name, flops, bytes, st);
+}
+
+hipError_t launch_gemm_nt_probe(int tile, const uint8_t* q4, const uint16_t* scale, int n_out, int n_in, const void* x,
+                                int M, float* out, hipStream_t st) {
+  NtArgs a{};
+  a.X = x; a.lda = n_in; a.M = M; a.K = n_in; a.nseg = 1;
+  a.seg[0].q4 = q4; a.seg[0].scale = scale; a.seg[0].N = n_out; a.seg[0].out = out; a.seg[0].ldo = n_out;
+  if (a.K % BK || !gemm_nt_mid_aligned(a) || tile >= kNtTiles) return hipErrorInvalidValue;
+  return run_nt(a, tile < 0 ? unsplit_nt(a, &n_out, false, false).cfg : tile, MID_F32, 1, "gemm_nt_f32out", 0.0, 0.0, st);
+}
+
+hipError_t launch_gemm_tn_probe(int tile, const uint8_t* q4, const uint16_t* scale, int n_out, int n_in, const void* g,
+                                int M, float* out, uint16_t* frags, bool write, hipStream_t st) {
+  if (tile >= kTnTiles) return hipErrorInvalidValue;
+  if (write) {
+    FragArgs f{};
+    f.seg[f.nseg++] = FragSeg{q4, scale, n_out, n_in, frags, 0};
+    const hipError_t e = launch_frag_weights(f, st);
+    if (e != hipSuccess) return e;
+  }
+  TnArgs a{};
+  a.M = M; a.Kout = n_in; a.nseg = 1; a.w16 = frags;
+  a.seg[0].G = (const bf16*)g; a.seg[0].ldg = n_out; a.seg[0].N = n_out;
+  a.out = out; a.ldo = n_in;
+  return run_tn(a, tile < 0 ? mid_plan_tn(M, n_in, &n_out, 1, 1, true).cfg : tile, TN_STORE_F32, 1, "gemm_tn_f32out", 0.0,
+                0.0, st);
 }
 
 }  // namespace mebp

@@ -104,7 +104,8 @@ bool nt_gated_fused(const NtArgs& a, int epi, int bn, int S);
 // Transposed orientation (input gradients): C[m][c] = sum_seg sum_n G_seg[m][n] * W_seg[n][c]
 // with W_seg int4 [N_seg][Kout/2]; reduction over the weight's output dim; G bf16 (bf16
 // MFMA operands).
-enum TnEpi { TN_STORE_F32 = 0, TN_ACT_BWD = 1, TN_PARTIAL_F32 = 2, TN_STORE_BF16 = 3 };
+// (TN_PLANES: the split planes of a layer product on fragments, set by its launcher)
+enum TnEpi { TN_STORE_F32 = 0, TN_ACT_BWD = 1, TN_PARTIAL_F32 = 2, TN_STORE_BF16 = 3, TN_PLANES = 4 };
 enum TnAMode { TN_A_BF16 = 0 };  // the A operand is a bf16 matrix
 
 struct TnSeg {
@@ -187,6 +188,13 @@ hipError_t launch_gemm_tn_big(const TnArgs& a, int epi, int amode, int bn, int S
 // large-tile kinds to launch_gemm_probe_big.
 hipError_t launch_gemm_probe(int kind, const uint8_t* q4, const uint16_t* scale, int n_out, int n_in, const void* x,
                              int M, float* out, hipStream_t st);
+// The kernels of gemm_mid.hip: tile = row of their table of configurations, or -1 for the one that
+// the plan of an unsplit product picks. The transposed one on the fragments in `frags`
+// (frag_elems), written first if `write`.
+hipError_t launch_gemm_nt_probe(int tile, const uint8_t* q4, const uint16_t* scale, int n_out, int n_in, const void* x,
+                                int M, float* out, hipStream_t st);
+hipError_t launch_gemm_tn_probe(int tile, const uint8_t* q4, const uint16_t* scale, int n_out, int n_in, const void* g,
+                                int M, float* out, uint16_t* frags, bool write, hipStream_t st);
 hipError_t launch_gemm_probe_big(int kind, const uint8_t* q4, const uint16_t* scale, int n_out, int n_in,
                                  const void* x, int M, float* out, hipStream_t st);
 

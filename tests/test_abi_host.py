@@ -274,3 +274,13 @@ def test_workspace_guard_mode_changes_the_layout_and_validates(built_lib):
     finally:
         assert L.mebp_set_workspace_guards(False) is True
     assert L.mebp_workspace_bytes(c, 2, 160) == plain
+
+
+def test_tile_kinds_refuse_what_their_kernels_do_not_take(built_lib):
+    w = L.MebpQ4(q4=0x1000, scale=0x2000)
+    g = lambda kind, n_out, n_in, wt=w: L.mebp_test_gemm(kind, wt, n_out, n_in, 0x400000, 32, 0x800000, 0, check=False)
+    assert g(L.TEST_GEMM_NT_MID + L.TEST_GEMM_NT_TILES, 64, 64) == L.MEBP_EINVAL
+    assert g(L.TEST_GEMM_TN_FRAG + L.TEST_GEMM_TN_TILES, 64, 64) == L.MEBP_EINVAL
+    assert g(L.TEST_GEMM_NT_MID, 64, 80) == L.MEBP_EUNSUPPORTED
+    assert g(L.TEST_GEMM_NT_MID, 64, 64, L.MebpQ4(q4=0x1000, scale=0x2002)) == L.MEBP_EUNSUPPORTED
+    assert g(L.TEST_GEMM_TN_FRAG, 65536, 1024) == L.MEBP_EUNSUPPORTED

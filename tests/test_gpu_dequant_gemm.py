@@ -1,8 +1,9 @@
 """Bit-exact check of the decompression that runs on the hot path: the int4 -> 16-bit
-conversion fused into every dequant-GEMM kernel (Algorithm 1, LazyLoadAndDecompressWeights;
-Sec. 3, base weight compression).
+conversion fused into every dequant-GEMM kernel, and the bf16 copy in operand order that the
+transposed products of most calls read (Algorithm 1, LazyLoadAndDecompressWeights; Sec. 3, base
+weight compression).
 
-Each production GEMM kernel is run through ``mebp_test_gemm`` on a one-hot activation
+Each GEMM kernel, in each tile configuration, is run through ``mebp_test_gemm`` on a one-hot activation
 (forward kernels) or a one-hot gradient (transposed kernels): every output is then a single
 product 1 * W_op with fp32 accumulation, i.e. exactly the operand the kernel decompressed.
 The forward kernels multiply fp16 operands, the transposed ones bf16, so the outputs must
@@ -123,3 +124,52 @@ def test_16bit_weight_mode_is_the_same_kernel(built_lib, gpu, fwd):
         outs.append(out)
     torch.cuda.synchronize()
     assert torch.equal(outs[0], outs[1])
+
+
+# The kernels of the configured shapes, in each tile configuration and in the one the library picks:
+# an odd number of reduction steps (fewer than a tile's K ranges take at the second shape) and of
+# 32-column blocks, ragged rows, and the aligned shape
+MID_SHAPES = [(592, 704, 808), (176, 64, 150), (1024, 512, 1100)]
+
+
+def _first_mismatch(got, exp):
+    bad = np.argwhere(got.view(np.uint32) != exp.view(np.uint32))
+    return bad.size == 0, f"{len(bad)} mismatches, first at {bad[0].tolist() if len(bad) else None}"
+
+
+@pytest.mark.parametrize("shape", MID_SHAPES, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("tile", [*range(L.TEST_GEMM_NT_TILES), L.TEST_GEMM_PLANNED])
+def test_forward_tiles_decompression_bit_exact(built_lib, gpu, tile, shape):
+    n_out, n_in, M = shape
+    q4, sb = _weights(n_out, n_in, seed=n_in + 3)
+    tq, ts, w = _upload(q4, sb, gpu)
+    x = torch.zeros((M, n_in), dtype=torch.float16, device=gpu)
+    x[torch.arange(M, device=gpu), torch.arange(M, device=gpu) % n_in] = 1.0
+    out = torch.full((M, n_out), float("nan"), dtype=torch.float32, device=gpu)
+    say("fused decompression, tile", tile, "n_out", n_out, "n_in", n_in, "M", M)
+    L.mebp_test_gemm(L.TEST_GEMM_NT_MID + tile, w, n_out, n_in, x.data_ptr(), M, out.data_ptr(),
+                     torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    ref = O.dequant_fp16_bits(q4, sb, n_in, 32).view(np.float16).astype(np.float32)
+    ok, msg = _first_mismatch(out.cpu().numpy(), ref[:, np.arange(M) % n_in].T)
+    assert ok, msg
+
+
+@pytest.mark.parametrize("shape", MID_SHAPES + SHAPES[:1], ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("tile", [*range(L.TEST_GEMM_TN_TILES), L.TEST_GEMM_PLANNED])
+def test_transposed_tiles_copy_bit_exact(built_lib, gpu, tile, shape):
+    n_out, n_in, M = shape
+    q4, sb = _weights(n_out, n_in, seed=n_out + 4)
+    tq, ts, w = _upload(q4, sb, gpu)
+    g = torch.zeros((M, n_out), dtype=torch.bfloat16, device=gpu)
+    g[torch.arange(M, device=gpu), torch.arange(M, device=gpu) % n_out] = 1.0
+    say("bf16 copy, tile", tile, "n_out", n_out, "n_in", n_in, "M", M)
+    ref = (O.dequant_bf16_bits(q4, sb, n_in, 32).astype(np.uint32) << 16).view(np.float32)
+    # with the copy written by the call, and once more on the copy that it left
+    for kind in (L.TEST_GEMM_TN_FRAG, L.TEST_GEMM_TN_FRAG_AGAIN):
+        out = torch.full((M, n_in), float("nan"), dtype=torch.float32, device=gpu)
+        L.mebp_test_gemm(kind + tile, w, n_out, n_in, g.data_ptr(), M, out.data_ptr(),
+                         torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        ok, msg = _first_mismatch(out.cpu().numpy(), ref[np.arange(M) % n_out, :])
+        assert ok, (kind, msg)
