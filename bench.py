@@ -87,12 +87,15 @@ KERNEL_PATTERNS = {
                       r"|k_gemm_nt_mid<(\d+, ){3}[03]>",
     "gemm_nt_f32out": r"k_gemm_nt(_big|_lds)?<(\d+, \d+, )?1(, (true|false))?(, \d+)?(, (true|false))?>"
                       r"|k_gemm_nt_mid<(\d+, ){3}1>",
+    "gemm_nt_planes": r"k_gemm_nt_mid<(\d+, ){3}4>",
     "gemm_nt_logits": r"k_gemm_nt(_big|_lds)?<(\d+, \d+, )?2(, (true|false))?(, \d+)?(, (true|false))?>"
                       r"|k_gemm_nt_mid<(\d+, ){3}2>",
     "gemm_tn_f32out": r"k_gemm_tn(_big|_lds)?<(\d+, )?0(, (true|false))?>|k_gemm_tn_frag<(\d+, ){3}0>",
     "gemm_tn_act_bwd": r"k_gemm_tn(_big|_lds)?<(\d+, )?1(, (true|false))?>|k_gemm_tn_frag<(\d+, ){3}1>",
     "gemm_tn_probs_dh": r"k_gemm_tn(_big|_lds)?<(\d+, )?2(, (true|false))?>|k_gemm_tn_frag<(\d+, ){3}2>",
     "gemm_tn_bf16out": r"k_gemm_tn(_big|_lds)?<(\d+, )?3(, (true|false))?>|k_gemm_tn_frag<(\d+, ){3}3>",
+    "gemm_tn_planes": r"k_gemm_tn_frag<(\d+, ){3}4>",
+    "frag_weights": r"k_frag_weights",
     "lora_rows": r"k_lora_rows<",
     "norm_lora": r"k_norm_lora<",
     "lora_outer": r"k_lora_outer<",

@@ -70,6 +70,21 @@ KERNELS = [
     ("k_lora_outer<true, 2>", "lora_outer"),
     ("k_attn_bwd_dkdv<64, 64>", "attn_bwd_dkdv"),
     ("k_attn_bwd_dq<256, 32, false>", "attn_bwd_dq"),
+    ("k_gemm_nt_mid<4, 4, 1, 0>", "gemm_nt_f16out"),
+    ("k_gemm_nt_mid<1, 1, 4, 1>", "gemm_nt_f32out"),
+    ("k_gemm_nt_mid<4, 4, 1, 2>", "gemm_nt_logits"),
+    ("k_gemm_nt_mid<4, 1, 4, 3>", "gemm_nt_f16out"),
+    ("k_gemm_nt_mid<2, 1, 8, 4>", "gemm_nt_planes"),
+    ("k_gemm_tn_frag<1, 1, 4, 0>", "gemm_tn_f32out"),
+    ("k_gemm_tn_frag<4, 1, 4, 1>", "gemm_tn_act_bwd"),
+    ("k_gemm_tn_frag<4, 1, 4, 2>", "gemm_tn_probs_dh"),
+    ("k_gemm_tn_frag<2, 4, 1, 3>", "gemm_tn_bf16out"),
+    ("k_gemm_tn_frag<2, 1, 4, 4>", "gemm_tn_planes"),
+    ("k_frag_weights", "frag_weights"),
+    ("k_norm_lora<3, 2>", "norm_lora"),
+    ("k_norm_plain<2>", None),
+    ("k_attn_bwd_both<64, 64, 64, true>", "attn_bwd_both"),
+    ("k_attn_bwd_reduce", None),
     ("k_nt_finalize<0>", None),
     ("k_tn_finalize_norm", None),
     ("k_ce_probs", None),
