@@ -756,8 +756,10 @@ hipError_t norm_lora_down(const Ctx& x, const mebp_layer_lora* lora, const float
   NormLoraArgs a{};
   a.x = src; a.w = w; a.y = dst;
   a.M = x.D.N; a.K = x.D.d; a.r = x.D.r; a.eps = x.c->rms_eps;
-  // (the recompute that runs beside a backward keeps two launches: the step of 24 layers at 256
-  // tokens takes 7.02 ms with them and 7.16 with one, whose 16 workgroups hold up the other stream)
+  // (the recompute that runs beside a backward keeps two launches: one, with its few workgroups, holds
+  // up the other stream. Whole steps as one graph, two launches against one: 0.5B 100 tokens 5.19 and
+  // 5.28 ms, 256 5.75 and 5.85, 512 8.72 and 8.86, 3 x 333 11.29 and 11.46, 1B 256 8.14 and 8.08, 512
+  // 12.00 and 12.11, 1.5B 300 13.26 and 13.28, 4 x 512 32.5 and 33.1)
   const bool beside = x.split_set != 0;
   for (int p : ps) {
     if (beside || !adapted(x, p)) continue;

@@ -533,8 +533,10 @@ __global__ void k_fill_i32(int* p, int n, int v) {
 // token splits of an outer launch with `cols` columns over all groups. Up to 4096 tokens the
 // waves split the tokens (TS), over the grid too from 2048 on (below, the reduce launch would
 // cost as much as it saves); beyond, about 768 workgroups side by side, each with eight steps at
-// least (the four launches and reductions of a layer: 4096 tokens, 1536 wide, 119 us with TS and
-// 156 without; 16384 tokens, 2560 wide, 516 us with TS and 443 without).
+// least. Layer backward, side by side against TS (us): 2400 tokens 0.5B 620 and 593, 1.5B 1068 and
+// 1043; 3300 0.5B 745 and 717, 1B 1044 and 1022; 4096 0.5B 839 and 814; then within 2 % either way
+// up to 8192 (5200 0.5B 1095 and 1072, 1.5B 1789 and 1787, 6000 1B 1173 and 1156, 7200 4B 4124 and
+// 4174); 16384 4B, the outer launches alone, 443 and 516.
 constexpr int kOuterTsSteps = 64;
 int outer_splits(int M, int cols) {
   const int steps = (M + LO_M - 1) / LO_M, ts = steps <= kOuterTsSteps, wide = ts ? LO_C : LO_C * LO_W;
