@@ -13,10 +13,12 @@ import numpy as np
 import pytest
 import torch
 
+import oracle as O
 from mebp_inputs import ALL7, PROJ, Config, layer_input, make_inputs
+from paper_2510_03425_amd import _lib as L
 from paper_2510_03425_amd.device import DeviceModel, slot_index
 
-from gpu_util import say
+from gpu_util import TOL, rel_l2, say, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -80,3 +82,29 @@ def test_lora_terms_keep_fp32(built_lib, gpu, case):
             close(name, got, sum(du[p] @ A[p] for p in ps))
             seen += 1
     say("gradients seen", seen)
+
+
+def test_outer_products_in_less_scratch_than_planned(built_lib, gpu):
+    """The gate / up launch of dB and dA plans 12 token splits here and the workspace has room for 9.
+    Bound: bf16 operands, as in every layer test; the last tokens weigh 40 times the others, so that a
+    split left out is an error of order one."""
+    b, t, d, f, r = 13, 500, 64, 6912, 8
+    cfg = Config(name="outer", n_layers=1, hidden=d, n_heads=1, n_kv_heads=1, head_dim=64, ffn=f, vocab=0, act="silu",
+                 lora_rank=r, lora_alpha=2.0 * r, lora_modules=ALL7, batch=b, seq=t)
+    inp = make_inputs(cfg, seed=9, norm="random")
+    x, dy = layer_input(cfg, 16)
+    dy[-3:] *= 40
+    dm = DeviceModel(inp, device=str(gpu))
+    lo, hi = (L.mebp_workspace_offset(dm.ccfg, b, t, slot_index(n)) for n in ("lora_part", "rope_global"))
+    assert (hi - lo) // (2 * (d + f) * r * 4) == 9
+    tx, tdy = torch.from_numpy(x).to(gpu), torch.from_numpy(dy).to(gpu)
+    dx = torch.full_like(tx, float("nan"))
+    say("outer products in less scratch")
+    dm.layer_backward(0, tx, tdy, dx)
+    torch.cuda.synchronize()
+    dx_ref, g_ref = O.layer_backward(cfg, 0, O.decompress_layer(cfg, inp, 0), x, dy)
+    errs = {"dx": rel_l2(to_np(dx) - dy, dx_ref - dy)}
+    for p, (dA, dB) in g_ref.items():
+        errs["dA_" + p], errs["dB_" + p] = rel_l2(to_np(dm.dA[0][p]), dA), rel_l2(to_np(dm.dB[0][p]), dB)
+    say("rel-L2", {k: f"{v:.2e}" for k, v in errs.items()})
+    assert max(errs.values()) <= TOL, errs
