@@ -135,7 +135,7 @@ void add_nt(PlaneFloats* p, int M, int K, std::initializer_list<int> Ns, bool ga
   const size_t q4 = gemm_part_floats(M, ncat, plan_nt(M, v, n, K, NT_STORE_F32).splits);
   p->nt_q4 = std::max(p->nt_q4, q4);
   size_t m = q4;
-  if (gemm_nt_mid_ok(K)) {
+  if (gemm_nt_mid_ok(M, K)) {
     const int s0 = gemm_nt_mid_splits(M, v, n, K, gated, false), s1 = n > 1 ? s0 : gemm_nt_mid_splits(M, v, n, K, false, true);
     m = gemm_part_floats(M, ncat, std::max(s0, s1));
   }
@@ -304,9 +304,9 @@ bool make_layout(const mebp_config* c, int B, int T, Layout* L, bool static_call
                elems[3] = {0, std::max({gu, qkv, frag_elems(D, FF), frag_elems(D, Q)}),
                            frag_elems(D, FF) + gu + frag_elems(D, Q) + qkv},
                lm_elems = V ? frag_elems((int)Vc, D) : 0, most = 0xffffffffu / 2;
-  const bool can = elems[FRAG_EACH] <= most;
+  const bool can = elems[FRAG_EACH] <= most && gemm_mid_rows_ok(M);
   const int Vl = V ? (int)(V % Vc ? V % Vc : Vc) : 0;
-  const bool lm_can = V && lm_elems <= most && large_tile_elems(M, D, {(int)Vc}, true);
+  const bool lm_can = V && lm_elems <= most && gemm_mid_rows_ok(M) && large_tile_elems(M, D, {(int)Vc}, true);
 
   // bytes of the route's own slots, and of a whole layout (without guards)
   auto set_route = [&](const Route& k, bool lm) {
@@ -1760,7 +1760,7 @@ int mebp_test_gemm(int32_t kind, const mebp_q4* w, int32_t n_out, int32_t n_in, 
   if (n_in % 16 || n_out % 16) return fail(MEBP_EUNSUPPORTED, "n_in %d / n_out %d not multiples of 16", n_in, n_out);
   if ((e = check_act(x, "x")) || (e = check_act(out, "out"))) return e;
   if (nt_mid) {
-    if (!gemm_nt_mid_ok(n_in) || !aligned(w->scale, 4))
+    if (!gemm_nt_mid_ok(M, n_in) || !aligned(w->scale, 4))
       return fail(MEBP_EUNSUPPORTED, "n_in %d not a multiple of 64 or scales not 4-byte aligned", n_in);
     HIP_TRY(launch_gemm_nt_probe(tile, w->q4, w->scale, n_out, n_in, x, M, out, (hipStream_t)stream));
     return MEBP_OK;

@@ -1007,8 +1007,8 @@ DEV void sched_tn_step_w16() {
 }
 
 // W16: the weights are bf16 values [N][Kout] (seg.q4 points at them, no scales), moved into
-// the transposed LDS tile without decompression (the same operands as the int4 kernel: what
-// mebp_test_gemm measures the decompression with).
+// the transposed LDS tile without decompression (the same operands as the int4 kernel; reached by
+// mebp_test_gemm alone).
 template <int BN, int EPI, bool W16 = false>
 __global__ __launch_bounds__(NTH, 1) void k_gemm_tn_big(const TnArgs a) {
   constexpr int NJ = BN / 64;

@@ -925,6 +925,9 @@ constexpr MidCfg kMidTn[] = {
     {2, 4, 1, 5.0f, 0.54f, 0.57f, 1.0f},  // 64 x 256
 };
 constexpr int kNtTiles = sizeof(kMidNt) / sizeof(MidCfg), kTnTiles = sizeof(kMidTn) / sizeof(MidCfg);
+// row tiles of a launch (the y dimension of a grid takes 65535 workgroups): beyond 8 million tokens
+// the 128-row tiles are too many, and the 256-row ones of the other kernels take over
+constexpr int kMaxRowTiles = 65535;
 struct MidPlan {
   int cfg, splits;
 };
@@ -944,6 +947,7 @@ MidPlan mid_plan(const MidCfg* cfgs, int n, int M, int ksteps, int unit, int max
   float bt = 1e30f;
   for (int i = 0; i < n; ++i) {
     const MidCfg& c = cfgs[i];
+    if ((M - 1) / (32 * c.mi) >= kMaxRowTiles) continue;
     const int base = columns(c) * ((M + 32 * c.mi - 1) / (32 * c.mi));
     for (int S = 1; S <= max_s; S = S < 4 ? S + 1 : S + S / 2) {
       if (S > 1 && S * c.wk * 2 > ksteps) break;  // two steps per wave at least
@@ -1010,7 +1014,9 @@ hipError_t launch_frag_weights(FragArgs a, hipStream_t st) {
   return hipGetLastError();
 }
 
-bool gemm_nt_mid_ok(int K) { return K % BK == 0; }
+bool gemm_mid_rows_ok(int M) { return (M - 1) / 128 < kMaxRowTiles; }
+
+bool gemm_nt_mid_ok(int M, int K) { return K % BK == 0 && gemm_mid_rows_ok(M); }
 
 bool gemm_nt_mid_aligned(const NtArgs& a) {
   bool ok = true;
@@ -1117,7 +1123,8 @@ MidPlan unsplit_nt(const NtArgs& a, const int* Ns, bool gated, bool logits) {
 }  // namespace
 
 hipError_t launch_gemm_nt_mid(const NtArgs& a, int epi, int S, double flops, double bytes, hipStream_t st) {
-  if (a.K % BK || a.lda % 8 || ((uintptr_t)a.X & 15) || !gemm_nt_mid_aligned(a)) return hipErrorInvalidValue;
+  if (!gemm_nt_mid_ok(a.M, a.K) || a.lda % 8 || ((uintptr_t)a.X & 15) || !gemm_nt_mid_aligned(a))
+    return hipErrorInvalidValue;
   int Ns[3];
   for (int s = 0; s < a.nseg; ++s) Ns[s] = a.seg[s].N;
   const bool logits = epi == NT_LOGITS, gated = a.gated && S == 1;
@@ -1135,7 +1142,7 @@ hipError_t launch_gemm_tn_frag(const TnArgs& a, int epi, int S, double flops, do
     Ns[s] = a.seg[s].N;
     if (a.seg[s].N % 8 || a.seg[s].ldg % 8 || ((uintptr_t)a.seg[s].G & 15)) return hipErrorInvalidValue;
   }
-  if (a.Kout % 8 || !a.w16) return hipErrorInvalidValue;
+  if (a.Kout % 8 || !a.w16 || !gemm_mid_rows_ok(a.M)) return hipErrorInvalidValue;
   // the tile from the plan that chose S planes; a plan of one plane where the caller dropped them
   MidPlan p = mid_plan_tn(a.M, a.Kout, Ns, a.nseg, epi == TN_PARTIAL_F32 ? kMaxHeadSplits : kMaxSplits,
                           epi == TN_PARTIAL_F32 || tn_followup(a, epi));

@@ -896,7 +896,7 @@ hipError_t launch_gemm_nt(const NtArgs& a0, int epi, hipStream_t st, hipEvent_t 
   int Ns[3];
   for (int s = 0; s < a.nseg; ++s) Ns[s] = a.seg[s].N;
   const GemmPlan plan = plan_nt(a.M, Ns, a.nseg, a.K, epi);
-  const bool mid = gemm_nt_mid_ok(a.K) && gemm_nt_mid_aligned(a);
+  const bool mid = gemm_nt_mid_ok(a.M, a.K) && gemm_nt_mid_aligned(a);
   int S = !mid ? plan.splits : epi == NT_LOGITS ? 1 : gemm_nt_mid_splits(a.M, Ns, a.nseg, a.K, a.gated, a.norm_w);
   if (S > 1 && (!a.part || a.part_floats < gemm_part_floats(a.M, ncat, S))) S = 1;
   if (a.norm_w && a.seg[0].N > 4096) S = 1;  // the fused row norm keeps a row in one workgroup

@@ -87,8 +87,10 @@ GemmPlan plan_tn(int M, int Kout, const int* Ns, int nseg, bool softmax);  // so
 int gemm_logit_stat_tiles(int V);
 hipError_t launch_gemm_nt_big(const NtArgs& a, int epi, int bn, int S, double flops, double bytes, hipStream_t st);
 // the products of gemm_mid.hip (reductions that are a multiple of 64): one launch with every
-// epilogue of the arguments fused except the row norm
-bool gemm_nt_mid_ok(int K);
+// epilogue of the arguments fused except the row norm; both directions up to as many tokens as
+// their row tiles make a grid for
+bool gemm_mid_rows_ok(int M);
+bool gemm_nt_mid_ok(int M, int K);
 // ... whose scales are 4-byte aligned: they are loaded 16 bytes at a time, which a buffer load takes
 // from any dword; others go to the kernels that load them one by one
 bool gemm_nt_mid_aligned(const NtArgs& a);

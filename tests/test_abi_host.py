@@ -284,3 +284,11 @@ def test_tile_kinds_refuse_what_their_kernels_do_not_take(built_lib):
     assert g(L.TEST_GEMM_NT_MID, 64, 80) == L.MEBP_EUNSUPPORTED
     assert g(L.TEST_GEMM_NT_MID, 64, 64, L.MebpQ4(q4=0x1000, scale=0x2002)) == L.MEBP_EUNSUPPORTED
     assert g(L.TEST_GEMM_TN_FRAG, 65536, 1024) == L.MEBP_EUNSUPPORTED
+
+
+def test_many_tokens_leave_the_128_row_tiles(built_lib):
+    """A grid's second dimension takes 65535 workgroups: products of more row tiles than that (calls
+    are accepted up to 2^24 tokens) stay with the kernels of 256-row tiles."""
+    ok = built_lib._ZN4mebp14gemm_nt_mid_okEii  # bool mebp::gemm_nt_mid_ok(int M, int K)
+    ok.restype = C.c_bool
+    assert ok(65535 * 128, 64) and not ok(65535 * 128 + 1, 64) and not ok(1 << 24, 64) and not ok(128, 80)
