@@ -1,5 +1,5 @@
 // Large-tile int4 group-dequant GEMMs for many tokens (M = B*T in the thousands): the same
-// products as gemm_q4.hip (forward "NT" and transposed "TN", Algorithm 1's lazily
+// products, of the same calls, as gemm_q4.hip (forward "NT" and transposed "TN", Algorithm 1's lazily
 // decompressed weights fused into the operand load), with a tiling sized for MFMA
 // throughput rather than for latency.
 //

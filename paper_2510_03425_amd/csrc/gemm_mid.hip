@@ -1,6 +1,7 @@
 // Int4 group-dequant forward GEMMs whose reduction is a multiple of 64 (every configured
 // shape), with every epilogue of the layer fused (LoRA up-projection, RoPE, act(gate) * up,
-// residual, logits statistics): no partial plane and no finalize pass.
+// residual, logits statistics): no partial plane and no finalize pass where the reduction is not
+// split over the grid. Behind them the transposed products on bf16 weights in operand order.
 //
 // What bounded the kernels they replace: at few tokens the 128 x 128 tiles gave too few
 // workgroups, so the reduction was split over workgroups and the fp32 planes went through

@@ -1,5 +1,8 @@
 // Int4 group-dequant GEMMs on MFMA (gfx950), the lazy decompression of Algorithm 1
-// fused into the matrix products of every base projection and of the tied LM head.
+// fused into the matrix products of every base projection and of the tied LM head: for few
+// tokens and the calls that the kernels of gemm_mid.hip do not take (reductions that are no
+// multiple of 64, scales off 4 bytes; transposed products where the workspace has no room for
+// their weights in bf16). Also the dispatch over all of them, and the split planes' sums.
 //
 // Both orientations use one 128x128 output tile per 256-thread workgroup (2x2 waves of
 // 64x64, 16x16x32 MFMA, fp32 accumulation) and a K step of 64. Activations are staged
