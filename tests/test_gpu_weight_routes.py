@@ -94,3 +94,55 @@ def test_library_buffer_takes_the_same_route(built_lib, gpu, case):
     for p, (a, b) in ref.items():
         assert torch.equal(dm.dA[0][p], a) and torch.equal(dm.dB[0][p], b), p
     _check(cfg, inp, dm, x, dy, dx)
+
+
+# below 256 tokens the LM head keeps no copy of its own and a layer's lie in its logits: whole steps,
+# whose LM head and layers take turns there (dx0 is asked for, so every layer needs all its copies)
+STEP_CASES = [("qwen2.5-0.5b", 100, 1), ("gemma3-1b", 200, 4), ("qwen2.5-1.5b", 120, 0)]
+
+
+@pytest.mark.parametrize("case", STEP_CASES, ids=lambda c: f"{c[0]}-{c[1]}")
+def test_step_on_each_route(built_lib, gpu, case):
+    name, t, copies = case
+    cfg = CONFIGS[name].with_(batch=1, seq=t, n_layers=3)
+    inp = make_inputs(cfg, seed=7, norm="random")
+    dm = DeviceModel(inp, device=str(gpu))
+    dx0 = torch.full((dm.N, cfg.hidden), float("nan"), dtype=torch.float32, device=gpu)
+    say("step", case, "workspace", dm.ws_bytes)
+    assert _copies(lambda: dm.train_step(dx0)) == copies * cfg.n_layers
+    ref = O.train_step(cfg, inp, keep_ckpts=False)
+    errs = {"dx0": rel_l2(to_np(dx0), ref.dx0)}
+    for l in range(cfg.n_layers):
+        for p, (dA, dB) in ref.grads[l].items():
+            errs[f"dA{l}_{p}"], errs[f"dB{l}_{p}"] = rel_l2(to_np(dm.dA[l][p]), dA), rel_l2(to_np(dm.dB[l][p]), dB)
+    say("loss", dm.loss.item(), ref.loss, "worst", max(errs.values()))
+    assert abs(dm.loss.item() - ref.loss) <= 1e-3 * abs(ref.loss) and max(errs.values()) <= TOL, errs
+    # the same bits as a replayed graph, with eager steps between the replays, and with guards
+    eager = dm.loss.clone(), dx0.clone(), dm.grad_probe().clone()
+    same = lambda: all(torch.equal(a, b) for a, b in zip(eager, (dm.loss, dx0, dm.grad_probe())))
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    with torch.cuda.stream(side):
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=side):
+            dm.train_step(dx0)
+    torch.cuda.current_stream().wait_stream(side)
+    for i in range(3):
+        dx0.fill_(float("nan"))
+        say("graph replay", i)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert same()
+        dm.train_step(dx0)
+        torch.cuda.synchronize()
+        assert same()
+    prev = L.mebp_set_workspace_guards(True)
+    try:
+        dm = DeviceModel(inp, device=str(gpu))
+        dx0.fill_(float("nan"))
+        say("guards")
+        dm.train_step(dx0)
+        torch.cuda.synchronize()
+        assert same()
+    finally:
+        L.mebp_set_workspace_guards(prev)
